@@ -14,6 +14,30 @@ template <typename T> __device__ __forceinline__ T fexp2(T x);
 template <> __device__ __forceinline__ float fexp2<float>(float x) { return __builtin_amdgcn_exp2f(x); }
 template <> __device__ __forceinline__ double fexp2<double>(double x) { return exp2(x); }
 
+// 2^x in FP64: x = n + f with n the nearest integer, 2^f = 1 + f g(f) with g the polynomial
+// of degree 10 interpolating (2^f - 1) / f at the Chebyshev nodes of [-1/2, 1/2] (relative
+// error 8e-18; 0.8 ulp with the evaluation's rounding), scaled by 2^n.  0 below 2^-1100
+// (-infinity included), NaN stays NaN; x must not exceed 2^31.  About 18 operations against
+// the library's 26.
+__device__ __forceinline__ double exp2_fp64(double x) {
+  constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52: x + kMagic holds n in its low bits
+  const double t = x + kMagic;
+  const double f = x - (t - kMagic);
+  double r = 4.4549605981865186e-10;
+  r = fma(f, r, 7.072585949269223e-09);
+  r = fma(f, r, 1.0178062445845774e-07);
+  r = fma(f, r, 1.321544258792169e-06);
+  r = fma(f, r, 1.525273382983612e-05);
+  r = fma(f, r, 1.540353044173605e-04);
+  r = fma(f, r, 1.3333558146416936e-03);
+  r = fma(f, r, 9.618129107606888e-03);
+  r = fma(f, r, 5.55041086648216e-02);
+  r = fma(f, r, 2.4022650695910097e-01);
+  r = fma(f, r, 6.931471805599453e-01);
+  r = __builtin_amdgcn_ldexp(fma(f, r, 1.0), __double2loint(t));
+  return x < -1100.0 ? 0.0 : r;
+}
+
 constexpr double kLn2 = 0.69314718055994530942;
 
 // x log(E/x) for a count x > 0 and a rate E > 0: the part of the centred Poisson term that

@@ -137,3 +137,26 @@ def test_hessian_and_newton_step_with_per_patch_psf(fitted, fp64):
     thn, rn, stn, locn = th.cpu().numpy(), r.cpu().numpy(), st.cpu().numpy(), loc.cpu().numpy()
     for s in np.nonzero(mask)[0][:4]:
         check_step(m, prob.theta0, int(s), thn[s], rn[s], stn[s], locn[s], fp64)
+
+
+@pytest.mark.parametrize("side", [3, 5, 15, 17, 31, 33, 61, 63])
+@pytest.mark.parametrize("K", [1, 4])
+def test_psf_fit_grid_sizes(side, K):
+    """Grids whose columns fill the workgroup's row strips exactly, with idle threads, with
+    fewer rows than strips and with a partial last row pass (float64 on both sides: 1e-9)."""
+    say(f"case: psf fit side={side} K={K}")
+    rng = np.random.default_rng(side * 10 + K)
+    ax = np.arange(side) - 0.5 * (side - 1)
+    r2 = ax[:, None] ** 2 + ax[None, :] ** 2
+    s = 0.12 * side + 0.4
+    base = np.exp(-0.5 * r2 / s ** 2) + 0.3 * np.exp(-0.5 * r2 / (2.2 * s) ** 2)
+    eig = np.stack([base, base * ax[None, :] / side, base * ax[:, None] / side])[None]
+    coef = rng.uniform(-0.2, 0.2, (1, 3, 6))
+    coef[0, 0, 0] += 1.0
+    size = np.array([[100.0, 80.0]])
+    xy = rng.uniform(0, 1, (3, 2)) * size
+    out = api.psf_fit_at(api.Context(0), eig, coef, size, np.zeros(3, np.int32), xy, K, 6).cpu().numpy()
+    for f in range(3):
+        img = OP.psf_image(eig[0], coef[0], size[0, 0], size[0, 1], xy[f, 0], xy[f, 1])
+        assert _scale_err(out[f, :K], OP.fit_mixture(img, K, 6)).max() <= 1e-9
+        assert np.all(out[f, K:] == 0)
