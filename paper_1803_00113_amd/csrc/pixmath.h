@@ -10,10 +10,6 @@ namespace celmi {
 // ----------------------------------------------------------------------------------------
 // precision helpers
 
-template <typename T> __device__ __forceinline__ T fexp2(T x);
-template <> __device__ __forceinline__ float fexp2<float>(float x) { return __builtin_amdgcn_exp2f(x); }
-template <> __device__ __forceinline__ double fexp2<double>(double x) { return exp2(x); }
-
 // 2^x in FP64: x = n + f with n the nearest integer, 2^f = 1 + f g(f) with g the polynomial
 // of degree 10 interpolating (2^f - 1) / f at the Chebyshev nodes of [-1/2, 1/2] (relative
 // error 8e-18; 0.8 ulp with the evaluation's rounding), scaled by 2^n.  0 below 2^-1100
@@ -37,6 +33,10 @@ __device__ __forceinline__ double exp2_fp64(double x) {
   r = __builtin_amdgcn_ldexp(fma(f, r, 1.0), __double2loint(t));
   return x < -1100.0 ? 0.0 : r;
 }
+
+template <typename T> __device__ __forceinline__ T fexp2(T x);
+template <> __device__ __forceinline__ float fexp2<float>(float x) { return __builtin_amdgcn_exp2f(x); }
+template <> __device__ __forceinline__ double fexp2<double>(double x) { return exp2_fp64(x); }
 
 constexpr double kLn2 = 0.69314718055994530942;
 
