@@ -975,16 +975,10 @@ static hipError_t launch_maps_t(cel_plan* p, const Table<T>* tables, hipStream_t
 // Enqueue prep + fused + finalize for `nv` variants starting at variant v0 over either all
 // sources (cls < 0) or one colour class, with optional active mask.  Outputs go to the
 // plan's per-variant arrays.
-constexpr int kPointPixelsPerLane = 4;
-
 template <typename T>
 static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* theta_trial, int v0, int nv,
                                bool grad, int cls, const uint8_t* active, hipStream_t sm, bool prep_base,
-                               double* local_out, double* grad_out, int64_t theta_vstride = 0,
-                               const uint8_t* active_v = nullptr) {
-  // theta_vstride > 0: likelihood mode -- variant v's parameters at theta + v * theta_vstride,
-  // no differences, no KL, the pixel sums of variant v to local_out + v * S
-  const bool point = theta_vstride > 0;
+                               double* local_out, double* grad_out) {
   Table<T>* tables = reinterpret_cast<Table<T>*>(sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f);
   hipError_t e = hipSuccess;
   PrepArgs pa;
@@ -998,13 +992,10 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   pa.tables = tables;
   pa.n_patches = p->P;
   pa.trial_variant = p->trial_variant;
-  pa.fd = point ? 0 : p->fd_mode;
+  pa.fd = p->fd_mode;
   pa.sky_min = p->d_skymin;
   pa.patch_psf = p->d_patch_psf;
   pa.records = p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0;
-  pa.theta_vstride = theta_vstride;
-  pa.active_v = active_v;   // (launch variant, source) pairs to evaluate: the likelihood pass
-  pa.active_v_stride = p->S;
   phase_mark(p, 0, sm);
   if (prep_base) {   // variant 0 of every source and its moment maps (neighbours read these)
     pa.variant0 = 0;
@@ -1047,13 +1038,7 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   fa.active = active;
   fa.variant0 = v0;
   fa.img_npsf = p->d_npsf;
-  fa.active_v = active_v;
-  fa.active_v_stride = p->S;
-  // the likelihood pass (values only, often one type per candidate) takes 4 pixels per lane
-  // whatever the plan's setting: more independent work per wavefront for thin candidates
-  // (10.2 ms per 56 x 1000 candidates against 12.1 at 2 and 10.8 at 8)
-  const int ppl = point ? kPointPixelsPerLane : p->opt.pixels_per_lane;
-  e = launch_fused<T>(fa, p->nexp, p->ndev, ppl, grad, n_items, nv, sm);
+  e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, grad, n_items, nv, sm);
   if (e != hipSuccess) return e;
   phase_mark(p, 3, sm);
   FinalizeArgs fz;
@@ -1073,18 +1058,13 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   fz.images = p->d_images;
   fz.prior = p->d_prior;
   fz.want_grad = grad ? 1 : 0;
-  const bool direct = (v0 == 0 && nv == 1) || point;
+  const bool direct = v0 == 0 && nv == 1;
   fz.local = direct && local_out ? local_out : p->v_local + (int64_t)v0 * p->S;
   fz.own = p->v_own + (int64_t)v0 * p->S;
   fz.grad = direct && grad_out ? grad_out : p->v_grad + (int64_t)v0 * p->S * kThetaN;
   fz.out_variant_stride = p->S;
   fz.trial_variant = p->trial_variant;
-  fz.fd = point ? 0 : p->fd_mode;
-  fz.theta_vstride = theta_vstride;
-  fz.no_kl = point ? 1 : 0;
-  fz.active_v = active_v;
-  fz.active_v_stride = p->S;
-  if (point) fz.err = nullptr;   // a candidate's non-finite likelihood is a result, not a fault
+  fz.fd = p->fd_mode;
   if (cls >= 0) {
     // jobs = members of the class
     fz.n_jobs = (int)p->class_src[cls].size();
@@ -1348,9 +1328,69 @@ extern "C" cel_status cel_elbo_grad_plain(cel_ctx* ctx, const cel_plan* cplan, c
 }
 
 // Exact Poisson log-likelihood at point values (Section 3.1's target p(x | w_s, a_s, z_{-s})):
-// the other sources at z_fixed give the neighbour maps once; each chunk of candidates is a
-// set of variants of the objective's pixel pass over the selected sources' work items.
+// the other sources at z_fixed give the pixels' background once; each chunk of candidates is
+// a set of variants of the point pass over the selected sources' work items.
 namespace celmi {
+
+template <typename T>
+static PointArgs<T> point_args(cel_plan* p) {
+  PointArgs<T> pa;
+  std::memset(&pa, 0, sizeof(pa));
+  pa.tasks = p->d_tasks;
+  pa.order = p->d_class_tasks[p->n_colours];
+  pa.patches = p->d_patches;
+  pa.nbr_idx = p->d_nbr;
+  pa.tables = reinterpret_cast<const Table<T>*>(sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f);
+  pa.variant_stride = p->P;
+  pa.xs = sizeof(T) == 8 ? (const void*)p->d_xs64 : (const void*)p->d_xs;
+  pa.maps = sizeof(T) == 8 ? (void*)p->d_maps64 : (void*)p->d_maps;
+  pa.sums = p->slots;
+  pa.n_tasks = p->n_tasks;
+  pa.img_npsf = p->d_npsf;
+  pa.S = p->S;
+  return pa;
+}
+
+// the candidates' tables, pixel sums and per-source totals: theta row c at theta + c * 32 S
+template <typename T>
+static hipError_t enqueue_point(cel_plan* p, const double* theta, int nc, double* ll, const uint8_t* act,
+                                hipStream_t sm) {
+  const int cls = p->n_colours;
+  PrepArgs ta;
+  std::memset(&ta, 0, sizeof(ta));
+  ta.theta = theta;
+  ta.theta_vstride = (int64_t)p->S * kThetaN;
+  ta.patch_list = p->d_class_patches[cls];
+  ta.patches = p->d_patches;
+  ta.images = p->d_images;
+  ta.prof = p->d_prof;
+  ta.tables = sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f;
+  ta.n_patches = p->P;
+  ta.trial_variant = -1;
+  ta.sky_min = p->d_skymin;
+  ta.patch_psf = p->d_patch_psf;
+  ta.records = kRecUsedType;
+  ta.active_v = act;
+  ta.active_v_stride = p->S;
+  hipError_t e = launch_prep_tables<T>(ta, (int)p->class_patches[cls].size(), nc, sm);
+  PointArgs<T> pa = point_args<T>(p);
+  pa.active_v = act;
+  if (e == hipSuccess) e = launch_point<T>(pa, p->nexp, p->ndev, (int)p->class_tasks[cls].size(), nc, sm);
+  PointSumArgs sa;
+  std::memset(&sa, 0, sizeof(sa));
+  sa.sums = p->slots;
+  sa.n_tasks = p->n_tasks;
+  sa.n_jobs = (int)p->class_src[cls].size();
+  sa.job_src = p->d_class_src[cls];
+  sa.patch_ptr = p->d_patch_ptr;
+  sa.patches = p->d_patches;
+  sa.pix_const = p->d_pixconst;
+  sa.active_v = act;
+  sa.ll = ll;
+  sa.S = p->S;
+  if (e == hipSuccess) e = launch_point_sum(sa, nc, sm);
+  return e;
+}
 
 cel_status point_setup(cel_plan* p, const double* z_fixed, const std::vector<uint8_t>& m, int chunk, hipStream_t sm) {
   const bool fp64 = p->opt.pixel_fp64 != 0;
@@ -1367,6 +1407,10 @@ cel_status point_setup(cel_plan* p, const double* z_fixed, const std::vector<uin
   hipError_t e = stage_selection(p, m, true, sm);   // the selection, staged as the step class
   if (e == hipSuccess) e = launch_point_theta(z_fixed, S, p->d_pt_theta, nullptr, sm);
   if (e == hipSuccess) e = prep_base(p, p->d_pt_theta, sm, fp64);
+  const int n_items = (int)p->class_tasks[p->n_colours].size();
+  if (e == hipSuccess)
+    e = fp64 ? launch_background<double>(point_args<double>(p), n_items, sm)
+             : launch_background<float>(point_args<float>(p), n_items, sm);
   return e == hipSuccess ? CEL_OK : CEL_EHIP;
 }
 
@@ -1375,9 +1419,7 @@ hipError_t point_loglik(cel_plan* p, int n_cand, const double* z_cand, double* l
   const bool fp64 = p->opt.pixel_fp64 != 0;
   const int S = p->S;
   const int chunk = p->pt_cap;
-  const int cls = p->n_colours;
   double* th_cand = p->d_pt_theta + (int64_t)S * kThetaN;
-  const int64_t row = (int64_t)S * kThetaN;
   hipError_t e = hipSuccess;
   for (int c0 = 0; c0 < n_cand && e == hipSuccess; c0 += chunk) {
     const int nc = std::min(chunk, n_cand - c0);
@@ -1385,8 +1427,8 @@ hipError_t point_loglik(cel_plan* p, int n_cand, const double* z_cand, double* l
     if (e != hipSuccess) break;
     double* out = ll + (int64_t)c0 * S;
     const uint8_t* act_c = act ? act + (int64_t)c0 * S : nullptr;
-    e = fp64 ? enqueue_eval<double>(p, th_cand, nullptr, 0, nc, false, cls, nullptr, sm, false, out, nullptr, row, act_c)
-             : enqueue_eval<float>(p, th_cand, nullptr, 0, nc, false, cls, nullptr, sm, false, out, nullptr, row, act_c);
+    e = fp64 ? enqueue_point<double>(p, th_cand, nc, out, act_c, sm)
+             : enqueue_point<float>(p, th_cand, nc, out, act_c, sm);
     if (e == hipSuccess && mark_support) e = launch_support_masked(p->d_pt_ok, p->d_mask, S, (int64_t)nc * S, out, sm);
   }
   return e;

@@ -125,8 +125,6 @@ struct FusedArgs {
   const uint8_t* active;       // per source (nullptr = all)
   int32_t variant0;            // variant index of blockIdx.y == 0
   const int32_t* img_npsf;     // PSF components per image
-  const uint8_t* active_v;     // per (launch variant, source), row stride active_v_stride (nullptr = all)
-  int64_t active_v_stride;
   double unscale[2];           // set by the launcher: 1/c and 1/c^2 for the centre and covariance sums
 };
 
@@ -144,6 +142,38 @@ struct MapArgs {
   const void* base;            // variant-0 tables
   void* maps;                  // out: (E_s, V_s) per packed pixel
   const int32_t* img_npsf;
+};
+
+// Arguments of the point-likelihood kernels.
+template <typename T>
+struct PointArgs {
+  const DTask* tasks;
+  const int32_t* order;        // launch order -> task id (the selected sources' items)
+  const DPatch* patches;
+  const int32_t* nbr_idx;
+  const Table<T>* tables;      // [candidate][P]
+  int64_t variant_stride;      // tables per candidate (= P)
+  const void* xs;              // (count, sky) per packed pixel
+  void* maps;                  // (E_s, background) per packed pixel (k_background)
+  double* sums;                // [candidate][n_tasks]: a work item's pixel sum
+  int64_t n_tasks;
+  const int32_t* img_npsf;
+  const uint8_t* active_v;     // per (candidate, source), row stride S (nullptr = all)
+  int64_t S;
+};
+
+// Arguments of the per-source sum of the point likelihood.
+struct PointSumArgs {
+  const double* sums;          // [candidate][n_tasks]
+  int64_t n_tasks;
+  int32_t n_jobs;
+  const int32_t* job_src;
+  const int32_t* patch_ptr;
+  const DPatch* patches;
+  const double* pix_const;     // [P][2]
+  const uint8_t* active_v;
+  double* ll;                  // [candidate][S]
+  int64_t S;
 };
 
 }  // namespace celmi

@@ -28,6 +28,7 @@ struct PrepArgs {
 };
 constexpr int kRecHessian = 1;
 constexpr int kRecRuns = 2;
+constexpr int kRecUsedType = 4;   // no records of a type of weight exactly 0 (point candidates)
 
 struct FinalizeArgs {
   int32_t n_jobs;              // sources handled by this launch
@@ -53,10 +54,6 @@ struct FinalizeArgs {
   int32_t trial_variant;
   int32_t fd;
   int32_t* err;                // device condition word (CEL_DEVERR_*), may be null
-  int64_t theta_vstride;       // as in PrepArgs
-  int32_t no_kl;               // 1: the pixel sum alone (point likelihood), no KL
-  const uint8_t* active_v;     // per (launch variant, source), row stride active_v_stride (null = all)
-  int64_t active_v_stride;
 };
 
 template <typename T>
@@ -66,6 +63,13 @@ hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool
                         int n_variants, hipStream_t st);
 template <typename T>
 hipError_t launch_maps(const MapArgs& a, int nexp, int ndev, int ppl, int n_items, hipStream_t st);
+// point likelihood: the pixels' rate without their own source (once per fixed point), the
+// candidates' pixel sums per work item, and their per-source totals
+template <typename T>
+hipError_t launch_background(const PointArgs<T>& a, int n_items, hipStream_t st);
+template <typename T>
+hipError_t launch_point(const PointArgs<T>& a, int nexp, int ndev, int n_items, int n_cand, hipStream_t st);
+hipError_t launch_point_sum(const PointSumArgs& a, int n_cand, hipStream_t st);
 hipError_t launch_finalize(const FinalizeArgs& a, int n_variants, hipStream_t st);
 hipError_t launch_total(const double* own, int n, double* out, hipStream_t st);
 hipError_t launch_pixels(const DPatch* patches, const cel_image* images, const double* knots, const float* pixels,

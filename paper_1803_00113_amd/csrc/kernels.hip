@@ -17,6 +17,8 @@
 //   k_total        one workgroup: fixed-order sum of the per-source owned objectives
 #include <math.h>
 
+#include <type_traits>
+
 #include "device.h"
 #include "kernels.h"
 #include "pixmath.h"
@@ -138,7 +140,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     tb->hdr[11] = (T)muy;
   }
   // components: 4 star slots then 4 x 16 galaxy slots
-  for (int c = lane; c < kMaxPsf + kMaxPsf * 2 * kMaxProf; c += 64) {
+  const int n_slots = (a.records & kRecUsedType) && w[0] == 0.0 ? kMaxPsf : kMaxPsf + kMaxPsf * 2 * kMaxProf;
+  for (int c = lane; c < n_slots; c += 64) {
     // a star slot (c < kMaxPsf) or a galaxy slot: the same 2x2 algebra, one code path
     const bool star = c < kMaxPsf;
     const int g = c - kMaxPsf;
@@ -234,11 +237,12 @@ __device__ __forceinline__ void stage_records(const Table<T>* __restrict__ tb, i
 // that weight.
 template <typename T, int PPL, int NEXP, int NDEV>
 __device__ __forceinline__ void eval_values(const Table<T>* __restrict__ tb, const T (*__restrict__ rec)[2 * kMaxProf][8],
-                                            int K, const T* px, const T* py, const T* box, T* f0, T* f1) {
+                                            int K, const T* px, const T* py, const T* box, T* f0, T* f1,
+                                            bool with_star = true) {
   T fe[PPL], fd[PPL];
 #pragma unroll
   for (int i = 0; i < PPL; ++i) fe[i] = fd[i] = f1[i] = (T)0;
-  const bool use_gal = tb->hdr[2] != (T)0, use_star = tb->hdr[3] != (T)0;
+  const bool use_gal = tb->hdr[2] != (T)0, use_star = with_star && tb->hdr[3] != (T)0;
   for (int k = 0; k < K; ++k) {
     const T mx = tb->star[k][0], my = tb->star[k][1];
     T dx[PPL], dy[PPL], xx[PPL], xy[PPL], yy[PPL];
@@ -258,7 +262,7 @@ __device__ __forceinline__ void eval_values(const Table<T>* __restrict__ tb, con
     for (int j = 0; j < NEXP + NDEV; ++j) rc[j] = tb->rc2[k][j < NEXP ? j : kMaxProf + (j - NEXP)];
     // a type of weight 0 sees its components at infinite distance: all skipped
     const auto d2s = uniform_cut_key(use_star ? d2 : (T)INFINITY), d2g = uniform_cut_key(use_gal ? d2 : (T)INFINITY);
-    if (!(d2s > cut_key(tb->rc2s[k]))) {
+    if (with_star && !(d2s > cut_key(tb->rc2s[k]))) {
 #pragma unroll
       for (int i = 0; i < PPL; ++i) f1[i] += comp_value<T>(tb->sq[k], xx[i], xy[i], yy[i]);
     }
@@ -549,7 +553,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   const DTask task = a.tasks[t];
   const DPatch P = a.patches[task.patch];
   if (a.active && !a.active[P.src]) return;
-  if (a.active_v && !a.active_v[(int64_t)blockIdx.y * a.active_v_stride + P.src]) return;
   const Table<T>* __restrict__ tb = a.own + (int64_t)v * a.variant_stride + task.patch;
   const int K = a.img_npsf[P.img];
   const int lane = threadIdx.x;
@@ -732,6 +735,131 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 }
 
 // ----------------------------------------------------------------------------------------
+// The point likelihood (candidate point values of a source against fixed neighbours).  A
+// point's type weights are exactly 0 and 1 and its variances 0, so a pixel's rate is the
+// background (sky and neighbours at the fixed point), the same for every candidate, plus one
+// type's light, and its term is x log(E / x) - (E - x).
+
+// k_background: per pixel of the selected sources' work items, sky plus the neighbours'
+// moment maps E_t, into the second word of the pixel's own map entry -- V_s, which is 0 at
+// point values, and which no one reads until the maps are made again.  Bound by the latency
+// of a pixel's dependent reads: 256 threads per item, two pixels each.
+constexpr int kBackgroundThreads = 256;
+template <typename T>
+__global__ __launch_bounds__(kBackgroundThreads) void k_background(PointArgs<T> a) {
+  using T2 = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
+  const DTask task = a.tasks[a.order[xcd_position((int)blockIdx.x, (int)gridDim.x)]];
+  const DPatch P = a.patches[task.patch];
+  const T2* xs = reinterpret_cast<const T2*>(a.xs) + P.off;
+  T2* maps = reinterpret_cast<T2*>(a.maps);
+  for (int idx = task.pix_begin + (int)threadIdx.x; idx < task.pix_end; idx += kBackgroundThreads) {
+    const int row = idx / P.w, col = idx - row * P.w;
+    T E = (T)xs[idx].y;
+    for (int nb = P.nbr_begin; nb < P.nbr_end; ++nb) {
+      const DPatch Q = a.patches[a.nbr_idx[nb]];
+      const int cx = col + P.x0 - Q.x0, cy = row + P.y0 - Q.y0;
+      if ((unsigned)cx < (unsigned)Q.w && (unsigned)cy < (unsigned)Q.h) E += (T)maps[Q.off + (cy * Q.w + cx)].x;
+    }
+    maps[P.off + idx].y = E;
+  }
+}
+
+// k_point: one wavefront per (work item, candidate).  Bound by VALU issue: per component and
+// pixel an exponent of three products from the pixel's monomials, an exponential and a sum
+// (6 issue slots against 9 of the objective's pixel kernel, whose exponent goes through the
+// derivatives' u = P d and whose objective must equal the gradient pass's bit for bit), only
+// the candidate's own type evaluated, no neighbours, no variance term.  4 pixels per lane:
+// the components' records are read once for four pixels.  94 sources x 56 candidates
+// (1.5e6 active pixels): the call 0.72 ms through the objective's pixel kernel, 0.40 ms here.
+template <typename T, int PPL, int NEXP, int NDEV>
+__global__ __launch_bounds__(64) void k_point(PointArgs<T> a) {
+  using T2 = typename std::conditional<sizeof(T) == 8, double2, float2>::type;
+  const int t = a.order[xcd_position((int)blockIdx.x, (int)gridDim.x)];
+  const DTask task = a.tasks[t];
+  const DPatch P = a.patches[task.patch];
+  const int v = blockIdx.y;
+  if (a.active_v && !a.active_v[(int64_t)v * a.S + P.src]) return;
+  const Table<T>* __restrict__ tb = a.tables + (int64_t)v * a.variant_stride + task.patch;
+  const int K = a.img_npsf[P.img];
+  const int lane = threadIdx.x;
+  const bool galaxy = tb->hdr[2] != (T)0;
+  const T flux = galaxy ? tb->hdr[0] : tb->hdr[1];
+  __shared__ T rec[kMaxPsf][2 * kMaxProf][8];
+  if (galaxy) stage_records<T>(tb, K, lane, rec);
+  const T2* xs = reinterpret_cast<const T2*>(a.xs) + P.off;
+  const T2* bg = reinterpret_cast<const T2*>(a.maps) + P.off;
+  const int step = 64 * PPL;
+  const int step_rows = step / P.w, step_cols = step - step_rows * P.w;
+  int col[PPL], row[PPL];
+#pragma unroll
+  for (int i = 0; i < PPL; ++i) {
+    const int idx = task.pix_begin + i * 64 + lane;
+    row[i] = idx / P.w;
+    col[i] = idx - row[i] * P.w;
+  }
+  double acc = 0.0;
+  for (int base = task.pix_begin; base < task.pix_end; base += step) {
+    T x[PPL], E[PPL], px[PPL], py[PPL], f[PPL];
+#pragma unroll
+    for (int i = 0; i < PPL; ++i) {
+      const int idx = min(base + i * 64 + lane, task.pix_end - 1);
+      x[i] = (T)xs[idx].x;
+      E[i] = (T)bg[idx].y;
+      px[i] = (T)col[i];
+      py[i] = (T)row[i];
+      f[i] = (T)0;
+    }
+    T box[4];
+    run_box<T>(base, min(base + step, task.pix_end), P.w, box);
+    if (galaxy) {
+      T f1[PPL];
+      eval_values<T, PPL, NEXP, NDEV>(tb, rec, K, px, py, box, f, f1, false);
+    } else {
+      for (int k = 0; k < K; ++k) {
+        const T mx = tb->star[k][0], my = tb->star[k][1];
+        if (uniform_cut_key(box_dist2<T>(mx, my, box)) > cut_key(tb->rc2s[k])) continue;
+#pragma unroll
+        for (int i = 0; i < PPL; ++i) {
+          const T dx = px[i] - mx, dy = py[i] - my;
+          f[i] += comp_value<T>(tb->sq[k], dx * dx, (T)2 * dx * dy, dy * dy);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PPL; ++i) {
+      const T Ei = fma(flux, f[i], E[i]);
+      const T Tm = (x[i] > (T)0 ? x_log_ratio<T>(x[i], Ei) : (T)0) - (Ei - x[i]);
+      acc += base + i * 64 + lane < task.pix_end ? (double)Tm : 0.0;
+      col[i] += step_cols;
+      row[i] += step_rows;
+      if (col[i] >= P.w) {
+        col[i] -= P.w;
+        row[i] += 1;
+      }
+    }
+  }
+  const double s = wave_sum<double>(acc);
+  if (lane == 0) a.sums[(int64_t)v * a.n_tasks + t] = s;
+}
+
+// k_point_sum: per (source, candidate) a wavefront whose lanes take the source's patches;
+// fixed order
+__global__ __launch_bounds__(256) void k_point_sum(PointSumArgs a) {
+  const int job = blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63, v = blockIdx.y;
+  if (job >= a.n_jobs) return;
+  const int s = a.job_src[job];
+  if (a.active_v && !a.active_v[(int64_t)v * a.S + s]) return;
+  double local = 0.0;
+  for (int p = a.patch_ptr[s] + lane; p < a.patch_ptr[s + 1]; p += 64) {
+    double sm = 0.0;
+    for (int t = a.patches[p].task_begin; t < a.patches[p].task_end; ++t) sm += a.sums[(int64_t)v * a.n_tasks + t];
+    local += sm + a.pix_const[2 * p];
+  }
+  local = wave_sum<double>(local);
+  if (lane == 0) a.ll[(int64_t)v * a.S + s] = local;
+}
+
+// ----------------------------------------------------------------------------------------
 // k_finalize: per (variant, source) a wavefront whose lanes take the source's patches,
 // partial sums combined in a fixed pairing, lane 0 applying the shape chain rule.  The KL
 // term and its gradient do not depend on the pixels: launched with two wavefronts per
@@ -748,9 +876,8 @@ __global__ __launch_bounds__(128) void k_finalize(FinalizeArgs a) {
   const int vv = blockIdx.y;
   const int v = a.variant0 + vv;
   if (a.active && !a.active[s]) return;
-  if (a.active_v && !a.active_v[(int64_t)vv * a.active_v_stride + s]) return;
   double th[kThetaN];
-  load_theta(a.theta, a.theta_trial, a.theta_vstride, s, v, a.fd_step, th, a.trial_variant, a.fd);
+  load_theta(a.theta, a.theta_trial, 0, s, v, a.fd_step, th, a.trial_variant, a.fd);
   // the central-difference variants (1..54) carry the pixel part of the gradient only: the
   // KL part of the Hessian is taken analytically by the trust-region kernel
   const bool fd_variant = a.fd && v >= 1 && v <= 2 * kParamN;
@@ -766,7 +893,7 @@ __global__ __launch_bounds__(128) void k_finalize(FinalizeArgs a) {
   // KL by the whole wavefront; its gradient is subtracted from zeros and added to the pixel
   // gradient below (a - b and a + (0 - b) are the same number)
   auto kl_to_lds = [&](double* gk) {
-    const double kl = a.no_kl ? 0.0 : kl_source_wave(*a.prior, th, gk, fd_variant ? 0.0 : 1.0, lane);
+    const double kl = kl_source_wave(*a.prior, th, gk, fd_variant ? 0.0 : 1.0, lane);
     if (lane == 0) {
       klg[0] = kl;
       #pragma unroll
@@ -1094,6 +1221,30 @@ hipError_t launch_maps(const MapArgs& a, int nexp, int ndev, int ppl, int n_item
   return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_background(const PointArgs<T>& a, int n_items, hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_background<T>, dim3(n_items), dim3(kBackgroundThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_point(const PointArgs<T>& a, int nexp, int ndev, int n_items, int n_cand, hipStream_t st) {
+  if (n_items <= 0 || n_cand <= 0) return hipSuccess;
+  constexpr int kPointPixelsPerLane = 4;
+  if (nexp == 6 && ndev == 8)
+    hipLaunchKernelGGL((k_point<T, kPointPixelsPerLane, 6, 8>), dim3(n_items, n_cand), dim3(64), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_point<T, kPointPixelsPerLane, 8, 8>), dim3(n_items, n_cand), dim3(64), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_point_sum(const PointSumArgs& a, int n_cand, hipStream_t st) {
+  if (a.n_jobs <= 0 || n_cand <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_point_sum, dim3((a.n_jobs + 3) / 4, n_cand), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_finalize(const FinalizeArgs& a, int n_variants, hipStream_t st) {
   if (a.n_jobs <= 0 || n_variants <= 0) return hipSuccess;
   // the KL on its own wavefront while all blocks fit on the chip at once (two-wavefront
@@ -1245,6 +1396,10 @@ template hipError_t launch_prep_tables<float>(const PrepArgs&, int, int, hipStre
 template hipError_t launch_prep_tables<double>(const PrepArgs&, int, int, hipStream_t);
 template hipError_t launch_maps<float>(const MapArgs&, int, int, int, int, hipStream_t);
 template hipError_t launch_maps<double>(const MapArgs&, int, int, int, int, hipStream_t);
+template hipError_t launch_background<float>(const PointArgs<float>&, int, hipStream_t);
+template hipError_t launch_background<double>(const PointArgs<double>&, int, hipStream_t);
+template hipError_t launch_point<float>(const PointArgs<float>&, int, int, int, int, hipStream_t);
+template hipError_t launch_point<double>(const PointArgs<double>&, int, int, int, int, hipStream_t);
 template hipError_t launch_fused<float>(const FusedArgs<float>&, int, int, int, bool, int, int,
                                         hipStream_t);
 template hipError_t launch_fused<double>(const FusedArgs<double>&, int, int, int, bool, int, int,

@@ -144,3 +144,21 @@ def test_degenerate_calls():
     same = api.loglik(plan, zf_d, zf_d[None].clone()).cpu().numpy()[0]
     want = np.array([L.log_likelihood(m, zf, s, zf[s]) for s in range(prob.n_sources)])
     assert np.all(np.abs(same - want) <= 1e-5 * np.abs(want))
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("chunk", [64, 320, 4096])
+def test_work_item_sizes(chunk, fp64):
+    """Work items shorter than a wavefront's four pixels per lane, with a partial second pass,
+    and of whole patches: stars and galaxies against the oracle at the module's tolerances."""
+    say(f"case: loglik chunk={chunk} fp64={fp64}")
+    prob = gen.config1()
+    m = E.Model(prob)
+    zf = gen.truth_point(prob)
+    zc = gen.perturbed_points(zf, 4, 23)
+    zc[:, :, 2] = (np.arange(4)[:, None] + np.arange(prob.n_sources)[None]) % 2
+    ll = run(prob, zf, zc, pixel_fp64=fp64, chunk_pixels=chunk)
+    pairs = [(c, s) for c in range(4) for s in range(prob.n_sources)]
+    want = oracle(m, zf, zc, pairs)
+    err = np.abs(np.array([ll[c, s] for c, s in pairs]) - want) / np.abs(want)
+    assert np.all(err <= (1e-10 if fp64 else 1e-5)), err.max()
