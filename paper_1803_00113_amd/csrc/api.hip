@@ -1144,7 +1144,7 @@ hipError_t plain_eval(cel_plan* p, const double* theta, hipStream_t sm, bool fp6
 }
 
 template <typename T>
-static hipError_t prep_base_t(cel_plan* p, const double* theta, hipStream_t sm, bool hess) {
+static hipError_t prep_base_t(cel_plan* p, const double* theta, hipStream_t sm) {
   Table<T>* tables = reinterpret_cast<Table<T>*>(sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f);
   PrepArgs pa;
   std::memset(&pa, 0, sizeof(pa));
@@ -1159,19 +1159,18 @@ static hipError_t prep_base_t(cel_plan* p, const double* theta, hipStream_t sm, 
   pa.fd = p->fd_mode;
   pa.sky_min = p->d_skymin;
   pa.patch_psf = p->d_patch_psf;
-  pa.records = (p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0) | (hess ? kRecHessian : 0);
+  pa.records = p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0;
   hipError_t e = launch_prep_tables<T>(pa, p->P, 1, sm);
   if (e == hipSuccess) e = launch_maps_t<T>(p, tables, sm);
   return e;
 }
 
-hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64, bool hess) {
-  return fp64 ? prep_base_t<double>(p, theta, sm, hess) : prep_base_t<float>(p, theta, sm, hess);
+hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64) {
+  return fp64 ? prep_base_t<double>(p, theta, sm) : prep_base_t<float>(p, theta, sm);
 }
 
 template <typename T>
-static hipError_t prep_class_t(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm,
-                               bool hess) {
+static hipError_t prep_class_t(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm) {
   const int np = (int)p->class_patches[cls].size();
   if (np == 0) return hipSuccess;
   PrepArgs pa;
@@ -1189,14 +1188,12 @@ static hipError_t prep_class_t(cel_plan* p, const double* theta, int cls, const 
   pa.fd = p->fd_mode;
   pa.sky_min = p->d_skymin;
   pa.patch_psf = p->d_patch_psf;
-  pa.records = (p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0) | (hess ? kRecHessian : 0);
+  pa.records = p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0;
   return launch_prep_tables<T>(pa, np, 1, sm);
 }
 
-hipError_t prep_class(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm, bool fp64,
-                      bool hess) {
-  return fp64 ? prep_class_t<double>(p, theta, cls, active, sm, hess)
-              : prep_class_t<float>(p, theta, cls, active, sm, hess);
+hipError_t prep_class(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm, bool fp64) {
+  return fp64 ? prep_class_t<double>(p, theta, cls, active, sm) : prep_class_t<float>(p, theta, cls, active, sm);
 }
 
 hipError_t eval_any(cel_plan* p, const double* theta, const double* theta_trial, int v0, int nv, bool grad, int cls,

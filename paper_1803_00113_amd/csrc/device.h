@@ -41,8 +41,6 @@ enum Slot {
 // density stays below 2^-30 (float tables) or 2^-60 (double) of the patch's smallest sky
 // value (bounded through the covariance's largest eigenvalue); -1 = negligible everywhere
 // hdr[8..9]: e0, e1 = expm1(variance of log l given the type) (for the analytic Hessian)
-// gt[k][j]: tau, tau^2, then tau^2/2 tr(E1 P E2 P) for the S-parameter pairs (xx,xx),
-//           (xx,xy), (xx,yy), (xy,xy), (xy,yy), (yy,yy)
 // hdr[10..11]: the source centre mu in patch-local pixels
 // sq[k], gq[k][j]: (-log2(e)/2 (P_xx, P_xy, P_yy), log2 weight) -- the exponent of a
 //   component at offset d from its centre is q0 dx^2 + q1 (2 dx dy) + q2 dy^2 + q3
@@ -54,8 +52,9 @@ enum Slot {
 //   (from gq[k][j][0..2]) the own-source kernel forms the exponent as d . u' + q3 and the
 //   covariance derivative from u' u'^T - c^2 P = c^2 (u u^T - P); its mean and covariance
 //   sums are c and c^2 times the plain ones and are divided back once per slot row.  One
-//   component's eight values are 32 bytes, copied to LDS once per work item.
-// gal and gt are written only for the exact Hessian's preparations
+//   component's eight values are 32 bytes, copied to LDS once per work item; the exact
+//   Hessian's kernel forms its own records from them.
+// unused: keeps the table's size, on which the static scratch buffer's limit rests
 template <typename T>
 // The records the pixel kernels read for every component (header, star records, cut radii,
 // exponent records) come first and together, so that a wavefront's scalar loads of one
@@ -70,8 +69,7 @@ struct alignas(64) Table {
   T sq[kMaxPsf][4];
   T pad0[4];
   T gq[kMaxPsf][2 * kMaxProf][8];
-  T gal[kMaxPsf][2 * kMaxProf][4];
-  T gt[kMaxPsf][2 * kMaxProf][8];
+  T unused[kMaxPsf][2 * kMaxProf][12];
   T rq[kMaxPsf][1 + 2 * kMaxProf];
   T pad1[20];
 };

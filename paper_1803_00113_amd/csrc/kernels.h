@@ -22,11 +22,10 @@ struct PrepArgs {
   const double* sky_min;       // per patch: smallest sky value (component cut)
   int64_t theta_vstride;       // > 0: variant v reads theta + v * theta_vstride (per-variant points)
   const double* patch_psf;     // [P][kMaxPsf][6] per-patch PSF mixtures (null: the image's)
-  int32_t records;             // extra table records: kRecHessian (gt), kRecRuns (rq)
+  int32_t records;             // extra table records: kRecRuns (rq), kRecUsedType
   const uint8_t* active_v;     // per (launch variant, source), row stride active_v_stride (null = all)
   int64_t active_v_stride;
 };
-constexpr int kRecHessian = 1;
 constexpr int kRecRuns = 2;
 constexpr int kRecUsedType = 4;   // no records of a type of weight exactly 0 (point candidates)
 

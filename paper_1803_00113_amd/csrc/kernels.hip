@@ -193,22 +193,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       gs[1] = (T)(c2 * Pxy);
       gs[2] = (T)(c2 * Pyy);
       gs[3] = (T)(0.5 * tau);
-      if (!(a.records & kRecHessian)) continue;
-      T* r = tb->gal[k][j];
-      r[0] = pv[0];
-      r[1] = pv[1];
-      r[2] = pv[2];
-      r[3] = (T)lw;
-      const double h = 0.5 * tau * tau;
-      T* q = tb->gt[k][j];
-      q[0] = (T)tau;
-      q[1] = (T)(tau * tau);
-      q[2] = (T)(h * Pxx * Pxx);
-      q[3] = (T)(h * 2.0 * Pxx * Pxy);
-      q[4] = (T)(h * Pxy * Pxy);
-      q[5] = (T)(h * (2.0 * Pxy * Pxy + 2.0 * Pxx * Pyy));
-      q[6] = (T)(h * 2.0 * Pxy * Pyy);
-      q[7] = (T)(h * Pyy * Pyy);
     }
   }
 }

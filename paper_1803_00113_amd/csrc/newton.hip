@@ -172,12 +172,8 @@ __device__ void kl_hessian_wave(const DPrior& pr, const double* th, double (*B)[
 // For T(E, V) = -E + x (log E - V / (2 E^2)):  T_E = c_E, T_V = c_V,
 //   T_EE = -x/E^2 - 3 x V / E^4, T_EV = x / E^3, T_VV = 0, so per pixel
 //   d2T/du dv = T_EE E_u E_v + T_EV (E_u V_v + E_v V_u) + c_E E_uv + c_V V_uv.
-// f0, f1 and their first and second derivatives in (mu, S, pi) come from the Gaussian
-// identities (N = normal density with precision P, u = P (p - m)):
-//   dN/dmu = N u,  d2N/dmu dmu = N (u u^T - P),  dN/dC[dC] = N (u^T dC u - tr(P dC)) / 2,
-//   d2N/dmu dC[dC] = dN[dC] u - N P dC u,
-//   d2N/dC dC[dC1, dC2] = dN[dC1] dN[dC2] / N - N u^T dC1 P dC2 u + N tr(dC1 P dC2 P) / 2,
-// with dC = tau dS for a galaxy component.  The kernel sums G_u and the 66 entries Q_uv
+// f0, f1 and their first and second derivatives in (mu, S, pi) are sums of normal densities
+// times Hermite polynomials (gal_hess).  The kernel sums G_u and the 66 entries Q_uv
 // per work item; k_hess_finalize maps them to theta_s by the chain rule.
 
 constexpr int kPrim = 11;
@@ -196,64 +192,60 @@ struct PixH {
   T h1[3];   // xx, xy, yy
 };
 
-// one galaxy component of one profile: value, first derivatives (per profile) and the
-// profile-weighted second derivatives in (mu, S)
+// A galaxy component's record: with c the exponent's scale and P' = c^2 P,
+//   (c P_xx, c P_xy, c P_yy, log2 weight), (P'_xx, P'_xy, P'_yy, tau / 2), 2 P', 3 P'.
+constexpr int kHRec = 16;
+
+// One galaxy component of one profile.  All derivatives of N = weight * normal(p; m, C) in
+// (m, S) are spatial ones, for the normal obeys the heat equation dN/dC = d2N/dm dm / 2 and
+// dC = tau dS: with the Hermite polynomials H of u = P d,
+//   dN/dm_a = N u_a, d2N/dm_a dm_b = N H_ab, dN/dS_ab = (tau/2) N H_ab (twice that for the
+//   off-diagonal), d2N/dm_c dS_ab = (tau/2) N H_abc, d2N/dS_ab dS_cd = (tau/2)^2 N H_abcd,
+//   H_ab = u_a u_b - P_ab, H_abc = u_c H_ab - P_ac u_b - P_bc u_a,
+//   H_abcd = u_d H_abc - P_ad H_bc - P_bd H_ac - P_cd H_ab.
+// They depend on the index counts alone: 3 + 4 + 5 values serve the 3 + 6 + 6 second
+// derivatives, by recurrence, with u' = c u (order-n sums carry c^n, divided back per pixel).
+// gs: sums of (tau/2) N H'_ab; h2, h3, h4: profile-weighted sums of N H', (tau/2) N H',
+// (tau/2)^2 N H'.
 template <typename T>
-__device__ __forceinline__ void gal_hess(const T* q, T Pxx, T Pxy, T Pyy, T lw, const T* gt, T wP, T dx, T dy, T xx,
-                                         T xy, T yy, T& f, T* gm, T* gs, T* hmm, T* hms, T* hss) {
-  const T ux = fma(Pxx, dx, Pxy * dy);
-  const T uy = fma(Pxy, dx, Pyy * dy);
-  const T N = comp_value<T>(q, xx, xy, yy);
-  const T qxx = fma(ux, ux, -Pxx), qxy = fma(ux, uy, -Pxy), qyy = fma(uy, uy, -Pyy);
-  const T tau = gt[0], tau2 = gt[1];
-  const T Nh = (T)0.5 * tau * N;
+__device__ __forceinline__ void gal_hess(const T* q, T wP, T dx, T dy, T& f, T* gm, T* gs, T* h2, T* h3, T* h4) {
+  const T ux = fma(q[0], dx, q[1] * dy);
+  const T uy = fma(q[1], dx, q[2] * dy);
+  const T N = fexp2<T>(fma(dx, ux, fma(dy, uy, q[3])));
+  const T *P = q + 4, *P2 = q + 8, *P3 = q + 11;
+  const T xx = fma(ux, ux, -P[0]), xy = fma(ux, uy, -P[1]), yy = fma(uy, uy, -P[2]);
+  const T xxx = ux * (xx - P2[0]), xxy = fma(uy, xx, -P2[1] * ux);
+  const T xyy = fma(ux, yy, -P2[1] * uy), yyy = uy * (yy - P2[2]);
+  const T xxxx = fma(ux, xxx, -P3[0] * xx), xxxy = fma(uy, xxx, -P3[1] * xx);
+  const T xxyy = fma(uy, xxy, fma(-P2[1], xy, -P[2] * xx));
+  const T xyyy = fma(ux, yyy, -P3[1] * yy), yyyy = fma(uy, yyy, -P3[2] * yy);
   f += N;
   gm[0] = fma(N, ux, gm[0]);
   gm[1] = fma(N, uy, gm[1]);
-  const T Nxx = Nh * qxx, Nxy = (T)2 * Nh * qxy, Nyy = Nh * qyy;
-  gs[0] += Nxx;
-  gs[1] += Nxy;
-  gs[2] += Nyy;
-  const T Nw = N * wP;
-  hmm[0] = fma(Nw, qxx, hmm[0]);
-  hmm[1] = fma(Nw, qxy, hmm[1]);
-  hmm[2] = fma(Nw, qyy, hmm[2]);
-  const T Ntw = Nw * tau;
-  const T vxx_x = ux * Pxx, vxx_y = ux * Pxy;
-  const T vxy_x = fma(Pxx, uy, Pxy * ux), vxy_y = fma(Pxy, uy, Pyy * ux);
-  const T vyy_x = uy * Pxy, vyy_y = uy * Pyy;
-  const T w0e = Nxx * wP, w1e = Nxy * wP, w2e = Nyy * wP;
-  // each term is one fma into the entry's accumulator (the sign of the terms in N P rides on
-  // the operand)
-  hms[0] = fma(w0e, ux, hms[0]);
-  hms[3] = fma(w0e, uy, hms[3]);
-  hms[1] = fma(w1e, ux, hms[1]);
-  hms[4] = fma(w1e, uy, hms[4]);
-  hms[2] = fma(w2e, ux, hms[2]);
-  hms[5] = fma(w2e, uy, hms[5]);
-  hms[0] = fma(-Ntw, vxx_x, hms[0]);
-  hms[3] = fma(-Ntw, vxx_y, hms[3]);
-  hms[1] = fma(-Ntw, vxy_x, hms[1]);
-  hms[4] = fma(-Ntw, vxy_y, hms[4]);
-  hms[2] = fma(-Ntw, vyy_x, hms[2]);
-  hms[5] = fma(-Ntw, vyy_y, hms[5]);
-  const T q1 = (T)2 * qxy;
-  const T Nwt2 = Nw * tau2;
-  hss[0] = fma(Nwt2, (T)0.25 * qxx * qxx - ux * vxx_x, hss[0]);
-  hss[1] = fma(Nwt2, (T)0.25 * qxx * q1 - ux * vxy_x, hss[1]);
-  hss[2] = fma(Nwt2, (T)0.25 * qxx * qyy - ux * vyy_x, hss[2]);
-  hss[3] = fma(Nwt2, (T)0.25 * q1 * q1 - fma(uy, vxy_x, ux * vxy_y), hss[3]);
-  hss[4] = fma(Nwt2, (T)0.25 * q1 * qyy - uy * vxy_y, hss[4]);
-  hss[5] = fma(Nwt2, (T)0.25 * qyy * qyy - uy * vyy_y, hss[5]);
-#pragma unroll
-  for (int e = 0; e < 6; ++e) hss[e] = fma(Nw, gt[2 + e], hss[e]);
+  const T Nt = N * q[7], Nw = N * wP, Nwt = Nw * q[7], Nwtt = Nwt * q[7];
+  gs[0] = fma(Nt, xx, gs[0]);
+  gs[1] = fma(Nt, xy, gs[1]);
+  gs[2] = fma(Nt, yy, gs[2]);
+  h2[0] = fma(Nw, xx, h2[0]);
+  h2[1] = fma(Nw, xy, h2[1]);
+  h2[2] = fma(Nw, yy, h2[2]);
+  h3[0] = fma(Nwt, xxx, h3[0]);
+  h3[1] = fma(Nwt, xxy, h3[1]);
+  h3[2] = fma(Nwt, xyy, h3[2]);
+  h3[3] = fma(Nwt, yyy, h3[3]);
+  h4[0] = fma(Nwtt, xxxx, h4[0]);
+  h4[1] = fma(Nwtt, xxxy, h4[1]);
+  h4[2] = fma(Nwtt, xxyy, h4[2]);
+  h4[3] = fma(Nwtt, xyyy, h4[3]);
+  h4[4] = fma(Nwtt, yyyy, h4[4]);
 }
 
 template <typename T, int NEXP, int NDEV>
-__device__ __forceinline__ void eval_own_hess(const Table<T>* __restrict__ tb, int K, T px, T py, const T* box,
-                                              PixH<T>& o) {
+__device__ __forceinline__ void eval_own_hess(const Table<T>* __restrict__ tb,
+                                              const T (*__restrict__ rec)[2 * kMaxProf][kHRec], int K, T px, T py,
+                                              const T* box, PixH<T>& o) {
   T fe = 0, fd = 0, gme[2] = {0, 0}, gmd[2] = {0, 0}, gse[3] = {0, 0, 0}, gsd[3] = {0, 0, 0};
-  T hmm[3] = {0, 0, 0}, hms[6] = {0, 0, 0, 0, 0, 0}, hss[6] = {0, 0, 0, 0, 0, 0};
+  T h2[3] = {0, 0, 0}, h3[4] = {0, 0, 0, 0}, h4[5] = {0, 0, 0, 0, 0};
   T f1 = 0, g1x = 0, g1y = 0, h1[3] = {0, 0, 0};
   const T pi = tb->hdr[7], omp = (T)1 - pi;
   __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
@@ -279,16 +271,14 @@ __device__ __forceinline__ void eval_own_hess(const Table<T>* __restrict__ tb, i
     }
 #pragma unroll
     for (int j = 0; j < NEXP; ++j)
-      if (!(d2k > cut_key(rc[j])))
-        gal_hess<T>(tb->gq[k][j], tb->gal[k][j][0], tb->gal[k][j][1], tb->gal[k][j][2], tb->gal[k][j][3],
-                    tb->gt[k][j], omp, dx, dy, xx, xy, yy, fe, gme, gse, hmm, hms, hss);
+      if (!(d2k > cut_key(rc[j]))) gal_hess<T>(rec[k][j], omp, dx, dy, fe, gme, gse, h2, h3, h4);
 #pragma unroll
     for (int j = 0; j < NDEV; ++j)
-      if (!(d2k > cut_key(rc[NEXP + j])))
-        gal_hess<T>(tb->gq[k][kMaxProf + j], tb->gal[k][kMaxProf + j][0], tb->gal[k][kMaxProf + j][1],
-                    tb->gal[k][kMaxProf + j][2], tb->gal[k][kMaxProf + j][3], tb->gt[k][kMaxProf + j], pi, dx, dy, xx,
-                    xy, yy, fd, gmd, gsd, hmm, hms, hss);
+      if (!(d2k > cut_key(rc[NEXP + j]))) gal_hess<T>(rec[k][kMaxProf + j], pi, dx, dy, fd, gmd, gsd, h2, h3, h4);
   }
+  // the orders' scales divided back; the off-diagonal S derivatives count twice
+  constexpr double c1 = 1.0 / kExpScale;
+  constexpr T s1 = (T)c1, s2 = (T)(c1 * c1), s3 = (T)(c1 * c1 * c1), s4 = (T)(c1 * c1 * c1 * c1);
   o.f1 = f1;
   o.g1[0] = g1x;
   o.g1[1] = g1y;
@@ -296,29 +286,33 @@ __device__ __forceinline__ void eval_own_hess(const Table<T>* __restrict__ tb, i
   o.h1[1] = h1[1];
   o.h1[2] = h1[2];
   o.f0 = fma(pi, fd, omp * fe);
-  o.g0[0] = fma(pi, gmd[0], omp * gme[0]);
-  o.g0[1] = fma(pi, gmd[1], omp * gme[1]);
+  constexpr T m2[3] = {s2, (T)2 * s2, s2};
 #pragma unroll
-  for (int e = 0; e < 3; ++e) o.g0[2 + e] = fma(pi, gsd[e], omp * gse[e]);
-  o.g0[5] = fd - fe;
-  o.h0[zidx(0, 0)] = hmm[0];
-  o.h0[zidx(0, 1)] = hmm[1];
-  o.h0[zidx(1, 1)] = hmm[2];
+  for (int e = 0; e < 2; ++e) {
+    o.g0[e] = s1 * fma(pi, gmd[e], omp * gme[e]);
+    o.h0[zidx(e, 5)] = s1 * (gmd[e] - gme[e]);
+  }
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
-    o.h0[zidx(0, 2 + e)] = hms[e];
-    o.h0[zidx(1, 2 + e)] = hms[3 + e];
+    o.g0[2 + e] = m2[e] * fma(pi, gsd[e], omp * gse[e]);
+    o.h0[zidx(2 + e, 5)] = m2[e] * (gsd[e] - gse[e]);
   }
-  o.h0[zidx(2, 2)] = hss[0];
-  o.h0[zidx(2, 3)] = hss[1];
-  o.h0[zidx(2, 4)] = hss[2];
-  o.h0[zidx(3, 3)] = hss[3];
-  o.h0[zidx(3, 4)] = hss[4];
-  o.h0[zidx(4, 4)] = hss[5];
-  o.h0[zidx(0, 5)] = gmd[0] - gme[0];
-  o.h0[zidx(1, 5)] = gmd[1] - gme[1];
-#pragma unroll
-  for (int e = 0; e < 3; ++e) o.h0[zidx(2 + e, 5)] = gsd[e] - gse[e];
+  o.g0[5] = fd - fe;
+  o.h0[zidx(0, 0)] = s2 * h2[0];
+  o.h0[zidx(0, 1)] = s2 * h2[1];
+  o.h0[zidx(1, 1)] = s2 * h2[2];
+  o.h0[zidx(0, 2)] = s3 * h3[0];
+  o.h0[zidx(0, 3)] = (T)2 * s3 * h3[1];
+  o.h0[zidx(0, 4)] = s3 * h3[2];
+  o.h0[zidx(1, 2)] = s3 * h3[1];
+  o.h0[zidx(1, 3)] = (T)2 * s3 * h3[2];
+  o.h0[zidx(1, 4)] = s3 * h3[3];
+  o.h0[zidx(2, 2)] = s4 * h4[0];
+  o.h0[zidx(2, 3)] = (T)2 * s4 * h4[1];
+  o.h0[zidx(2, 4)] = s4 * h4[2];
+  o.h0[zidx(3, 3)] = (T)4 * s4 * h4[2];
+  o.h0[zidx(3, 4)] = (T)2 * s4 * h4[3];
+  o.h0[zidx(4, 4)] = s4 * h4[4];
   o.h0[zidx(5, 5)] = 0;
 }
 
@@ -338,6 +332,10 @@ struct HessArgs {
 // The float form is held to at most 168 VGPRs, three wavefronts per SIMD (its live set fits
 // there without spilling; at the two wavefronts that 194 VGPRs allowed the kernel stalled on
 // latency).  The double form keeps its natural allocation.
+// Bound by VALU issue, about 53 slots per galaxy component and pixel (84 when each second
+// derivative had its own formula and per-component constants came by scalar loads from the
+// table; the records are now formed once per item in LDS): Hessians of 200 sources (3.7e6
+// active pixels) 397 -> 304 us per call, a Newton step of 339 sources 964 -> 775 us.
 template <typename T, int NEXP, int NDEV>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_hess(HessArgs a) {
   const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
@@ -348,6 +346,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.tables) + task.patch;
   const int K = a.img_npsf[P.img];
   const int lane = threadIdx.x;
+  // the galaxy components' records, one component per lane
+  __shared__ __align__(16) T rec[kMaxPsf][2 * kMaxProf][kHRec];
+  static_assert(kMaxPsf * 2 * kMaxProf <= 64, "one component per lane");
+  if (lane < K * 2 * kMaxProf) {
+    const T* q = &tb->gq[0][0][0] + lane * 8;
+    T* r = &rec[0][0][0] + lane * kHRec;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = q[e];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      r[8 + e] = (T)2 * q[4 + e];
+      r[11 + e] = (T)3 * q[4 + e];
+    }
+  }
+  __syncthreads();
   const T L0 = tb->hdr[0], L1 = tb->hdr[1], w0 = tb->hdr[2], w1 = tb->hdr[3];
   const T e0 = tb->hdr[8], e1 = tb->hdr[9];
   const T w01 = w0 * w1, aa = w1, oma2 = (T)1 - (T)2 * aa;
@@ -377,7 +390,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     run_box<int>(base, min(base + 64, task.pix_end), P.w, ibox);
     const T box[4] = {(T)ibox[0], (T)ibox[1], (T)ibox[2], (T)ibox[3]};
     PixH<T> o;
-    eval_own_hess<T, NEXP, NDEV>(tb, K, (T)col, (T)row, box, o);
+    eval_own_hess<T, NEXP, NDEV>(tb, rec, K, (T)col, (T)row, box, o);
     T Eb = sky, Vb = 0;
     bool own = true;
     for (int nb = P.nbr_begin; nb < P.nbr_end; ++nb) {
@@ -1351,7 +1364,7 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   const bool analytic = !p->opt.hessian_fd;
   if (analytic) {
     // tables (and maps) at the iterate, then the exact Hessians with the gradients
-    e = maps_current ? prep_class(p, theta, cls, active, sm, fp64, true) : prep_base(p, theta, sm, fp64, true);
+    e = maps_current ? prep_class(p, theta, cls, active, sm, fp64) : prep_base(p, theta, sm, fp64);
     if (e == hipSuccess)
       e = enqueue_hessian(p, theta, p->d_class_tasks[cls], (int)p->class_tasks[cls].size(), p->d_class_src[cls], nsrc,
                           active, true, p->v_local, p->v_grad, p->d_hess, sm);
@@ -1620,7 +1633,7 @@ extern "C" cel_status cel_elbo_hessian(cel_ctx* ctx, const cel_plan* cplan, cons
   for (int s = 0; s < p->S; ++s) p->h_mask[s] = mask ? (mask[s] ? 1 : 0) : 1;
   hipError_t e = hipMemcpyAsync(p->d_mask, p->h_mask, p->S, hipMemcpyHostToDevice, sm);
   if (e == hipSuccess) e = hipEventRecord(p->mask_copied, sm);
-  if (e == hipSuccess) e = prep_base(p, theta, sm, fp64, true);
+  if (e == hipSuccess) e = prep_base(p, theta, sm, fp64);
   if (e == hipSuccess)
     e = enqueue_hessian(p, theta, p->d_order, (int)p->n_tasks, nullptr, p->S, p->d_mask, true,
                         elbo_local ? elbo_local : p->v_local, grad ? grad : p->v_grad, hess, sm);
