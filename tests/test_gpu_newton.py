@@ -162,3 +162,68 @@ def test_sweep_checkpoint_resume_identical(tmp_path):
     assert torch.equal(th_c, th_a) and torch.equal(r_c, r_a) and torch.equal(st_c, st_a)
     assert rep_c["elbo"] == rep_a["elbo"] and rep_c["next_colour"] == 0
     assert rep_b["n_newton_steps"] + rep_c["n_newton_steps"] == rep_a["n_newton_steps"]
+
+
+@pytest.mark.parametrize("logit", [None, -800.0])
+@pytest.mark.parametrize("radius", [1e-4, 0.05, 1.0, 20.0])
+def test_step_solves_its_subproblem(radius, logit):
+    """Steps inside the region, on its boundary, with an indefinite Hessian, and (type weight
+    exactly 0: a row of the Hessian and its gradient vanish) the hard case: the step's model
+    value is the oracle's optimum for the same gradient and Hessian (float64: 1e-10 of the
+    gain, and the gradient times the rounding with which theta holds the step), and it lies in
+    the region; a rejected step shrinks the radius to |p| / 4."""
+    say(f"case: trust-region subproblem, radius {radius}, type logit {logit}")
+    prob = tiny()
+    ctx = api.Context(0, pixel_fp64=True, hessian_fp64=True)
+    plan = api.Plan(ctx, prob)
+    th0 = prob.theta0.copy()
+    if logit is not None:
+        th0[:, 2] = logit
+    H, g, _ = (t.cpu().numpy() for t in api.elbo_hessian(plan, th0))
+    th = torch.as_tensor(th0, device="cuda").contiguous()
+    r = torch.full((prob.n_sources,), radius, dtype=torch.float64, device="cuda")
+    st, _ = api.newton_step(plan, th, r, plan.colours == 0)
+    thn, rn, stn = th.cpu().numpy(), r.cpu().numpy(), st.cpu().numpy()
+    for s in np.nonzero(plan.colours == 0)[0]:
+        po, lam, hard = NW.tr_subproblem(g[s, :27], H[s], radius)
+        value = lambda p: float(g[s, :27] @ p + 0.5 * p @ H[s] @ p)
+        p = thn[s, :27] - th0[s, :27]
+        say(f"  s={s} status {stn[s]} lam {lam:.3g} hard {hard} |p| {np.linalg.norm(p):.6g} gain {value(p):.6g}")
+        if stn[s] == _ffi.ST_ACCEPTED:
+            assert np.linalg.norm(p) <= radius * (1 + 1e-9)
+            held = 2.0 ** -53 * float(np.abs(g[s, :27]) @ np.abs(th0[s, :27]))
+            assert abs(value(p) - value(po)) <= 1e-10 * abs(value(po)) + held
+        else:
+            assert stn[s] == _ffi.ST_REJECTED and np.all(p == 0)
+            assert abs(rn[s] - 0.25 * np.linalg.norm(po)) <= 1e-8 * np.linalg.norm(po)
+
+
+@pytest.mark.parametrize("radius", [0.5, 2.0])
+def test_step_hard_case(radius):
+    """A type weight of exactly 0 at the other type's optimum, but for the flux: -H is singular
+    along the type logit and the unused type's coordinates with no gradient there, so the step
+    is completed to the boundary among them."""
+    say(f"case: trust-region hard case, radius {radius}")
+    prob = tiny()
+    ctx = api.Context(0, pixel_fp64=True, hessian_fp64=True)
+    plan = api.Plan(ctx, prob)
+    th0 = prob.theta0.copy()
+    th0[:, 2] = -800.0
+    th0 = torch.as_tensor(th0, device="cuda").contiguous()
+    api.sweep(plan, th0, n_sweeps=2, max_newton_iters=50)
+    th0 = th0.cpu().numpy()
+    th0[:, 3] += 1e-2
+    H, g, _ = (t.cpu().numpy() for t in api.elbo_hessian(plan, th0))
+    th = torch.as_tensor(th0, device="cuda").contiguous()
+    r = torch.full((prob.n_sources,), radius, dtype=torch.float64, device="cuda")
+    st, _ = api.newton_step(plan, th, r, plan.colours == 0)
+    thn, stn = th.cpu().numpy(), st.cpu().numpy()
+    for s in np.nonzero(plan.colours == 0)[0]:
+        po, lam, hard = NW.tr_subproblem(g[s, :27], H[s], radius)
+        value = lambda p: float(g[s, :27] @ p + 0.5 * p @ H[s] @ p)
+        p = thn[s, :27] - th0[s, :27]
+        say(f"  s={s} status {stn[s]} lam {lam:.3g} hard {hard} |p| {np.linalg.norm(p):.6g} gain {value(p):.6g}")
+        if stn[s] == _ffi.ST_ACCEPTED:
+            held = 2.0 ** -53 * float(np.abs(g[s, :27]) @ np.abs(th0[s, :27]))
+            assert np.linalg.norm(p) <= radius * (1 + 1e-9)
+            assert abs(value(p) - value(po)) <= 1e-10 * abs(value(po)) + held
