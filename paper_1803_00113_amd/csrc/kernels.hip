@@ -201,19 +201,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 // k_fused: the per-pixel hot loop
 
 // Copy the galaxy components' exponent records of the K PSF components of one table into
-// LDS (one wavefront; 16-byte vectors).  Each component's record is then one broadcast LDS
+// LDS (THREADS threads; 16-byte vectors).  Each component's record is then one broadcast LDS
 // read rather than a scalar-cache load: the tables of the wavefronts resident on a compute
 // unit exceed its scalar cache.
-template <typename T>
+template <typename T, int THREADS = 64>
 __device__ __forceinline__ void stage_records(const Table<T>* __restrict__ tb, int K, int lane,
                                               T (*rec)[2 * kMaxProf][8]) {
   constexpr int kVec = 16 / sizeof(T);   // values per 16-byte vector
   const int n = K * 2 * kMaxProf * 8 / kVec;
   const uint4* src = reinterpret_cast<const uint4*>(&tb->gq[0][0][0]);
   uint4* dst = reinterpret_cast<uint4*>(&rec[0][0][0]);
-  for (int i = lane; i < n; i += 64) dst[i] = src[i];
+  for (int i = lane; i < n; i += THREADS) dst[i] = src[i];
   __syncthreads();
 }
+
+// The pixel functions below write out their fused products: an expression left to the
+// compiler may be fused one way in one instantiation and another way in the next, and a
+// source's sums must not depend on which of them a launch takes.
 
 // Values of a source's star (f1) and galaxy (f0) light at PPL pixels (local coords of the
 // source's own patch).  Neighbour evaluation: no derivatives.  A type of weight exactly 0
@@ -223,6 +227,7 @@ template <typename T, int PPL, int NEXP, int NDEV>
 __device__ __forceinline__ void eval_values(const Table<T>* __restrict__ tb, const T (*__restrict__ rec)[2 * kMaxProf][8],
                                             int K, const T* px, const T* py, const T* box, T* f0, T* f1,
                                             bool with_star = true) {
+#pragma clang fp contract(off)
   T fe[PPL], fd[PPL];
 #pragma unroll
   for (int i = 0; i < PPL; ++i) fe[i] = fd[i] = f1[i] = (T)0;
@@ -265,7 +270,7 @@ __device__ __forceinline__ void eval_values(const Table<T>* __restrict__ tb, con
   }
   const T pi = tb->hdr[7];
 #pragma unroll
-  for (int i = 0; i < PPL; ++i) f0[i] = pi * fd[i] + ((T)1 - pi) * fe[i];
+  for (int i = 0; i < PPL; ++i) f0[i] = fma(pi, fd[i], ((T)1 - pi) * fe[i]);
 }
 
 // Own source: values and partial derivatives w.r.t. the pixel-frame centre mu, the
@@ -286,6 +291,7 @@ struct OwnPix {
 template <typename T, int PPL, int MODE>
 __device__ __forceinline__ void comp_own(const T* __restrict__ q, const T* __restrict__ r, const T* dx, const T* dy,
                                          T* f, T* gx, T* gy, T* sxx, T* sxy, T* syy) {
+#pragma clang fp contract(off)
   const T q0 = q[0], q1 = q[1], q2 = q[2], lw = q[3];
 #pragma unroll
   for (int i = 0; i < PPL; ++i) {
@@ -320,7 +326,6 @@ __device__ __forceinline__ void eval_own(const Table<T>* __restrict__ tb, const 
     o.fe[i] = o.gex[i] = o.gey[i] = o.sexx[i] = o.sexy[i] = o.seyy[i] = (T)0;
     o.fd[i] = o.gdx[i] = o.gdy[i] = o.sdxx[i] = o.sdxy[i] = o.sdyy[i] = (T)0;
   }
-  __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
   const bool use_gal = DERIV || tb->hdr[2] != (T)0, use_star = DERIV || tb->hdr[3] != (T)0;
   for (int k = 0; k < K; ++k) {
     const T mx = tb->star[k][0], my = tb->star[k][1];
@@ -357,35 +362,40 @@ __device__ __forceinline__ void eval_own(const Table<T>* __restrict__ tb, const 
 }
 
 // k_maps: every source's own moments E_s, V_s (values only) on its patches' overlap boxes at
-// the base parameters, read by the pixel kernel for overlapping neighbours.
-template <typename T, int PPL, int NEXP, int NDEV>
-__global__ __launch_bounds__(64) void k_maps(MapArgs a) {
+// the base parameters, read by the pixel kernel for overlapping neighbours.  W = 1: one
+// wavefront per work item, PPL pixels per lane; W = PPL: PPL wavefronts per item, one pixel
+// per lane of each (small launches; the component cuts see the same PPL-pixel groups, so the
+// values are the same).
+template <typename T, int PPL, int NEXP, int NDEV, int W>
+__global__ __launch_bounds__(64 * W) void k_maps(MapArgs a) {
+#pragma clang fp contract(off)
+  constexpr int NP = PPL / W;   // pixels per lane
+  static_assert(W == 1 || W == PPL, "one pixel per lane, or one wavefront");
   const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
   const DMapTask task = a.tasks[pos];
   const DPatch P = a.patches[task.patch];
   const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.base) + task.patch;
   const int K = a.img_npsf[P.img];
-  const int lane = threadIdx.x;
   const T L0 = tb->hdr[0], L1 = tb->hdr[1], w0 = tb->hdr[2], w1 = tb->hdr[3];
   const T k0 = tb->hdr[4], k1 = tb->hdr[5], w01 = tb->hdr[6];
   __shared__ T rec[kMaxPsf][2 * kMaxProf][8];
-  stage_records<T>(tb, K, lane, rec);
-  // box-local coordinates of this lane's pixels, advanced by a carry per group (patch-local:
+  stage_records<T, 64 * W>(tb, K, threadIdx.x, rec);
+  // box-local coordinates of this thread's pixels, advanced by a carry per group (patch-local:
   // plus the box corner)
   const int bw = task.w;
   const int step = 64 * PPL;
   const int step_rows = step / bw, step_cols = step - step_rows * bw;
-  int col[PPL], row[PPL];
+  int col[NP], row[NP];
 #pragma unroll
-  for (int i = 0; i < PPL; ++i) {
-    const int idx = task.pix_begin + i * 64 + lane;
+  for (int i = 0; i < NP; ++i) {
+    const int idx = task.pix_begin + i * 64 + (int)threadIdx.x;
     row[i] = idx / bw;
     col[i] = idx - row[i] * bw;
   }
   for (int base = task.pix_begin; base < task.pix_end; base += step) {
-    T px[PPL], py[PPL], f0[PPL], f1[PPL];
+    T px[NP], py[NP], f0[NP], f1[NP];
 #pragma unroll
-    for (int i = 0; i < PPL; ++i) {
+    for (int i = 0; i < NP; ++i) {
       px[i] = (T)(col[i] + task.x0);
       py[i] = (T)(row[i] + task.y0);
     }
@@ -393,13 +403,13 @@ __global__ __launch_bounds__(64) void k_maps(MapArgs a) {
     run_box<int>(base, min(base + step, task.pix_end), bw, ibox);
     const T box[4] = {(T)(ibox[0] + task.x0), (T)(ibox[1] + task.x0), (T)(ibox[2] + task.y0),
                       (T)(ibox[3] + task.y0)};
-    eval_values<T, PPL, NEXP, NDEV>(tb, rec, K, px, py, box, f0, f1);
+    eval_values<T, NP, NEXP, NDEV>(tb, rec, K, px, py, box, f0, f1);
 #pragma unroll
-    for (int i = 0; i < PPL; ++i) {
-      const int idx = base + i * 64 + lane;
+    for (int i = 0; i < NP; ++i) {
+      const int idx = base + i * 64 + (int)threadIdx.x;
       if (idx >= task.pix_end) continue;
       const T a0 = L0 * f0[i], a1 = L1 * f1[i], d = a0 - a1;
-      const T Es = w0 * a0 + w1 * a1;
+      const T Es = fma(w0, a0, w1 * a1);
       const T Vs = fma(k0 * f0[i], f0[i], fma(k1 * f1[i], f1[i], w01 * d * d));
       const int64_t at = P.off + (int64_t)(row[i] + task.y0) * P.w + col[i] + task.x0;
       if constexpr (sizeof(T) == 8)
@@ -408,7 +418,7 @@ __global__ __launch_bounds__(64) void k_maps(MapArgs a) {
         reinterpret_cast<float2*>(a.maps)[at] = make_float2(Es, Vs);
     }
 #pragma unroll
-    for (int i = 0; i < PPL; ++i) {
+    for (int i = 0; i < NP; ++i) {
       col[i] += step_cols;
       row[i] += step_rows;
       if (col[i] >= bw) {
@@ -528,9 +538,17 @@ __global__ __launch_bounds__(64) void k_maps_runs(MapArgs a) {
   }
 }
 
-template <typename T, int PPL, bool GRAD, int NEXP, int NDEV>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? 6 : 1))) void k_fused(
+// W = 1: one wavefront per work item.  W = kFlush: as many wavefronts per item as it has pixel
+// groups between flushes, a group each, for launches whose items leave the chip idle; the
+// wavefronts add to the item's per-lane sums in turn, through LDS, in the order in which one
+// wavefront would, so that an item's sums do not depend on the launch's size.
+constexpr int kFlush = 4;   // pixel groups between flushes of the per-lane sums
+template <typename T, int PPL, bool GRAD, int NEXP, int NDEV, int W>
+__global__ __launch_bounds__(64 * W)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) : 1))) void k_fused(
     FusedArgs<T> a) {
+#pragma clang fp contract(off)
+  static_assert(W == 1 || W == kFlush, "a flush after every pass of the workgroup");
   const int v = a.variant0 + blockIdx.y;
   const int wi = a.order_offset + xcd_position((int)blockIdx.x, (int)gridDim.x);
   const int t = a.order ? a.order[wi] : wi;
@@ -539,30 +557,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   if (a.active && !a.active[P.src]) return;
   const Table<T>* __restrict__ tb = a.own + (int64_t)v * a.variant_stride + task.patch;
   const int K = a.img_npsf[P.img];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   // the galaxy components' records of this patch, staged in LDS once per work item
   __shared__ T rec[kMaxPsf][2 * kMaxProf][8];
-  stage_records<T>(tb, K, lane, rec);
+  stage_records<T, 64 * W>(tb, K, threadIdx.x, rec);
+  // the per-lane sums on their way from wavefront to wavefront
+  __shared__ T chain[W > 1 ? S_T : 1][64];
+  __shared__ double chain_t[W > 1 ? 2 : 1][64];
   const T L0 = tb->hdr[0], L1 = tb->hdr[1], w0 = tb->hdr[2], w1 = tb->hdr[3];
   const T k0 = tb->hdr[4], k1 = tb->hdr[5], w01 = tb->hdr[6], pi = tb->hdr[7];
   // objective sums in FP64 per lane.  The 11 gradient sums are kept per lane in the pixel
   // precision over at most kFlush pixel groups, then summed over the wavefront in FP64 into
   // the work item's slot row (so a lane's partial sum never spans more than kFlush * PPL
   // pixels, whatever the chunk size)
-  constexpr int kFlush = 4;
   double acc_t = 0.0, acc_own = 0.0;
   T part[S_T];
 #pragma unroll
   for (int q = 0; q < S_T; ++q) part[q] = (T)0;
   double* out = a.slots + (int64_t)blockIdx.y * a.slot_variant_stride + (int64_t)t * kSlots;
-  // patch-local coordinates of this lane's pixels, advanced by 64*PPL pixels per group:
+  // patch-local coordinates of this lane's pixels, advanced by 64*PPL*W pixels per pass:
   // one integer division at the start, then a carry
-  const int step = 64 * PPL;
+  const int group_px = 64 * PPL, step = group_px * W;
   const int step_rows = step / P.w, step_cols = step - step_rows * P.w;
   T px[PPL], py[PPL];
 #pragma unroll
   for (int i = 0; i < PPL; ++i) {
-    const int idx = task.pix_begin + i * 64 + lane;
+    const int idx = task.pix_begin + wave * group_px + i * 64 + lane;
     const int row = idx / P.w;
     px[i] = (T)(idx - row * P.w);
     py[i] = (T)row;
@@ -570,7 +590,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   const T wT = (T)P.w, srT = (T)step_rows, scT = (T)step_cols;
   int group = 0;
 
-  for (int base = task.pix_begin; base < task.pix_end; base += step, ++group) {
+  for (int pass = task.pix_begin; pass < task.pix_end; pass += step, ++group) {
+    const int base = pass + wave * group_px;   // (W > 1: past the item's end for its last wavefronts)
     T xv[PPL], sky[PPL];
     bool valid[PPL];
 #pragma unroll
@@ -592,9 +613,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     T f0[PPL], f1[PPL];
     OwnPix<T, PPL> o;
     int ibox[4];
-    run_box<int>(base, min(base + step, task.pix_end), P.w, ibox);
+    const bool any = W == 1 || base < task.pix_end;
+    run_box<int>(base, max(min(base + group_px, task.pix_end), base + 1), P.w, ibox);
     const T box[4] = {(T)ibox[0], (T)ibox[1], (T)ibox[2], (T)ibox[3]};
-    eval_own<T, PPL, NEXP, NDEV, GRAD>(tb, rec, K, px, py, box, o);
+    if (W == 1) __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
+    eval_own<T, PPL, NEXP, NDEV, GRAD>(tb, rec, any ? K : 0, px, py, box, o);
 #pragma unroll
     for (int i = 0; i < PPL; ++i) {
       f1[i] = o.f1[i];
@@ -606,7 +629,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     for (int i = 0; i < PPL; ++i) {
       const T a0 = L0 * f0[i], a1 = L1 * f1[i];
       d[i] = a0 - a1;
-      E[i] = sky[i] + w0 * a0 + w1 * a1;
+      E[i] = fma(w1, a1, fma(w0, a0, sky[i]));
       V[i] = fma(k0 * f0[i], f0[i], fma(k1 * f1[i], f1[i], w01 * d[i] * d[i]));
       own[i] = true;
     }
@@ -619,7 +642,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       ix[i] = (int)px[i];
       iy[i] = (int)py[i];
     }
-    for (int nb = P.nbr_begin; nb < P.nbr_end; ++nb) {
+    for (int nb = P.nbr_begin; nb < (any ? P.nbr_end : P.nbr_begin); ++nb) {
       const DPatch Q = a.patches[a.nbr_idx[nb]];
       const int ox = P.x0 - Q.x0, oy = P.y0 - Q.y0;
       if (ibox[0] + ox >= Q.w || ibox[1] + ox < 0 || ibox[2] + oy >= Q.h || ibox[3] + oy < 0) continue;
@@ -644,6 +667,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         }
       }
     }
+    if constexpr (W > 1) {   // this wavefront's turn: take over the sums of those before it
+      for (int w = 0; w < wave; ++w) __syncthreads();
+      if (GRAD)
+#pragma unroll
+        for (int q = 0; q < S_T; ++q) part[q] = wave > 0 ? chain[q][lane] : (T)0;
+      if (wave > 0 || group > 0) {
+        acc_t = chain_t[0][lane];
+        acc_own = chain_t[1][lane];
+      }
+    }
     // pixel term (centred: the data constant x log x - x - log x! is added per patch in
     // FP64) and adjoint coefficients
 #pragma unroll
@@ -651,7 +684,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       const T x = xv[i];
       const T invE = frcp<T>(E[i]);
       const T xr = x * invE * invE;
-      T Tm = (x > (T)0 ? x_log_ratio<T>(x, E[i]) : (T)0) - (E[i] - x) - (T)0.5 * xr * V[i];
+      T Tm = fma((T)-0.5 * xr, V[i], (x > (T)0 ? x_log_ratio<T>(x, E[i]) : (T)0) - (E[i] - x));
       if (!valid[i]) Tm = (T)0;
       acc_t += (double)Tm;
       acc_own += own[i] ? (double)Tm : 0.0;
@@ -659,13 +692,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         T cE = fma(xr * invE, V[i], (x - E[i]) * invE);
         T cV = (T)-0.5 * xr;
         if (!valid[i]) cE = cV = (T)0;
-        const T rho0 = cE * w0 * L0 + (T)2 * cV * fma(k0, f0[i], w01 * L0 * d[i]);
-        const T rho1 = cE * w1 * L1 + (T)2 * cV * fma(k1, f1[i], -w01 * L1 * d[i]);
-        const T omp = (T)1 - pi;
-        const T g0x = pi * o.gdx[i] + omp * o.gex[i], g0y = pi * o.gdy[i] + omp * o.gey[i];
-        const T s0xx = pi * o.sdxx[i] + omp * o.sexx[i];
-        const T s0xy = (T)2 * (pi * o.sdxy[i] + omp * o.sexy[i]);
-        const T s0yy = pi * o.sdyy[i] + omp * o.seyy[i];
+        const T cV2 = (T)2 * cV, omp = (T)1 - pi, wd = w01 * d[i];
+        const T rho0 = fma(cE * w0, L0, cV2 * fma(k0, f0[i], wd * L0));
+        const T rho1 = fma(cE * w1, L1, cV2 * fma(k1, f1[i], -(wd * L1)));
+        const T g0x = fma(pi, o.gdx[i], omp * o.gex[i]), g0y = fma(pi, o.gdy[i], omp * o.gey[i]);
+        const T s0xx = fma(pi, o.sdxx[i], omp * o.sexx[i]);
+        const T s0xy = (T)2 * fma(pi, o.sdxy[i], omp * o.sexy[i]);
+        const T s0yy = fma(pi, o.sdyy[i], omp * o.seyy[i]);
         const T cVf0 = cV * f0[i], cVf1 = cV * f1[i];
         part[S_CE_F0] = fma(cE, f0[i], part[S_CE_F0]);
         part[S_CE_F1] = fma(cE, f1[i], part[S_CE_F1]);
@@ -680,8 +713,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         part[S_PI] = fma(rho0, o.fd[i] - o.fe[i], part[S_PI]);
       }
     }
-    if (GRAD && (group % kFlush == kFlush - 1 || base + step >= task.pix_end)) {
-      const bool first = group < kFlush;
+    if constexpr (W > 1) {
+      if (GRAD)
+#pragma unroll
+        for (int q = 0; q < S_T; ++q) chain[q][lane] = part[q];
+      chain_t[0][lane] = acc_t;
+      chain_t[1][lane] = acc_own;
+      for (int w = wave; w < W; ++w) __syncthreads();
+    }
+    // flush: after kFlush groups or the item's last (W > 1: by the last wavefront)
+    if (GRAD && (W > 1 ? wave == W - 1 : group % kFlush == kFlush - 1 || base + step >= task.pix_end)) {
+      const bool first = W > 1 ? group == 0 : group < kFlush;
       // the 11 wavefront sums together, then lane 0 reads each from the lane holding it and
       // stores it scaled back (the centre sums carry the records' scale c, the covariance
       // sums c^2); no per-lane slot index or address lives across the pixel loop
@@ -710,6 +752,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       py[i] = r;
     }
   }
+  if (W > 1 && wave != W - 1) return;
   const double acc[2] = {acc_t, acc_own};
   const double s_t = wave_sums<2>(acc, lane);   // lane 0: the pixel term, lane 32: the owned part
   const int tslot = wave_sums_slot<2>(lane);
@@ -1151,6 +1194,20 @@ hipError_t launch_prep_tables(const PrepArgs& a, int n_patches_launch, int n_var
   return hipGetLastError();
 }
 
+// Several wavefronts per work item while the launch's items alone would leave most of the chip
+// idle and its time is one item's latency.  Pixel kernel, one wavefront per item / four: 20
+// items 27 / 12 us, 115 items (values) 25 / 11, 3610 items 49 / 45; 12570 items 106 / 134;
+// double, 3425 items 123 / 141.  Map kernel: 20 items 12.0 / 9.1, 330 items 13.2 / 10.6; 2835
+// items 24.8 / 27.0.
+template <typename T>
+static bool wide_pixels(int64_t n_items) {
+  return n_items <= (sizeof(T) == 8 ? 512 : 4096);
+}
+template <typename T>
+static bool wide_maps(int64_t n_items) {
+  return n_items <= (sizeof(T) == 8 ? 512 : 1024);
+}
+
 template <typename T, int PPL, bool GRAD>
 static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int n_items, int n_var,
                                  hipStream_t st) {
@@ -1158,10 +1215,14 @@ static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int 
   FusedArgs<T> k = a;
   k.unscale[0] = 1.0 / kExpScale;
   k.unscale[1] = 1.0 / (kExpScale * kExpScale);
-  if (nexp == 6 && ndev == 8)
-    hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8>), grid, dim3(64), 0, st, k);
-  else
-    hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 8, 8>), grid, dim3(64), 0, st, k);
+  const bool wide = wide_pixels<T>((int64_t)n_items * n_var);
+  if (nexp == 6 && ndev == 8) {
+    if (wide) hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
+    else hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, 1>), grid, dim3(64), 0, st, k);
+  } else {
+    if (wide) hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 8, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
+    else hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 8, 8, 1>), grid, dim3(64), 0, st, k);
+  }
   return hipGetLastError();
 }
 
@@ -1180,22 +1241,30 @@ hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool
   }
 }
 
+template <typename T, int PPL>
+static void maps_dispatch(const MapArgs& a, bool std_prof, int n_items, hipStream_t st) {
+  const bool wide = PPL > 1 && wide_maps<T>(n_items);
+  if (std_prof) {
+    if (wide) hipLaunchKernelGGL((k_maps<T, PPL, 6, 8, PPL>), dim3(n_items), dim3(64 * PPL), 0, st, a);
+    else hipLaunchKernelGGL((k_maps<T, PPL, 6, 8, 1>), dim3(n_items), dim3(64), 0, st, a);
+  } else {
+    if (wide) hipLaunchKernelGGL((k_maps<T, PPL, 8, 8, PPL>), dim3(n_items), dim3(64 * PPL), 0, st, a);
+    else hipLaunchKernelGGL((k_maps<T, PPL, 8, 8, 1>), dim3(n_items), dim3(64), 0, st, a);
+  }
+}
+
 template <typename T>
 hipError_t launch_maps(const MapArgs& a, int nexp, int ndev, int ppl, int n_items, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
   const bool std_prof = nexp == 6 && ndev == 8;
   if (ppl == 1) {
-    if (std_prof) hipLaunchKernelGGL((k_maps<T, 1, 6, 8>), dim3(n_items), dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((k_maps<T, 1, 8, 8>), dim3(n_items), dim3(64), 0, st, a);
+    maps_dispatch<T, 1>(a, std_prof, n_items, st);
   } else if (ppl == 2) {
-    if (std_prof) hipLaunchKernelGGL((k_maps<T, 2, 6, 8>), dim3(n_items), dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((k_maps<T, 2, 8, 8>), dim3(n_items), dim3(64), 0, st, a);
+    maps_dispatch<T, 2>(a, std_prof, n_items, st);
   } else if (ppl == 4) {
-    if (std_prof) hipLaunchKernelGGL((k_maps<T, 4, 6, 8>), dim3(n_items), dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((k_maps<T, 4, 8, 8>), dim3(n_items), dim3(64), 0, st, a);
+    maps_dispatch<T, 4>(a, std_prof, n_items, st);
   } else if (ppl == 8) {
-    if (std_prof) hipLaunchKernelGGL((k_maps<T, 8, 6, 8>), dim3(n_items), dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((k_maps<T, 8, 8, 8>), dim3(n_items), dim3(64), 0, st, a);
+    maps_dispatch<T, 8>(a, std_prof, n_items, st);
   } else if (ppl == -1) {   // runs along rows, values by recurrence
     if (std_prof) hipLaunchKernelGGL((k_maps_runs<T, 6, 8>), dim3(n_items), dim3(64), 0, st, a);
     else hipLaunchKernelGGL((k_maps_runs<T, 8, 8>), dim3(n_items), dim3(64), 0, st, a);

@@ -209,6 +209,7 @@ constexpr int kHRec = 16;
 // (tau/2)^2 N H'.
 template <typename T>
 __device__ __forceinline__ void gal_hess(const T* q, T wP, T dx, T dy, T& f, T* gm, T* gs, T* h2, T* h3, T* h4) {
+#pragma clang fp contract(off)
   const T ux = fma(q[0], dx, q[1] * dy);
   const T uy = fma(q[1], dx, q[2] * dy);
   const T N = fexp2<T>(fma(dx, ux, fma(dy, uy, q[3])));
@@ -244,11 +245,11 @@ template <typename T, int NEXP, int NDEV>
 __device__ __forceinline__ void eval_own_hess(const Table<T>* __restrict__ tb,
                                               const T (*__restrict__ rec)[2 * kMaxProf][kHRec], int K, T px, T py,
                                               const T* box, PixH<T>& o) {
+#pragma clang fp contract(off)
   T fe = 0, fd = 0, gme[2] = {0, 0}, gmd[2] = {0, 0}, gse[3] = {0, 0, 0}, gsd[3] = {0, 0, 0};
   T h2[3] = {0, 0, 0}, h3[4] = {0, 0, 0, 0}, h4[5] = {0, 0, 0, 0, 0};
   T f1 = 0, g1x = 0, g1y = 0, h1[3] = {0, 0, 0};
   const T pi = tb->hdr[7], omp = (T)1 - pi;
-  __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
   for (int k = 0; k < K; ++k) {
     const T mx = tb->star[k][0], my = tb->star[k][1];
     const T dx = px - mx, dy = py - my;
@@ -336,8 +337,16 @@ struct HessArgs {
 // derivative had its own formula and per-component constants came by scalar loads from the
 // table; the records are now formed once per item in LDS): Hessians of 200 sources (3.7e6
 // active pixels) 397 -> 304 us per call, a Newton step of 339 sources 964 -> 775 us.
-template <typename T, int NEXP, int NDEV>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void k_hess(HessArgs a) {
+//
+// W = 1: one wavefront per work item.  W = kHessWaves: that many per item, a pass of 64 pixels
+// each, for launches whose items leave the chip idle; as in the pixel kernel they add to the
+// item's per-lane sums in turn, in the order of one wavefront, and the products are written
+// out fused, so that an item's sums do not depend on the launch's size.
+constexpr int kHessWaves = 8;
+template <typename T, int NEXP, int NDEV, int W>
+__global__ __launch_bounds__(64 * W)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void k_hess(HessArgs a) {
+#pragma clang fp contract(off)
   const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
   const int t = a.order ? a.order[pos] : pos;
   const DTask task = a.tasks[t];
@@ -345,11 +354,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   if (a.active && !a.active[P.src]) return;
   const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.tables) + task.patch;
   const int K = a.img_npsf[P.img];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   // the galaxy components' records, one component per lane
   __shared__ __align__(16) T rec[kMaxPsf][2 * kMaxProf][kHRec];
   static_assert(kMaxPsf * 2 * kMaxProf <= 64, "one component per lane");
-  if (lane < K * 2 * kMaxProf) {
+  if (threadIdx.x < K * 2 * kMaxProf) {
     const T* q = &tb->gq[0][0][0] + lane * 8;
     T* r = &rec[0][0][0] + lane * kHRec;
 #pragma unroll
@@ -363,18 +372,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   __syncthreads();
   const T L0 = tb->hdr[0], L1 = tb->hdr[1], w0 = tb->hdr[2], w1 = tb->hdr[3];
   const T e0 = tb->hdr[8], e1 = tb->hdr[9];
-  const T w01 = w0 * w1, aa = w1, oma2 = (T)1 - (T)2 * aa;
+  const T w01 = w0 * w1, aa = w1, oma2 = fma((T)-2, aa, (T)1);
   double tsum = 0, town = 0;
   T G[kPrim], Q[kHQ];
+  // the per-lane sums on their way from wavefront to wavefront
+  __shared__ T chain[W > 1 ? kPrim + kHQ : 1][64];
+  __shared__ double chain_t[W > 1 ? 2 : 1][64];
 #pragma unroll
   for (int u = 0; u < kPrim; ++u) G[u] = 0;
 #pragma unroll
   for (int u = 0; u < kHQ; ++u) Q[u] = 0;
-  // this lane's patch-local pixel coordinates, advanced by 64 pixels per pass with a carry
-  const int step_rows = 64 / P.w, step_cols = 64 - step_rows * P.w;
-  int row = (task.pix_begin + lane) / P.w;
-  int col = task.pix_begin + lane - row * P.w;
-  for (int base = task.pix_begin; base < task.pix_end; base += 64) {
+  // this lane's patch-local pixel coordinates, advanced by 64 W pixels per pass with a carry
+  constexpr int step = 64 * W;
+  const int step_rows = step / P.w, step_cols = step - step_rows * P.w;
+  int row = (task.pix_begin + (int)threadIdx.x) / P.w;
+  int col = task.pix_begin + (int)threadIdx.x - row * P.w;
+  for (int pass = task.pix_begin; pass < task.pix_end; pass += step) {
+    const int base = pass + wave * 64;
+    const bool any = W == 1 || base < task.pix_end;
     int idx = base + lane;
     const bool valid = idx < task.pix_end;
     if (!valid) idx = task.pix_begin;
@@ -387,13 +402,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       xv = xs.x; sky = xs.y;
     }
     int ibox[4];
-    run_box<int>(base, min(base + 64, task.pix_end), P.w, ibox);
+    run_box<int>(base, max(min(base + 64, task.pix_end), base + 1), P.w, ibox);
     const T box[4] = {(T)ibox[0], (T)ibox[1], (T)ibox[2], (T)ibox[3]};
     PixH<T> o;
-    eval_own_hess<T, NEXP, NDEV>(tb, rec, K, (T)col, (T)row, box, o);
+    if (W == 1) __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
+    eval_own_hess<T, NEXP, NDEV>(tb, rec, any ? K : 0, (T)col, (T)row, box, o);
     T Eb = sky, Vb = 0;
     bool own = true;
-    for (int nb = P.nbr_begin; nb < P.nbr_end; ++nb) {
+    for (int nb = P.nbr_begin; nb < (any ? P.nbr_end : P.nbr_begin); ++nb) {
       const DPatch Qp = a.patches[a.nbr_idx[nb]];
       const int ox = P.x0 - Qp.x0, oy = P.y0 - Qp.y0;
       // a neighbour whose rectangle misses this pass's pixel box is skipped as a whole
@@ -411,18 +427,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         if (Qp.src < P.src) own = false;
       }
     }
+    if constexpr (W > 1) {   // this wavefront's turn: take over the sums of those before it
+      for (int w = 0; w < wave; ++w) __syncthreads();
+      if (wave > 0 || pass > task.pix_begin) {
+#pragma unroll
+        for (int u = 0; u < kPrim; ++u) G[u] = chain[u][lane];
+#pragma unroll
+        for (int u = 0; u < kHQ; ++u) Q[u] = chain[kPrim + u][lane];
+        tsum = chain_t[0][lane];
+        town = chain_t[1][lane];
+      }
+    }
     const T f0 = o.f0, f1 = o.f1;
-    const T d = L0 * f0 - L1 * f1;
-    const T Es = w0 * L0 * f0 + w1 * L1 * f1;
+    const T a0 = L0 * f0, a1 = L1 * f1, d = a0 - a1;
+    const T Es = fma(w0, a0, w1 * a1);
     const T k0 = w0 * L0 * L0 * e0, k1 = w1 * L1 * L1 * e1;
     const T Vs = fma(k0 * f0, f0, fma(k1 * f1, f1, w01 * d * d));
     const T E = Eb + Es, V = Vb + Vs, x = xv;
     const T invE = frcp<T>(E);
     const T xr = x * invE * invE;
-    T Tm = (x > (T)0 ? x_log_ratio<T>(x, E) : (T)0) - (E - x) - (T)0.5 * xr * V;
+    T Tm = fma((T)-0.5 * xr, V, (x > (T)0 ? x_log_ratio<T>(x, E) : (T)0) - (E - x));
     T cE = fma(xr * invE, V, (x - E) * invE);
     T cV = (T)-0.5 * xr;
-    T TEE = -xr - (T)3 * xr * V * invE * invE;
+    T TEE = -fma((T)3 * xr * V * invE, invE, xr);
     T TEV = xr * invE;
     if (!valid) Tm = cE = cV = TEE = TEV = 0;
     tsum += (double)Tm;
@@ -432,7 +459,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
       g1z[j] = j < 2 ? o.g1[j] : (T)0;
-      dz[j] = L0 * o.g0[j] - L1 * g1z[j];
+      dz[j] = fma(L0, o.g0[j], -(L1 * g1z[j]));
     }
     // the (z, z) block: with E_zz = w0 L0 h0 + w1 L1 h1 and
     //   V_zz = 2 (k0 (g0 g0^T + f0 h0) + k1 (g1 g1^T + f1 h1) + w01 (dz dz^T + d (L0 h0 - L1 h1))),
@@ -471,15 +498,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     Eu[2] = w1 * f1;
     Eu[3] = 0;
     Eu[4] = 0;
-    Vu[0] = -L0 * L0 * e0 * f0 * f0 + L1 * L1 * e1 * f1 * f1 + oma2 * d * d;
-    Vu[1] = (T)2 * w0 * L0 * e0 * f0 * f0 + (T)2 * w01 * d * f0;
-    Vu[2] = (T)2 * w1 * L1 * e1 * f1 * f1 - (T)2 * w01 * d * f1;
-    Vu[3] = w0 * L0 * L0 * f0 * f0;
-    Vu[4] = w1 * L1 * L1 * f1 * f1;
+    const T ea0 = e0 * a0, ea1 = e1 * a1, w01d = w01 * d;
+    Vu[0] = fma(oma2 * d, d, fma(ea1, a1, -(ea0 * a0)));
+    Vu[1] = (T)2 * fma(w0 * ea0, f0, w01d * f0);
+    Vu[2] = (T)2 * fma(w1 * ea1, f1, -(w01d * f1));
+    Vu[3] = w0 * a0 * a0;
+    Vu[4] = w1 * a1 * a1;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-      Eu[5 + j] = w0 * L0 * o.g0[j] + w1 * L1 * g1z[j];
-      Vu[5 + j] = (T)2 * (k0 * f0 * o.g0[j] + k1 * f1 * g1z[j] + w01 * d * dz[j]);
+      Eu[5 + j] = fma(w0 * L0, o.g0[j], w1 * L1 * g1z[j]);
+      Vu[5 + j] = (T)2 * fma(k0 * f0, o.g0[j], fma(k1 * f1, g1z[j], w01d * dz[j]));
     }
     // T_EE E_u E_v + T_EV (E_u V_v + V_u E_v) = E_u a_v + c_u E_v with a = T_EE E + T_EV V,
     // c = T_EV V
@@ -502,30 +530,34 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       }
     }
     // second derivatives of E_s and V_s
-    Q[qidx(0, 0)] += cV * (T)-2 * d * d;
-    Q[qidx(0, 1)] += fma(cE, -f0, cV * ((T)-2 * L0 * e0 * f0 * f0 + (T)2 * oma2 * d * f0));
-    Q[qidx(0, 2)] += fma(cE, f1, cV * ((T)2 * L1 * e1 * f1 * f1 - (T)2 * oma2 * d * f1));
-    Q[qidx(0, 3)] += cV * (-L0 * L0 * f0 * f0);
-    Q[qidx(0, 4)] += cV * (L1 * L1 * f1 * f1);
-    Q[qidx(1, 1)] += cV * ((T)2 * w0 * e0 * f0 * f0 + (T)2 * w01 * f0 * f0);
-    Q[qidx(1, 2)] += cV * ((T)-2 * w01 * f0 * f1);
-    Q[qidx(1, 3)] += cV * ((T)2 * w0 * L0 * f0 * f0);
-    Q[qidx(2, 2)] += cV * ((T)2 * w1 * e1 * f1 * f1 + (T)2 * w01 * f1 * f1);
-    Q[qidx(2, 4)] += cV * ((T)2 * w1 * L1 * f1 * f1);
+    auto add = [&](int u, int v, T x, T y) { Q[qidx(u, v)] = fma(x, y, Q[qidx(u, v)]); };
+    const T f00 = f0 * f0, f11 = f1 * f1;
+    add(0, 0, cV2, -(d * d));
+    add(0, 1, cE, -f0);
+    add(0, 1, cV2, fma(oma2 * d, f0, -(ea0 * f0)));
+    add(0, 2, cE, f1);
+    add(0, 2, cV2, fma(-(oma2 * d), f1, ea1 * f1));
+    add(0, 3, cV, -(a0 * a0));
+    add(0, 4, cV, a1 * a1);
+    add(1, 1, cV2, fma(w0, e0, w01) * f00);
+    add(1, 2, cV2, -(w01 * f0 * f1));
+    add(1, 3, cV2, w0 * a0 * f0);
+    add(2, 2, cV2, fma(w1, e1, w01) * f11);
+    add(2, 4, cV2, w1 * a1 * f1);
     // the (amplitude, z) pairs are linear in g0, g1 and dz with weights fixed per pixel:
     //   Q[0][z] += c_E (-dz) + c_V (-2 L0^2 e0 f0 g0 + 2 L1^2 e1 f1 g1 + 2 (1 - 2a) d dz)
     //   Q[1][z] += c_E w0 g0 + c_V (4 w0 L0 e0 f0 g0 + 2 w01 (f0 dz + d g0))
     //   Q[2][z] += c_E w1 g1 + c_V (4 w1 L1 e1 f1 g1 - 2 w01 (f1 dz + d g1))
     //   Q[3][z] += c_V 2 w0 L0^2 f0 g0,  Q[4][z] += c_V 2 w1 L1^2 f1 g1
-    const T a0 = -cV2 * L0 * L0 * e0 * f0, b0 = cV2 * L1 * L1 * e1 * f1, c0 = fma(cV2 * oma2, d, -cE);
-    const T a1 = fma(cE, w0, cV2 * fma((T)2 * w0 * L0 * e0, f0, w01 * d)), c1 = cV2 * w01 * f0;
-    const T b2 = fma(cE, w1, cV2 * fma((T)2 * w1 * L1 * e1, f1, -w01 * d)), c2 = -cV2 * w01 * f1;
-    const T a3 = cV2 * w0 * L0 * L0 * f0, b4 = cV2 * w1 * L1 * L1 * f1;
+    const T p0 = -(cV2 * L0 * ea0), b0 = cV2 * L1 * ea1, c0 = fma(cV2 * oma2, d, -cE);
+    const T p1 = fma(cE, w0, cV2 * fma((T)2 * w0, ea0, w01d)), c1 = cV2 * w01 * f0;
+    const T b2 = fma(cE, w1, cV2 * fma((T)2 * w1, ea1, -w01d)), c2 = -(cV2 * w01 * f1);
+    const T a3 = cV2 * w0 * L0 * a0, b4 = cV2 * w1 * L1 * a1;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
       const T g0j = o.g0[j], dzj = dz[j];
-      T q0 = fma(a0, g0j, fma(c0, dzj, Q[qidx(0, 5 + j)]));
-      T q1 = fma(a1, g0j, fma(c1, dzj, Q[qidx(1, 5 + j)]));
+      T q0 = fma(p0, g0j, fma(c0, dzj, Q[qidx(0, 5 + j)]));
+      T q1 = fma(p1, g0j, fma(c1, dzj, Q[qidx(1, 5 + j)]));
       T q2 = fma(c2, dzj, Q[qidx(2, 5 + j)]);
       if (j < 2) {
         q0 = fma(b0, g1z[j], q0);
@@ -537,6 +569,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       Q[qidx(2, 5 + j)] = q2;
       Q[qidx(3, 5 + j)] = fma(a3, g0j, Q[qidx(3, 5 + j)]);
     }
+    if constexpr (W > 1) {
+#pragma unroll
+      for (int u = 0; u < kPrim; ++u) chain[u][lane] = G[u];
+#pragma unroll
+      for (int u = 0; u < kHQ; ++u) chain[kPrim + u][lane] = Q[u];
+      chain_t[0][lane] = tsum;
+      chain_t[1][lane] = town;
+      for (int w = wave; w < W; ++w) __syncthreads();
+    }
     col += step_cols;
     row += step_rows;
     if (col >= P.w) {
@@ -544,6 +585,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       row += 1;
     }
   }
+  if (W > 1 && wave != W - 1) return;   // the last wavefront holds the item's sums
   // the slot row's 79 wavefront sums, formed together in two groups (the first 64 of the 77
   // first- and second-order sums, exchanged in the pixel precision at the first step; then
   // the two objective sums with the last 13); the lane holding a sum stores it
@@ -1505,10 +1547,20 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   ha.hslots = p->d_hslots;
   ha.active = active;
   ha.img_npsf = p->d_npsf;
-  if (p->nexp == 6 && p->ndev == 8)
-    hipLaunchKernelGGL((k_hess<T, 6, 8>), dim3(n_items), dim3(64), 0, sm, ha);
-  else
-    hipLaunchKernelGGL((k_hess<T, 8, 8>), dim3(n_items), dim3(64), 0, sm, ha);
+  // kHessWaves wavefronts per item while the items are at most two per compute unit: 115 items
+  // 74 us with one, 25 with eight; 260 items 66 / 37; 1885 items 72 / 150.  (Not the double
+  // form, whose sums alone fill a wavefront's registers.)
+  constexpr int kHessWideItems = 512;
+  const bool std_prof = p->nexp == 6 && p->ndev == 8;
+  if constexpr (sizeof(T) == 4) {
+    if (n_items <= kHessWideItems) {
+      if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, kHessWaves>), dim3(n_items), dim3(64 * kHessWaves), 0, sm, ha);
+      else hipLaunchKernelGGL((k_hess<T, 8, 8, kHessWaves>), dim3(n_items), dim3(64 * kHessWaves), 0, sm, ha);
+      return hipGetLastError();
+    }
+  }
+  if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, 1>), dim3(n_items), dim3(64), 0, sm, ha);
+  else hipLaunchKernelGGL((k_hess<T, 8, 8, 1>), dim3(n_items), dim3(64), 0, sm, ha);
   return hipGetLastError();
 }
 
@@ -1546,13 +1598,15 @@ static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_
   return hipGetLastError();
 }
 
-// One Newton iteration of colour class `cls` on the sources flagged in `active`.  With
-// maps_current the neighbour moment maps are taken as they are (none of the class's
-// neighbours has moved since they were made: the sweep refreshes them once per class) and
-// only the class's own tables are rebuilt.
+// What of the iterate's tables and neighbour moment maps a Newton iteration finds made: the
+// maps (none of the class's neighbours has moved since they were made: the sweep refreshes
+// them once per class), so that only the class's own tables are rebuilt; or both.
+enum class Made { kNothing, kMaps, kAll };
+
+// One Newton iteration of colour class `cls` on the sources flagged in `active`.
 static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radius, uint8_t* active, int cls,
                                        int32_t* status, double* out_local, bool clear_done, hipStream_t sm,
-                                       bool maps_current = false) {
+                                       Made made = Made::kNothing) {
   const bool fp64 = p->opt.pixel_fp64 || p->opt.hessian_fp64;
   const int nsrc = (int)p->class_src[cls].size();
   if (nsrc == 0) return hipSuccess;
@@ -1560,7 +1614,9 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   const bool analytic = !p->opt.hessian_fd;
   if (analytic) {
     // tables (and maps) at the iterate, then the exact Hessians with the gradients
-    e = maps_current ? prep_class(p, theta, cls, active, sm, fp64) : prep_base(p, theta, sm, fp64);
+    e = made == Made::kAll    ? hipSuccess
+        : made == Made::kMaps ? prep_class(p, theta, cls, active, sm, fp64)
+                              : prep_base(p, theta, sm, fp64);
     if (e == hipSuccess)
       e = enqueue_hessian(p, theta, p->d_class_tasks[cls], (int)p->class_tasks[cls].size(), p->d_class_src[cls], nsrc,
                           active, true, p->v_local, p->v_grad, p->d_hess, sm);
@@ -1679,11 +1735,13 @@ extern "C" cel_status cel_newton_step(cel_ctx* ctx, const cel_plan* cplan, doubl
   const bool maps_once = !p->opt.hessian_fd;
   if (maps_once && e == hipSuccess && cls >= 0) e = prep_base(p, theta, sm, p->opt.pixel_fp64 || p->opt.hessian_fp64);
   if (cls == p->n_colours) {
-    if (e == hipSuccess) e = enqueue_newton_class(p, theta, radius, p->d_mask, cls, step_status, elbo_local, false, sm, true);
+    if (e == hipSuccess)
+      e = enqueue_newton_class(p, theta, radius, p->d_mask, cls, step_status, elbo_local, false, sm, Made::kAll);
   } else {
     for (int c : used) {
       if (e != hipSuccess) break;
-      e = enqueue_newton_class(p, theta, radius, p->d_mask, c, step_status, elbo_local, false, sm, maps_once);
+      e = enqueue_newton_class(p, theta, radius, p->d_mask, c, step_status, elbo_local, false, sm,
+                               maps_once ? Made::kAll : Made::kNothing);
     }
   }
   if (e == hipSuccess) {
@@ -1767,7 +1825,8 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
           hipGraph_t graph;
           e = hipStreamBeginCapture(sm, hipStreamCaptureModeThreadLocal);
           if (e != hipSuccess) break;
-          hipError_t e2 = enqueue_newton_class(p, theta, radius, p->d_mask, c, status, nullptr, true, sm, maps_once);
+          hipError_t e2 = enqueue_newton_class(p, theta, radius, p->d_mask, c, status, nullptr, true, sm,
+                                                maps_once ? Made::kMaps : Made::kNothing);
           e = hipStreamEndCapture(sm, &graph);
           if (e2 != hipSuccess) e = e2;
           if (e != hipSuccess) break;
@@ -1783,7 +1842,8 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
       }
       for (int it = 0; it < o.max_newton_iters && e == hipSuccess; ++it) {
         if (exec) e = hipGraphLaunch(exec, sm);
-        else e = enqueue_newton_class(p, theta, radius, p->d_mask, c, status, nullptr, true, sm, maps_once);
+        else e = enqueue_newton_class(p, theta, radius, p->d_mask, c, status, nullptr, true, sm,
+                                                maps_once ? Made::kMaps : Made::kNothing);
         ++steps;
         if (e != hipSuccess) break;
         if ((it + 1) % check_every == 0 || it + 1 == o.max_newton_iters) {

@@ -142,7 +142,7 @@ template <typename T>
 __device__ __forceinline__ T box_dist2(T mx, T my, const T* box) {
   const T ddx = fmax(fmax(box[0] - mx, mx - box[1]), (T)0);
   const T ddy = fmax(fmax(box[2] - my, my - box[3]), (T)0);
-  return ddx * ddx + ddy * ddy;
+  return fma(ddx, ddx, ddy * ddy);
 }
 
 // Pixel box (patch-local columns x0..x1, rows y0..y1) of the run [base, end) of a
