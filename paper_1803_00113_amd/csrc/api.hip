@@ -466,8 +466,7 @@ cel_status ensure_newton(cel_plan* p) {
       (st = track(p, &p->d_hslots, T1 * 80)) ||
       (st = track(p, &p->d_step_src, S1)) || (st = track(p, &p->d_step_patches, P1)) ||
       (st = track(p, &p->d_step_tasks, T1)) ||
-      (st = track(p, &p->d_hess, S1 * kParamN * kParamN)) ||
-      (st = track(p, &p->d_hpart, S1 * kHessParts * kHessPartN)))
+      (st = track(p, &p->d_hess, S1 * kParamN * kParamN)))
     return st;
   if (hipMemset(p->d_trial_active, 0, S1) != hipSuccess) return CEL_EHIP;
   // pinned words, event and stream: the plan's own (after an append), else a kit from a

@@ -38,6 +38,12 @@ constexpr int kLd = kN + 1;   // padded LDS row
 
 
 
+// LDS written by lanes of one wavefront, read by other lanes of it
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Hessian of KL_s in the unconstrained coordinates (the same KL as the objective: the type
 // KL, the normal KL of log r, the colour bound F = -log sum_j w_j exp(-D_j), and minus the
 // log prior densities of the radius, profile and axis point masses), times sc, added into
@@ -48,7 +54,7 @@ constexpr int kLd = kN + 1;   // padded LDS row
 // 8 i + j takes prior colour component j of type i -- its weight xi_j, dD_j and d2D_j --
 // and the sums over j of xi_j (d2D_j - dD_j dD_j^T) and xi_j dD_j are formed through LDS
 // in fixed order (work: 16 x 44 and 2 x 44 doubles); lanes then add the two 8 x 8 colour
-// blocks and lane 0 the remaining terms.  Ends after a barrier.
+// blocks and lane 0 the remaining terms.
 constexpr int kKlw = 44;   // 36 upper-triangle entries of the 8 x 8 block + 8 gradient entries
 template <int LD>
 __device__ void kl_hessian_wave(const DPrior& pr, const double* th, double (*B)[LD], double sc, int lane,
@@ -98,14 +104,14 @@ __device__ void kl_hessian_wave(const DPrior& pr, const double* th, double (*B)[
 #pragma unroll
     for (int u = 0; u < 8; ++u) work[lane][36 + u] = xi * dD[u];
   }
-  __syncthreads();
+  wave_lds_sync();
   for (int e2 = lane; e2 < 2 * kKlw; e2 += 64) {
     const int ii = e2 / kKlw, q = e2 % kKlw;
     double acc = 0;
     for (int jj = 0; jj < 8; ++jj) acc += work[8 * ii + jj][q];
     sums[ii][q] = acc;
   }
-  __syncthreads();
+  wave_lds_sync();
   const double eta = th[2], a = sigmoid(eta), aa = a * (1.0 - a);
   // colour blocks: entry (u, w) of type ii, lanes 0..63 twice
   for (int e2 = lane; e2 < 2 * 64; e2 += 64) {
@@ -157,7 +163,7 @@ __device__ void kl_hessian_wave(const DPrior& pr, const double* th, double (*B)[
       B[26][26] += sc * ((pr.axis[0] + pr.axis[1] - 2.0) * p * (1.0 - p));
     }
   }
-  __syncthreads();
+  wave_lds_sync();
 }
 
 // ----------------------------------------------------------------------------------------
@@ -658,21 +664,11 @@ struct HessFinArgs {
   const double* pix_const;
   const cel_image* images;
   const DPrior* prior;
-  int32_t with_kl;             // 1: the Hessian includes the KL part (value and gradient always do)
   double* local;               // [S]
   double* grad;                // [S][32]
   double* hess;                // [S][27][27]
   int32_t* err;                // device condition word (non-finite Hessian entries)
-  double* part;                // [S][kHParts][kPartN] per-part sums: Hessian, gradient, local
 };
-
-// The pixel part of a source's Hessian is summed over its patches by kHParts wavefronts,
-// each taking a contiguous quarter of the patches (a single wavefront per source leaves
-// most SIMDs idle and waits on every latency alone); k_hess_combine adds the parts in a
-// fixed order and the KL terms.
-constexpr int kHParts = kHessParts;
-constexpr int kPartN = kHessPartN;   // Hessian, gradient, local, pad
-static_assert(kPartN >= kN * kN + kN + 1, "part record too small");
 
 // Sparsity of J = dr/dtheta (r: the 11 primitive coordinates, theta: the 27 parameters):
 // column k has jcount(k) nonzero rows jrow(k, e) -- the centre rows for the position, the
@@ -690,257 +686,278 @@ __device__ __forceinline__ int jrow(int k, int e) {
   return 7 + e;
 }
 
-__global__ __launch_bounds__(64) void k_hess_finalize(HessFinArgs a) {
-  const int s = a.job_src ? a.job_src[blockIdx.x] : (int)blockIdx.x;
-  if (a.active && !a.active[s]) return;
-  const int lane = threadIdx.x;
-  const int w = blockIdx.y;
-  // slot sums and flux moments of up to kPB patches, gathered together (one memory and one
-  // exp latency per batch instead of per patch)
-  constexpr int kPB = 16, kHU = 2 + kPrim + kHQ;
-  __shared__ double smb[kPB][kHU], Lfb[kPB][2], evb[kPB][2];
-  __shared__ double Qr[kPrim][kPrim], Gr[kPrim];
-  // column k of dr/dtheta: rows jr[k][e] with values jv[k][e] (zero past jcount(k)); dg the
-  // diagonal and sblk the S-block second-derivative terms
-  __shared__ double jv[kN][3], dg[kN], sblk[3][3];
-  __shared__ int jr[kN][3];
-  __shared__ double gs[kThetaN];
-  __shared__ double th[kN], sd1[3][3], sd2[3][3][3];
-  __shared__ double rv[2], cvv[2][4];
-  if (lane < kN) th[lane] = a.theta[(int64_t)s * kThetaN + lane];
-  if (lane < kThetaN) gs[lane] = 0.0;
-  __syncthreads();
-  if (lane == 0) sigma_derivs(th[23], th[24], th[26], sd1, sd2);
-  if (lane < kN) {
-#pragma unroll
-    for (int e = 0; e < 3; ++e) jr[lane][e] = e < jcount(lane) ? jrow(lane, e) : jrow(lane, 0);
-  }
-  // flux and colour variances, one per lane
-  if (lane >= 1 && lane < 11) {
-    const int l = lane - 1;
-    const double e = exp(l < 2 ? th[5 + l] : th[15 + (l - 2)]);
-    if (l < 2) rv[l] = e;
-    else cvv[(l - 2) / 4][(l - 2) % 4] = e;
-  }
-  __syncthreads();
-  // this lane's Hessian entries idx = lane + 64 m accumulate in registers over the patches
-  constexpr int kHPer = (kN * kN + 63) / 64;
-  double hacc[kHPer];
-#pragma unroll
-  for (int m = 0; m < kHPer; ++m) hacc[m] = 0.0;
-  double local = 0.0;
-  const double aa = sigmoid(th[2]), pi = sigmoid(th[25]);
-  // this part's patches: a contiguous share of the source's
-  const int q0 = a.patch_ptr[s], nq = a.patch_ptr[s + 1] - q0, per = (nq + kHParts - 1) / kHParts;
-  const int p0 = q0 + min(nq, w * per), p1 = q0 + min(nq, (w + 1) * per);
-  for (int pb = p0; pb < p1; pb += kPB) {
-    const int nb = min(kPB, p1 - pb);
-    for (int e = lane; e < nb * kHU; e += 64) {
-      const int q = e / kHU, l = e % kHU;
-      const DPatch P = a.patches[pb + q];
-      double acc = 0;
-      for (int t = P.task_begin; t < P.task_end; ++t) acc += a.hslots[(int64_t)t * kHSlots + l];
-      smb[q][l] = acc;
-    }
-    // flux moments of each patch's band: L_i = iota exp(m_i + v_i / 2) and e_i = exp(v_i),
-    // lane 4 q + 2 w + i
-    if (lane < 4 * nb) {
-      const int q = lane >> 2, i = lane & 1, w = (lane >> 1) & 1;
-      const cel_image& imq = a.images[a.patches[pb + q].img];
-      double m = th[3 + i], var = rv[i];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const double W = c_W[imq.band][c];
-        m += W * th[7 + 4 * i + c];
-        var += W * W * cvv[i][c];
-      }
-      const double ex = exp(w == 0 ? m + 0.5 * var : var);
-      if (w == 0) Lfb[q][i] = imq.iota * ex;
-      else evb[q][i] = ex;
-    }
-    __syncthreads();
-    for (int q = 0; q < nb; ++q) {
-      const int p = pb + q;
-      const DPatch P = a.patches[p];
-      const cel_image& im = a.images[P.img];
-      const double* sm = smb[q];
-      const double* Lf = Lfb[q];
-      const double* ev = evb[q];
-      local += sm[0] + a.pix_const[2 * p];
-      // stage 1: y = (a, L0, L1, e0, e1, z) -> r = (a, m0, v0, m1, v1, z).  Each r is reached
-      // from at most two y: a <- a; m_i <- L_i (dL/dm = L); v_i <- L_i (L/2) and e_i (e^v);
-      // z <- z.  Qr = Jy^T Qy Jy + sum_u g_u d2y_u/dr2, Gr = Jy^T g.  Written without
-      // branches: the second source of an r that has one is given weight 0.
-      auto ysrc = [&](int r, int* u, double* j) {
-        const bool flux = r >= 1 && r <= 4;
-        const int i = (r - 1) >> 1;
-        const bool var = flux && ((r & 1) == 0);
-        const double L = i ? Lf[1] : Lf[0], e = i ? ev[1] : ev[0];
-        u[0] = flux ? 1 + i : r;
-        j[0] = flux ? (var ? 0.5 * L : L) : 1.0;
-        u[1] = var ? 3 + i : u[0];
-        j[1] = var ? e : 0.0;
-      };
-      for (int idx = lane; idx < kPrim * kPrim; idx += 64) {
-        const int r = idx / kPrim, r2 = idx % kPrim;
-        int ua[2], ub[2];
-        double ja[2], jb[2];
-        ysrc(r, ua, ja);
-        ysrc(r2, ub, jb);
-        double v = 0;
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 2; ++y) {
-            const int u = ua[x], w = ub[y];
-            v += ja[x] * sm[2 + kPrim + (u <= w ? qidx(u, w) : qidx(w, u))] * jb[y];
-          }
-        // second derivatives of y in r: L_i: mm = L, mv = L/2, vv = L/4; e_i: vv = e^v
-        if (r >= 1 && r <= 4 && r2 >= 1 && r2 <= 4 && ((r - 1) >> 1) == ((r2 - 1) >> 1)) {
-          const int i = (r - 1) >> 1;
-          const double gL = sm[3 + i], ge = sm[5 + i];
-          const double L = i ? Lf[1] : Lf[0], e = i ? ev[1] : ev[0];
-          const int nv = ((r & 1) == 0) + ((r2 & 1) == 0);   // how many of r, r2 are v_i
-          v += gL * L * (nv == 0 ? 1.0 : nv == 1 ? 0.5 : 0.25) + (nv == 2 ? ge * e : 0.0);
-        }
-        Qr[r][r2] = v;
-      }
-      if (lane < kPrim) {
-        int ua[2];
-        double ja[2];
-        ysrc(lane, ua, ja);
-        Gr[lane] = ja[0] * sm[2 + ua[0]] + ja[1] * sm[2 + ua[1]];
-      }
-      __syncthreads();   // Gr is read below
-      // stage 2: the nonzero values of column k of J = dr/dtheta (zero-padded to 3), all
-      // candidates formed and one selected
-      if (lane < kN) {
-        const int k = lane;
-        const double A00 = im.A[0][0], A01 = im.A[0][1], A10 = im.A[1][0], A11 = im.A[1][1];
-        const int c = (k - 7) & 3, ti = (k - 15) >> 2;
-        const double W = c_W[im.band][c];
-        const int t = k == 23 ? 0 : k == 24 ? 1 : 2;
-        double sv[3];
-        conj_A(im.A, sd1[t], sv);
-        const bool sk = k == 23 || k == 24 || k == 26;
-        double v0 = 0.0;
-        v0 = k == 0 ? A00 : k == 1 ? A01 : v0;
-        v0 = k == 2 ? aa * (1.0 - aa) : v0;
-        v0 = (k == 3 || k == 4) ? 1.0 : v0;
-        v0 = (k == 5 || k == 6) ? rv[k == 6] : v0;
-        v0 = (k >= 7 && k < 15) ? W : v0;
-        v0 = (k >= 15 && k < 23) ? W * W * cvv[ti & 1][c] : v0;
-        v0 = k == 25 ? pi * (1.0 - pi) : v0;
-        v0 = sk ? sv[0] : v0;
-        jv[k][0] = v0;
-        jv[k][1] = k == 0 ? A10 : k == 1 ? A11 : sk ? sv[1] : 0.0;
-        jv[k][2] = sk ? sv[2] : 0.0;
-        // the diagonal second-derivative terms sum_r Gr[r] d2r/dtheta_k^2 (outside the S block)
-        double dgk = 0.0;
-        dgk = k == 2 ? Gr[0] * aa * (1.0 - aa) * (1.0 - 2.0 * aa) : dgk;
-        dgk = (k == 5 || k == 6) ? Gr[2 + 2 * (k - 5)] * rv[k == 6] : dgk;
-        dgk = (k >= 15 && k < 23) ? Gr[2 + 2 * (ti & 1)] * W * W * cvv[ti & 1][c] : dgk;
-        dgk = k == 25 ? Gr[10] * pi * (1.0 - pi) * (1.0 - 2.0 * pi) : dgk;
-        dg[k] = dgk;
-      }
-      // S block (angle, radius, axis): sum_r Gr[r] d2S_r/dt dt'
-      if (lane >= 32 && lane < 41) {
-        const int ti = (lane - 32) / 3, tk = (lane - 32) % 3;
-        double sv[3];
-        conj_A(im.A, sd2[ti][tk], sv);
-        sblk[ti][tk] = Gr[7] * sv[0] + Gr[8] * sv[1] + Gr[9] * sv[2];
-      }
-      __syncthreads();
-      // H += J^T Qr J + the second-derivative terms, 3 x 3 terms per entry (zero-padded
-      // columns; the rows of column k are jr[k][e])
-#pragma unroll
-      for (int m = 0; m < kHPer; ++m) {
-        const int idx = lane + 64 * m;
-        if (idx >= kN * kN) break;
-        const int i = idx / kN, k = idx % kN;
-        double v = 0;
-#pragma unroll
-        for (int x = 0; x < 3; ++x) {
-          const int r = jr[i][x];
-          double tt = 0;
-#pragma unroll
-          for (int y = 0; y < 3; ++y) tt += Qr[r][jr[k][y]] * jv[k][y];
-          v += jv[i][x] * tt;
-        }
-        if (i == k) v += dg[i];
-        const int si = i == 23 ? 0 : i == 24 ? 1 : i == 26 ? 2 : -1;
-        const int sk = k == 23 ? 0 : k == 24 ? 1 : k == 26 ? 2 : -1;
-        if (si >= 0 && sk >= 0) v += sblk[si][sk];
-        hacc[m] += v;
-      }
-      if (lane < kN) gs[lane] += jv[lane][0] * Gr[jr[lane][0]] + jv[lane][1] * Gr[jr[lane][1]] + jv[lane][2] * Gr[jr[lane][2]];
-      __syncthreads();
-    }
-  }
-  // this part's sums
-  double* out = a.part + ((int64_t)s * kHParts + w) * kPartN;
-#pragma unroll
-  for (int m = 0; m < kHPer; ++m) {
-    const int idx = lane + 64 * m;
-    if (idx < kN * kN) out[idx] = hacc[m];
-  }
-  __syncthreads();   // gs is complete
-  if (lane < kN) out[kN * kN + lane] = gs[lane];
-  if (lane == 0) out[kN * kN + kN] = local;   // (every lane holds the same sum)
+// k_hess_finalize: a source's Hessian, gradient and local objective from its work items' sums,
+// one workgroup per source.  Its time is the latency of dependent FP64 chains, so the
+// independent parts run on wavefronts of their own: kHParts of them take a contiguous share
+// of the patches each, one the KL value and gradient, one the KL Hessian; the parts are
+// added in LDS in a fixed order.  Per patch H += J^T (Qr J) is formed in two products over
+// the at most three nonzero rows of J's columns, upper triangle only (six entries per lane in
+// registers).  3 sources of 5 patches: 46 us as two kernels (four part wavefronts, then the
+// parts' sum with the KL terms), 13 us here; 200 sources 57 / 14.7; 339 of 10 patches 61 / 36.
+constexpr int kHParts = 8;
+constexpr int kHWaves = kHParts + 2;
+constexpr int kHTri = kN * (kN + 1) / 2;      // 378
+constexpr int kHPer = (kHTri + 63) / 64;      // per lane
+constexpr int kHU = 2 + kPrim + kHQ;
+
+// entry e of the upper triangle of a kN x kN matrix, row by row
+__device__ __forceinline__ void tri_entry(int e, int& i, int& k) {
+  const float b = 2 * kN + 1;
+  i = (int)((b - sqrtf(b * b - 8.0f * (float)e)) * 0.5f);
+  i = min(max(i, 0), kN - 1);
+  if (i * (2 * kN + 1 - i) / 2 > e) --i;
+  else if ((i + 1) * (2 * kN - i) / 2 <= e) ++i;
+  k = e - i * (2 * kN + 1 - i) / 2 + i;
 }
 
-// one wavefront per source: the parts' sums in a fixed order, then the KL value, gradient
-// and (with with_kl) Hessian, and the outputs
-__global__ __launch_bounds__(64) void k_hess_combine(HessFinArgs a) {
+struct HessPartLds {
+  // (once its patches are done: the part's Hessian, gradient and local objective)
+  double sm[kHU], Lf[2], ev[2];   // a patch's sums and flux moments
+  double Qr[kPrim][kPrim], Gr[kPrim], QJ[kPrim][kN];
+  // column k of dr/dtheta: rows jr[k][e] with values jv[k][e] (zero past jcount(k)); dg the
+  // diagonal and sblk the S-block second-derivative terms
+  double jv[kN][3], dg[kN], sblk[3][3];
+  int jr[kN][3];
+  double th[kN], sd1[3][3], sd2[3][3][3];
+  double rv[2], cvv[2][4];
+};
+static_assert(sizeof(HessPartLds) >= (kHTri + kN + 1) * sizeof(double), "a part's sums fit over its work arrays");
+
+__global__ __launch_bounds__(64 * kHWaves) void k_hess_finalize(HessFinArgs a) {
   const int s = a.job_src ? a.job_src[blockIdx.x] : (int)blockIdx.x;
   if (a.active && !a.active[s]) return;
-  const int lane = threadIdx.x;
-  __shared__ double Hs[kN][kLd], gs[kThetaN], th[kN];
-  if (lane < kN) th[lane] = a.theta[(int64_t)s * kThetaN + lane];
-  const double* part = a.part + (int64_t)s * kHParts * kPartN;
-  for (int idx = lane; idx < kN * kN; idx += 64) {
-    double h = 0.0;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ HessPartLds part_lds[kHParts];
+  auto part = [&](int q) { return reinterpret_cast<double*>(&part_lds[q]); };
+  __shared__ double Hk[kN][kLd], klg[kN + 1];        // minus the KL's Hessian and gradient; its value
+  const double* theta = a.theta + (int64_t)s * kThetaN;
+  if (w == kHParts) {
+    double thr[kThetaN], gk[kThetaN];
 #pragma unroll
-    for (int w = 0; w < kHParts; ++w) h += part[w * kPartN + idx];
-    Hs[idx / kN][idx % kN] = h;
-  }
-  if (lane < kThetaN) {
-    double g = 0.0;
-    if (lane < kN)
-#pragma unroll
-      for (int w = 0; w < kHParts; ++w) g += part[w * kPartN + kN * kN + lane];
-    gs[lane] = g;
-  }
-  double local = 0.0;
-#pragma unroll
-  for (int w = 0; w < kHParts; ++w) local += part[w * kPartN + kN * kN + kN];
-  __syncthreads();
-  // KL: value, gradient and (optionally) Hessian
-  __shared__ double klv;
-  {
-    double gk[kThetaN];
-#pragma unroll
-    for (int k = 0; k < kThetaN; ++k) gk[k] = 0.0;
-    const double kv = kl_source_wave(*a.prior, th, gk, 1.0, lane);   // every lane: gk = -grad KL
+    for (int k = 0; k < kThetaN; ++k) {
+      thr[k] = theta[k];
+      gk[k] = 0.0;
+    }
+    const double kv = kl_source_wave(*a.prior, thr, gk, 1.0, lane);   // every lane: gk = -grad KL
     if (lane == 0) {
-      klv = kv;
+      klg[kN] = kv;
 #pragma unroll
-      for (int k = 0; k < kN; ++k) gs[k] += gk[k];
+      for (int k = 0; k < kN; ++k) klg[k] = gk[k];
+    }
+  } else if (w == kHParts + 1) {
+    __shared__ double klw[16][kKlw], kls[2][kKlw];
+    double thr[kThetaN];
+#pragma unroll
+    for (int k = 0; k < kThetaN; ++k) thr[k] = theta[k];
+    for (int idx = lane; idx < kN * kN; idx += 64) Hk[idx / kN][idx % kN] = 0.0;
+    wave_lds_sync();
+    kl_hessian_wave<kLd>(*a.prior, thr, Hk, -1.0, lane, klw, kls);
+  } else {
+    HessPartLds& m = part_lds[w];
+    if (lane < kN) m.th[lane] = theta[lane];
+    wave_lds_sync();
+    if (lane == 0) sigma_derivs(m.th[23], m.th[24], m.th[26], m.sd1, m.sd2);
+    if (lane < kN) {
+#pragma unroll
+      for (int e = 0; e < 3; ++e) m.jr[lane][e] = e < jcount(lane) ? jrow(lane, e) : jrow(lane, 0);
+    }
+    // flux and colour variances, one per lane
+    if (lane >= 1 && lane < 11) {
+      const int l = lane - 1;
+      const double e = exp(l < 2 ? m.th[5 + l] : m.th[15 + (l - 2)]);
+      if (l < 2) m.rv[l] = e;
+      else m.cvv[(l - 2) / 4][(l - 2) % 4] = e;
+    }
+    wave_lds_sync();
+    // this lane's Hessian entries (ti, tk) = entry lane + 64 m accumulate in registers
+    double hacc[kHPer], gsum = 0.0, local = 0.0;
+    int ti[kHPer], tk[kHPer];
+#pragma unroll
+    for (int q = 0; q < kHPer; ++q) {
+      hacc[q] = 0.0;
+      tri_entry(min(lane + 64 * q, kHTri - 1), ti[q], tk[q]);
+    }
+    const double aa = sigmoid(m.th[2]), pi = sigmoid(m.th[25]);
+    // this part's patches: a contiguous share of the source's
+    const int q0 = a.patch_ptr[s], nq = a.patch_ptr[s + 1] - q0, per = (nq + kHParts - 1) / kHParts;
+    const int p0 = q0 + min(nq, w * per), p1 = q0 + min(nq, (w + 1) * per);
+    for (int p = p0; p < p1; ++p) {
+      {
+        const cel_image& im = a.images[a.patches[p].img];
+        // the work items' sums, four items' loads at a time
+        const int t1 = a.patches[p].task_end;
+        double s0 = 0.0, s1 = 0.0;
+        for (int t = a.patches[p].task_begin; t < t1; t += 4) {
+          double x[4], y[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const double* row = a.hslots + (int64_t)min(t + u, t1 - 1) * kHSlots;
+            x[u] = row[lane];
+            y[u] = row[min(64 + lane, kHU - 1)];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            s0 += t + u < t1 ? x[u] : 0.0;
+            s1 += t + u < t1 ? y[u] : 0.0;
+          }
+        }
+        m.sm[lane] = s0;
+        if (64 + lane < kHU) m.sm[64 + lane] = s1;
+        // flux moments of the patch's band: L_i = iota exp(m_i + v_i / 2) and e_i = exp(v_i),
+        // lane 2 w + i
+        if (lane < 4) {
+          const int i = lane & 1, which = (lane >> 1) & 1;
+          double mean = m.th[3 + i], var = m.rv[i];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const double W = c_W[im.band][c];
+            mean += W * m.th[7 + 4 * i + c];
+            var += W * W * m.cvv[i][c];
+          }
+          const double ex = exp(which == 0 ? mean + 0.5 * var : var);
+          if (which == 0) m.Lf[i] = im.iota * ex;
+          else m.ev[i] = ex;
+        }
+        wave_lds_sync();
+        const double *sm = m.sm, *Lf = m.Lf, *ev = m.ev;
+        local += sm[0] + a.pix_const[2 * p];
+        // stage 1: y = (a, L0, L1, e0, e1, z) -> r = (a, m0, v0, m1, v1, z).  Each r is reached
+        // from at most two y: a <- a; m_i <- L_i (dL/dm = L); v_i <- L_i (L/2) and e_i (e^v);
+        // z <- z.  Qr = Jy^T Qy Jy + sum_u g_u d2y_u/dr2, Gr = Jy^T g.  Written without
+        // branches: the second source of an r that has one is given weight 0.
+        auto ysrc = [&](int r, int* u, double* j) {
+          const bool flux = r >= 1 && r <= 4;
+          const int i = (r - 1) >> 1;
+          const bool var = flux && ((r & 1) == 0);
+          const double L = i ? Lf[1] : Lf[0], e = i ? ev[1] : ev[0];
+          u[0] = flux ? 1 + i : r;
+          j[0] = flux ? (var ? 0.5 * L : L) : 1.0;
+          u[1] = var ? 3 + i : u[0];
+          j[1] = var ? e : 0.0;
+        };
+        for (int idx = lane; idx < kPrim * kPrim; idx += 64) {
+          const int r = idx / kPrim, r2 = idx % kPrim;
+          int ua[2], ub[2];
+          double ja[2], jb[2];
+          ysrc(r, ua, ja);
+          ysrc(r2, ub, jb);
+          double v = 0;
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+              const int u = ua[x], z = ub[y];
+              v += ja[x] * sm[2 + kPrim + (u <= z ? qidx(u, z) : qidx(z, u))] * jb[y];
+            }
+          // second derivatives of y in r: L_i: mm = L, mv = L/2, vv = L/4; e_i: vv = e^v
+          if (r >= 1 && r <= 4 && r2 >= 1 && r2 <= 4 && ((r - 1) >> 1) == ((r2 - 1) >> 1)) {
+            const int i = (r - 1) >> 1;
+            const double gL = sm[3 + i], ge = sm[5 + i];
+            const double L = i ? Lf[1] : Lf[0], e = i ? ev[1] : ev[0];
+            const int nv = ((r & 1) == 0) + ((r2 & 1) == 0);   // how many of r, r2 are v_i
+            v += gL * L * (nv == 0 ? 1.0 : nv == 1 ? 0.5 : 0.25) + (nv == 2 ? ge * e : 0.0);
+          }
+          m.Qr[r][r2] = v;
+        }
+        if (lane < kPrim) {
+          int ua[2];
+          double ja[2];
+          ysrc(lane, ua, ja);
+          m.Gr[lane] = ja[0] * sm[2 + ua[0]] + ja[1] * sm[2 + ua[1]];
+        }
+        wave_lds_sync();   // Gr is read below
+        // stage 2: the nonzero values of column k of J = dr/dtheta (zero-padded to 3), all
+        // candidates formed and one selected
+        if (lane < kN) {
+          const int k = lane;
+          const double A00 = im.A[0][0], A01 = im.A[0][1], A10 = im.A[1][0], A11 = im.A[1][1];
+          const int c = (k - 7) & 3, tv = (k - 15) >> 2;
+          const double W = c_W[im.band][c];
+          const int t = k == 23 ? 0 : k == 24 ? 1 : 2;
+          double sv[3];
+          conj_A(im.A, m.sd1[t], sv);
+          const bool sk = k == 23 || k == 24 || k == 26;
+          double v0 = 0.0;
+          v0 = k == 0 ? A00 : k == 1 ? A01 : v0;
+          v0 = k == 2 ? aa * (1.0 - aa) : v0;
+          v0 = (k == 3 || k == 4) ? 1.0 : v0;
+          v0 = (k == 5 || k == 6) ? m.rv[k == 6] : v0;
+          v0 = (k >= 7 && k < 15) ? W : v0;
+          v0 = (k >= 15 && k < 23) ? W * W * m.cvv[tv & 1][c] : v0;
+          v0 = k == 25 ? pi * (1.0 - pi) : v0;
+          v0 = sk ? sv[0] : v0;
+          m.jv[k][0] = v0;
+          m.jv[k][1] = k == 0 ? A10 : k == 1 ? A11 : sk ? sv[1] : 0.0;
+          m.jv[k][2] = sk ? sv[2] : 0.0;
+          // the diagonal second-derivative terms sum_r Gr[r] d2r/dtheta_k^2 (outside the S block)
+          double dgk = 0.0;
+          dgk = k == 2 ? m.Gr[0] * aa * (1.0 - aa) * (1.0 - 2.0 * aa) : dgk;
+          dgk = (k == 5 || k == 6) ? m.Gr[2 + 2 * (k - 5)] * m.rv[k == 6] : dgk;
+          dgk = (k >= 15 && k < 23) ? m.Gr[2 + 2 * (tv & 1)] * W * W * m.cvv[tv & 1][c] : dgk;
+          dgk = k == 25 ? m.Gr[10] * pi * (1.0 - pi) * (1.0 - 2.0 * pi) : dgk;
+          m.dg[k] = dgk;
+        }
+        // S block (angle, radius, axis): sum_r Gr[r] d2S_r/dt dt'
+        if (lane >= 32 && lane < 41) {
+          const int si = (lane - 32) / 3, sk = (lane - 32) % 3;
+          double sv[3];
+          conj_A(im.A, m.sd2[si][sk], sv);
+          m.sblk[si][sk] = m.Gr[7] * sv[0] + m.Gr[8] * sv[1] + m.Gr[9] * sv[2];
+        }
+        wave_lds_sync();
+        // QJ = Qr J, then H += J^T QJ + the second-derivative terms (columns zero-padded; the
+        // rows of column k are jr[k][e])
+        for (int idx = lane; idx < kPrim * kN; idx += 64) {
+          const int r = idx / kN, k = idx % kN;
+          double v = 0;
+#pragma unroll
+          for (int y = 0; y < 3; ++y) v += m.Qr[r][m.jr[k][y]] * m.jv[k][y];
+          m.QJ[r][k] = v;
+        }
+        if (lane < kN)
+          gsum += m.jv[lane][0] * m.Gr[m.jr[lane][0]] + m.jv[lane][1] * m.Gr[m.jr[lane][1]] + m.jv[lane][2] * m.Gr[m.jr[lane][2]];
+        wave_lds_sync();
+#pragma unroll
+        for (int q6 = 0; q6 < kHPer; ++q6) {
+          const int i = ti[q6], k = tk[q6];
+          double v = 0;
+#pragma unroll
+          for (int x = 0; x < 3; ++x) v += m.jv[i][x] * m.QJ[m.jr[i][x]][k];
+          if (i == k) v += m.dg[i];
+          const int si = i == 23 ? 0 : i == 24 ? 1 : i == 26 ? 2 : -1;
+          const int sk = k == 23 ? 0 : k == 24 ? 1 : k == 26 ? 2 : -1;
+          if (si >= 0 && sk >= 0) v += m.sblk[si][sk];
+          hacc[q6] += v;
+        }
+        wave_lds_sync();
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kHPer; ++q)
+      if (lane + 64 * q < kHTri) part(w)[lane + 64 * q] = hacc[q];
+    if (lane < kN) part(w)[kHTri + lane] = gsum;
+    if (lane == 0) part(w)[kHTri + kN] = local;   // (every lane holds the same sum)
+  }
+  __syncthreads();
+  bool fin = true;
+  for (int e = threadIdx.x; e < kHTri + kN + 1; e += 64 * kHWaves) {
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kHParts; ++q) v += part(q)[e];
+    if (e < kHTri) {
+      int i, k;
+      tri_entry(e, i, k);
+      v += Hk[i][k];
+      fin = fin && isfinite(v);
+      a.hess[(int64_t)s * kN * kN + i * kN + k] = v;
+      a.hess[(int64_t)s * kN * kN + k * kN + i] = v;
+    } else if (e < kHTri + kN) {
+      a.grad[(int64_t)s * kThetaN + e - kHTri] = v + klg[e - kHTri];
+    } else {
+      a.local[s] = v - klg[kN];
     }
   }
-  if (a.with_kl) {
-    __shared__ double klw[16][kKlw], kls[2][kKlw];
-    kl_hessian_wave<kLd>(*a.prior, th, Hs, -1.0, lane, klw, kls);
-  }
-  __syncthreads();
-  if (lane == 0 && a.local) a.local[s] = local - klv;
-  if (a.grad && lane < kThetaN) a.grad[(int64_t)s * kThetaN + lane] = lane < kN ? gs[lane] : 0.0;
-  bool fin = true;
-  for (int idx = lane; idx < kN * kN; idx += 64) {
-    const double h = Hs[idx / kN][idx % kN];
-    fin = fin && isfinite(h);
-    a.hess[(int64_t)s * kN * kN + idx] = h;
-  }
+  if (threadIdx.x >= kN && threadIdx.x < kThetaN) a.grad[(int64_t)s * kThetaN + threadIdx.x] = 0.0;
   if (a.err && !fin) atomicOr(a.err, CEL_DEVERR_NONFINITE_HESSIAN);
 }
 
@@ -1097,12 +1114,6 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
 // every pair orthogonal to 1e-15; then lambda_k = |w_k| - c and v_k = w_k / |w_k|.
 constexpr int kTrWaves = 4;
 constexpr int kTrRounds = 40;
-
-// LDS written by lanes of one wavefront, read by other lanes of it
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-}
 
 __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
   const int s = a.job_src ? a.job_src[blockIdx.x] : (int)blockIdx.x;
@@ -1564,11 +1575,10 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   return hipGetLastError();
 }
 
-// Analytic per-source Hessians (pixel part, plus the KL part when with_kl) of the sources
-// flagged in `active` among `srcs` (device list, n_src entries; null = 0..S-1), with their
+// Analytic per-source Hessians (pixel and KL parts) of the sources flagged in `active` among `srcs` (device list, n_src entries; null = 0..S-1), with their
 // gradients and local objectives.  The base tables and maps must be current.
 static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_t* order, int n_items,
-                                  const int32_t* srcs, int n_src, const uint8_t* active, bool with_kl, double* local,
+                                  const int32_t* srcs, int n_src, const uint8_t* active, double* local,
                                   double* grad, double* hess, hipStream_t sm) {
   const bool fp64 = p->opt.pixel_fp64 || p->opt.hessian_fp64;
   hipError_t e = fp64 ? launch_hess_t<double>(p, order, n_items, active, sm)
@@ -1586,15 +1596,11 @@ static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_
   fa.pix_const = p->d_pixconst;
   fa.images = p->d_images;
   fa.prior = p->d_prior;
-  fa.with_kl = with_kl ? 1 : 0;
   fa.local = local;
   fa.grad = grad;
   fa.hess = hess;
-  fa.err = with_kl ? p->d_err : nullptr;   // the Newton path reports through the step status
-  fa.part = p->d_hpart;
-  hipLaunchKernelGGL(k_hess_finalize, dim3(n_src, kHParts), dim3(64), 0, sm, fa);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hess_combine, dim3(n_src), dim3(64), 0, sm, fa);
+  fa.err = p->d_err;
+  hipLaunchKernelGGL(k_hess_finalize, dim3(n_src), dim3(64 * kHWaves), 0, sm, fa);
   return hipGetLastError();
 }
 
@@ -1619,7 +1625,7 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
                               : prep_base(p, theta, sm, fp64);
     if (e == hipSuccess)
       e = enqueue_hessian(p, theta, p->d_class_tasks[cls], (int)p->class_tasks[cls].size(), p->d_class_src[cls], nsrc,
-                          active, true, p->v_local, p->v_grad, p->d_hess, sm);
+                          active, p->v_local, p->v_grad, p->d_hess, sm);
   } else {
     // gradients at the iterate and at the 54 central-difference points, then the Hessians
     e = eval_any(p, theta, nullptr, 0, 2 * kParamN + 1, true, cls, active, sm, true, fp64);
@@ -1891,7 +1897,7 @@ extern "C" cel_status cel_elbo_hessian(cel_ctx* ctx, const cel_plan* cplan, cons
   if (e == hipSuccess) e = hipEventRecord(p->mask_copied, sm);
   if (e == hipSuccess) e = prep_base(p, theta, sm, fp64);
   if (e == hipSuccess)
-    e = enqueue_hessian(p, theta, p->d_order, (int)p->n_tasks, nullptr, p->S, p->d_mask, true,
+    e = enqueue_hessian(p, theta, p->d_order, (int)p->n_tasks, nullptr, p->S, p->d_mask,
                         elbo_local ? elbo_local : p->v_local, grad ? grad : p->v_grad, hess, sm);
   return e == hipSuccess ? CEL_OK : CEL_EHIP;
 }
