@@ -960,7 +960,7 @@ extern "C" cel_status cel_plan_info(const cel_plan* plan, int64_t* n_units, int3
 namespace celmi {
 
 template <typename T>
-static hipError_t launch_maps_t(cel_plan* p, const Table<T>* tables, hipStream_t sm) {
+static hipError_t launch_maps_t(cel_plan* p, const Table<T>* tables, hipStream_t sm, const uint8_t* skip = nullptr) {
   MapArgs ma;
   std::memset(&ma, 0, sizeof(ma));
   ma.tasks = p->d_map_tasks;
@@ -968,6 +968,7 @@ static hipError_t launch_maps_t(cel_plan* p, const Table<T>* tables, hipStream_t
   ma.base = tables;
   ma.maps = sizeof(T) == 8 ? (void*)p->d_maps64 : (void*)p->d_maps;
   ma.img_npsf = p->d_npsf;
+  ma.skip = skip;
   return launch_maps<T>(ma, p->nexp, p->ndev, p->opt.map_pixels_per_lane, (int)p->map_tasks_h.size(), sm);
 }
 
@@ -1143,7 +1144,7 @@ hipError_t plain_eval(cel_plan* p, const double* theta, hipStream_t sm, bool fp6
 }
 
 template <typename T>
-static hipError_t prep_base_t(cel_plan* p, const double* theta, hipStream_t sm) {
+static hipError_t prep_base_t(cel_plan* p, const double* theta, hipStream_t sm, const uint8_t* stepped) {
   Table<T>* tables = reinterpret_cast<Table<T>*>(sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f);
   PrepArgs pa;
   std::memset(&pa, 0, sizeof(pa));
@@ -1160,12 +1161,12 @@ static hipError_t prep_base_t(cel_plan* p, const double* theta, hipStream_t sm) 
   pa.patch_psf = p->d_patch_psf;
   pa.records = p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0;
   hipError_t e = launch_prep_tables<T>(pa, p->P, 1, sm);
-  if (e == hipSuccess) e = launch_maps_t<T>(p, tables, sm);
+  if (e == hipSuccess) e = launch_maps_t<T>(p, tables, sm, stepped);
   return e;
 }
 
-hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64) {
-  return fp64 ? prep_base_t<double>(p, theta, sm) : prep_base_t<float>(p, theta, sm);
+hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64, const uint8_t* stepped) {
+  return fp64 ? prep_base_t<double>(p, theta, sm, stepped) : prep_base_t<float>(p, theta, sm, stepped);
 }
 
 template <typename T>

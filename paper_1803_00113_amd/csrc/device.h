@@ -140,6 +140,7 @@ struct MapArgs {
   const void* base;            // variant-0 tables
   void* maps;                  // out: (E_s, V_s) per packed pixel
   const int32_t* img_npsf;
+  const uint8_t* skip;         // per source: its maps are not read (nullptr = none)
 };
 
 // Arguments of the point-likelihood kernels.

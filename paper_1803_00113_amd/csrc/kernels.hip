@@ -374,6 +374,7 @@ __global__ __launch_bounds__(64 * W) void k_maps(MapArgs a) {
   const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
   const DMapTask task = a.tasks[pos];
   const DPatch P = a.patches[task.patch];
+  if (a.skip && a.skip[P.src]) return;
   const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.base) + task.patch;
   const int K = a.img_npsf[P.img];
   const T L0 = tb->hdr[0], L1 = tb->hdr[1], w0 = tb->hdr[2], w1 = tb->hdr[3];
@@ -463,6 +464,7 @@ __global__ __launch_bounds__(64) void k_maps_runs(MapArgs a) {
   const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
   const DMapTask task = a.tasks[pos];
   const DPatch P = a.patches[task.patch];
+  if (a.skip && a.skip[P.src]) return;
   const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.base) + task.patch;
   const int K = a.img_npsf[P.img];
   const int lane = threadIdx.x;

@@ -1739,7 +1739,8 @@ extern "C" cel_status cel_newton_step(cel_ctx* ctx, const cel_plan* cplan, doubl
   if (union_class) cls = p->n_colours;
   hipError_t e = stage_selection(p, m, union_class, sm);
   const bool maps_once = !p->opt.hessian_fd;
-  if (maps_once && e == hipSuccess && cls >= 0) e = prep_base(p, theta, sm, p->opt.pixel_fp64 || p->opt.hessian_fp64);
+  if (maps_once && e == hipSuccess && cls >= 0)
+    e = prep_base(p, theta, sm, p->opt.pixel_fp64 || p->opt.hessian_fp64, p->d_mask);
   if (cls == p->n_colours) {
     if (e == hipSuccess)
       e = enqueue_newton_class(p, theta, radius, p->d_mask, cls, step_status, elbo_local, false, sm, Made::kAll);
@@ -1821,7 +1822,9 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
       // the neighbours of this class keep their parameters during its iterations: their
       // moment maps are made once here (analytic Hessian path)
       const bool maps_once = !p->opt.hessian_fd;
-      if (maps_once && (e = prep_base(p, theta, sm, p->opt.pixel_fp64 || p->opt.hessian_fp64)) != hipSuccess) break;
+      if (maps_once &&
+          (e = prep_base(p, theta, sm, p->opt.pixel_fp64 || p->opt.hessian_fp64, p->d_mask)) != hipSuccess)
+        break;
       hipGraphExec_t exec = nullptr;
       if (o.use_graph) {
         auto& G = p->graphs[c];

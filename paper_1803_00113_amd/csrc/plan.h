@@ -172,8 +172,11 @@ hipError_t eval_any(cel_plan* p, const double* theta, const double* theta_trial,
                     const uint8_t* active, hipStream_t sm, bool prep_base, bool fp64, double* local_out = nullptr,
                     double* grad_out = nullptr);
 hipError_t plain_eval(cel_plan* p, const double* theta, hipStream_t sm, bool fp64);
-// component tables at the iterate for every patch and the neighbour moment maps
-hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64);
+// component tables at the iterate for every patch and the neighbour moment maps; stepped: per
+// source, the pairwise non-overlapping sources about to be stepped (device, null = none),
+// whose maps no one reads: a third of the map pass for the largest colour class of the
+// 1000-source batch (107 / 81 us)
+hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64, const uint8_t* stepped = nullptr);
 // component tables at the iterate for the patches of colour class cls only (sources flagged
 // in active); the maps are left as they are
 hipError_t prep_class(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm, bool fp64);
