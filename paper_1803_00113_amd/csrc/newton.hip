@@ -38,12 +38,6 @@ constexpr int kLd = kN + 1;   // padded LDS row
 
 
 
-// LDS written by lanes of one wavefront, read by other lanes of it
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // Hessian of KL_s in the unconstrained coordinates (the same KL as the objective: the type
 // KL, the normal KL of log r, the colour bound F = -log sum_j w_j exp(-D_j), and minus the
 // log prior densities of the radius, profile and axis point masses), times sc, added into
@@ -738,7 +732,7 @@ __global__ __launch_bounds__(64 * kHWaves) void k_hess_finalize(HessFinArgs a) {
       thr[k] = theta[k];
       gk[k] = 0.0;
     }
-    const double kv = kl_source_wave(*a.prior, thr, gk, 1.0, lane);   // every lane: gk = -grad KL
+    const double kv = kl_source_wave(*a.prior, thr, source_exps(thr, lane), gk, 1.0, lane);   // every lane: gk = -grad KL
     if (lane == 0) {
       klg[kN] = kv;
 #pragma unroll

@@ -123,7 +123,6 @@ static __device__ __constant__ double c_W[5][4] = {
     {-1, -1, 0, 0}, {0, -1, 0, 0}, {0, 0, 0, 0}, {0, 0, 1, 0}, {0, 0, 1, 1}};
 
 __device__ __forceinline__ double sigmoid(double x) { return 1.0 / (1.0 + exp(-x)); }
-__device__ __forceinline__ double softplus(double x) { return x > 0 ? x + log1p(exp(-x)) : log1p(exp(x)); }
 
 
 
@@ -226,6 +225,68 @@ __device__ __forceinline__ int wave_sums_slot(int lane) {
   }
 }
 
+// LDS written by lanes of one wavefront, read by other lanes of it
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The value `v` of the lane whose index differs in bit OFF (1, 2, 4 or 8), by data-parallel
+// moves instead of an LDS permute.  The 4 and 8 moves reverse a group of 8 or 16 lanes: they
+// are exchanges for values that the lanes of each quad (each group of 8) already share.
+template <int OFF>
+__device__ __forceinline__ double dpp_xor(double v) {
+  constexpr int ctrl = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+
+// sum and maximum over each group of 8 lanes, the same bits in every lane of a group
+__device__ __forceinline__ double sum8(double v) {
+  v += dpp_xor<1>(v);
+  v += dpp_xor<2>(v);
+  return v + dpp_xor<4>(v);
+}
+__device__ __forceinline__ double max8(double v) {
+  v = fmax(v, dpp_xor<1>(v));
+  v = fmax(v, dpp_xor<2>(v));
+  return fmax(v, dpp_xor<4>(v));
+}
+
+// Transcendental functions of a source's parameters, one argument per lane and broadcast, so
+// that each function's code runs once per wavefront (all 64 lanes active) instead of once per
+// value.
+struct SourceExps {
+  double rv[2], cv[2][4];        // flux and colour variances exp(th[5 + i]), exp(th[15 + 4 i + k])
+  double rad;                    // exp(th[24])
+  double a, prof, axis;          // sigmoid(th[2]), sigmoid(th[25]), sigmoid(th[26])
+};
+
+__device__ __forceinline__ SourceExps source_exps(const double* th, int lane) {
+  double x = 0.0;
+#pragma unroll
+  for (int l = 0; l < 14; ++l) {
+    const double v = l < 2 ? th[5 + l] : l < 10 ? th[13 + l] : l == 10 ? th[24] : l == 11 ? -th[2]
+                     : l == 12 ? -th[25] : -th[26];
+    x = lane == l ? v : x;
+  }
+  double e = exp(x);
+  if (lane >= 11) e = 1.0 / (1.0 + e);
+  SourceExps r;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    r.rv[i] = read_lane(e, i);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r.cv[i][k] = read_lane(e, 2 + 4 * i + k);
+  }
+  r.rad = read_lane(e, 10);
+  r.a = read_lane(e, 11);
+  r.prof = read_lane(e, 12);
+  r.axis = read_lane(e, 13);
+  return r;
+}
+
 // Colour bounds of both types (Section 4.2.3 at their optimal weights): the values
 // -log sum_j w_j exp(-D_j) and their gradients with respect to the colour means (gm) and
 // log colour variances (gv), summed over the prior components j with weights xi_j,
@@ -233,8 +294,8 @@ __device__ __forceinline__ int wave_sums_slot(int lane) {
 // takes prior component j of type i (lanes 16..63 repeat lanes 0..15), the maximum,
 // normaliser and gradient sums are combined by fixed butterflies within each group of 8
 // lanes, and every lane receives both types' results.
-__device__ inline void colour_bound_wave(const DPrior& pr, const double* th, int lane, double* kc, double (*gm)[4],
-                                         double (*gv)[4]) {
+__device__ inline void colour_bound_wave(const DPrior& pr, const double* th, const SourceExps& ex, int lane, double* kc,
+                                         double (*gm)[4], double (*gv)[4]) {
   static_assert(CEL_N_COLOUR_COMPONENTS == 8, "one lane per prior colour component, groups of 8");
   const int i = (lane >> 3) & 1, j = lane & 7;
   double cm[4], cv[4], lcv[4];
@@ -242,7 +303,7 @@ __device__ inline void colour_bound_wave(const DPrior& pr, const double* th, int
   for (int k = 0; k < 4; ++k) {   // selects, not a lane-dependent index into th
     cm[k] = i ? th[11 + k] : th[7 + k];
     lcv[k] = i ? th[19 + k] : th[15 + k];
-    cv[k] = exp(lcv[k]);
+    cv[k] = i ? ex.cv[1][k] : ex.cv[0][k];
   }
   const double sum_lcv = lcv[0] + lcv[1] + lcv[2] + lcv[3];
   double tr = 0, maha = 0, row[4];
@@ -256,61 +317,62 @@ __device__ inline void colour_bound_wave(const DPrior& pr, const double* th, int
     maha += (cm[k] - pr.c_mean[i][j][k]) * r;
   }
   const double e = pr.c_logw[i][j] - 0.5 * (tr + maha - 4.0 + pr.c_logdet[i][j] - sum_lcv);
-  double mx = e;
-#pragma unroll
-  for (int off = 1; off < 8; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-  const double ex = exp(e - mx);
-  double z = ex;
-#pragma unroll
-  for (int off = 1; off < 8; off <<= 1) z += __shfl_xor(z, off, 64);
-  const double xi = ex / z;
+  const double mx = max8(e);
+  const double w = exp(e - mx);
+  const double z = sum8(w);
+  const double xi = w / z;
   double part[9];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    part[k] = xi * row[k];
-    part[4 + k] = xi * 0.5 * (pr.c_prec[i][j][k][k] * cv[k] - 1.0);
+    part[k] = sum8(xi * row[k]);
+    part[4 + k] = sum8(xi * 0.5 * (pr.c_prec[i][j][k][k] * cv[k] - 1.0));
   }
   part[8] = -(mx + log(z));
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-#pragma unroll
-    for (int off = 1; off < 8; off <<= 1) part[q] += __shfl_xor(part[q], off, 64);
-  }
-  // this lane's group holds type i; the other type comes from the group 8 lanes away
-  double other[9];
-#pragma unroll
-  for (int q = 0; q < 9; ++q) other[q] = __shfl_xor(part[q], 8, 64);
-  const bool first = i == 0;
+  // lanes 0..7 hold type 0, lanes 8..15 type 1
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    gm[0][k] = first ? part[k] : other[k];
-    gm[1][k] = first ? other[k] : part[k];
-    gv[0][k] = first ? part[4 + k] : other[4 + k];
-    gv[1][k] = first ? other[4 + k] : part[4 + k];
+    gm[0][k] = read_lane(part[k], 0);
+    gm[1][k] = read_lane(part[k], 8);
+    gv[0][k] = read_lane(part[4 + k], 0);
+    gv[1][k] = read_lane(part[4 + k], 8);
   }
-  kc[0] = first ? part[8] : other[8];
-  kc[1] = first ? other[8] : part[8];
+  kc[0] = read_lane(part[8], 0);
+  kc[1] = read_lane(part[8], 8);
 }
 
 // KL(q(z_s) || p(z_s)) and its gradient in the unconstrained coordinates (equations eq:kl,
 // kleq; Supplement A with the readings: flux KL is the normal KL of log r with variances;
 // colour KL is the bound of Section 4.2.3 at its optimal weights; point-mass terms are
-// minus the log prior density; direction and angle terms are constants and dropped), given
-// the colour bounds kc and their gradients.  Subtracts gs times the gradient from g.
-__device__ inline double kl_assemble(const DPrior& pr, const double* th, double* g, double gs, const double* kc,
-                                     const double (*gm)[4], const double (*gv)[4]) {
+// minus the log prior density; direction and angle terms are constants and dropped), by a
+// whole wavefront (all lanes active; every lane gets the value and applies the gradient to
+// its own g).  Subtracts gs times the gradient from g.  Its time is the latency of its
+// transcendental functions (14 exponentials, six log1p, four logarithms when each lane took
+// them all), so they are taken across lanes: the finalisation of 3 sources without a gradient,
+// little else than the KL, 9.1 -> 6.4 us.
+__device__ inline double kl_source_wave(const DPrior& pr, const double* th, const SourceExps& ex, double* g, double gs,
+                                        int lane) {
+  double kc[2], gm[2][4], gv[2][4];
+  colour_bound_wave(pr, th, ex, lane, kc, gm, gv);
+  // lanes 0-2: softplus(x) = max(x, 0) + log1p(exp(-|x|)) of the type, profile and axis logits
+  // (the second term serves x and -x); lanes 3-5: logs of the flux and radius prior variances
+  const double lx = lane == 0 ? th[2] : lane == 1 ? th[25] : th[26];
+  const double sp = log1p(exp(-fabs(lx)));
+  const double lg = log(lane == 3 ? pr.r[0][1] : lane == 4 ? pr.r[1][1] : 2.0 * M_PI * pr.radius[1]);
+  const double l1p[3] = {read_lane(sp, 0), read_lane(sp, 1), read_lane(sp, 2)};
+  const double log_R2[2] = {read_lane(lg, 3), read_lane(lg, 4)}, log_E2 = read_lane(lg, 5);
+  auto softplus = [](double x, double l) { return fmax(x, 0.0) + l; };
   const double eta = th[2];
-  const double a = sigmoid(eta);
-  const double log_a = -softplus(-eta), log_1ma = -softplus(eta);
+  const double a = ex.a;
+  const double log_a = -softplus(-eta, l1p[0]), log_1ma = -softplus(eta, l1p[0]);
   double kl = a * (log_a - pr.log_a) + (1.0 - a) * (log_1ma - pr.log_1ma);
   double dk_da = eta - pr.logit_a;          // d KL_a / d a
   const double q[2] = {1.0 - a, a};
   double part[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const double rm = th[3 + i], lrv = th[5 + i], rv = exp(lrv);
+    const double rm = th[3 + i], lrv = th[5 + i], rv = ex.rv[i];
     const double R1 = pr.r[i][0], R2 = pr.r[i][1];
-    const double kr = 0.5 * (log(R2) - lrv) + (rv + (rm - R1) * (rm - R1)) / (2.0 * R2) - 0.5;
+    const double kr = 0.5 * (log_R2[i] - lrv) + (rv + (rm - R1) * (rm - R1)) / (2.0 * R2) - 0.5;
     g[3 + i] -= gs * q[i] * (rm - R1) / R2;
     g[5 + i] -= gs * q[i] * (-0.5 + rv / (2.0 * R2));
 #pragma unroll
@@ -325,28 +387,20 @@ __device__ inline double kl_assemble(const DPrior& pr, const double* th, double*
   g[2] -= gs * (dk_da * a * (1.0 - a));
   // radius: point mass vs log-normal
   const double lr = th[24], E1 = pr.radius[0], E2 = pr.radius[1];
-  kl += lr + 0.5 * log(2.0 * M_PI * E2) + (lr - E1) * (lr - E1) / (2.0 * E2);
+  kl += lr + 0.5 * log_E2 + (lr - E1) * (lr - E1) / (2.0 * E2);
   g[24] -= gs * (1.0 + (lr - E1) / E2);
   // profile and axis: point mass vs Beta
   {
-    const double e = th[25], p = sigmoid(e), lp = -softplus(-e), l1p = -softplus(e);
-    kl += -(pr.profile[0] - 1.0) * lp - (pr.profile[1] - 1.0) * l1p + pr.lbeta_profile;
+    const double e = th[25], p = ex.prof, lp = -softplus(-e, l1p[1]), lq = -softplus(e, l1p[1]);
+    kl += -(pr.profile[0] - 1.0) * lp - (pr.profile[1] - 1.0) * lq + pr.lbeta_profile;
     g[25] -= gs * (-(pr.profile[0] - 1.0) * (1.0 - p) + (pr.profile[1] - 1.0) * p);
   }
   {
-    const double e = th[26], p = sigmoid(e), lp = -softplus(-e), l1p = -softplus(e);
-    kl += -(pr.axis[0] - 1.0) * lp - (pr.axis[1] - 1.0) * l1p + pr.lbeta_axis;
+    const double e = th[26], p = ex.axis, lp = -softplus(-e, l1p[2]), lq = -softplus(e, l1p[2]);
+    kl += -(pr.axis[0] - 1.0) * lp - (pr.axis[1] - 1.0) * lq + pr.lbeta_axis;
     g[26] -= gs * (-(pr.axis[0] - 1.0) * (1.0 - p) + (pr.axis[1] - 1.0) * p);
   }
   return kl;
-}
-
-// KL and gradient by a whole wavefront (all lanes active; every lane gets the value and
-// applies the gradient to its own g)
-__device__ inline double kl_source_wave(const DPrior& pr, const double* th, double* g, double gs, int lane) {
-  double kc[2], gm[2][4], gv[2][4];
-  colour_bound_wave(pr, th, lane, kc, gm, gv);
-  return kl_assemble(pr, th, g, gs, kc, gm, gv);
 }
 
 }  // namespace celmi
