@@ -1020,12 +1020,12 @@ __device__ __forceinline__ double wave_max(double v) {
 // (B + lam I) p = g by an unpivoted L D L^T factorisation of one wavefront: lane c < 27 holds
 // column c in registers, a step broadcasts the pivot column by lane reads, and p is p_c in
 // lane c.  Returns false (uniformly) when a pivot is not positive: B + lam I is not positive
-// definite.  Otherwise w = (B + lam I)^-1 p, like p, and sums: |p|^2, p . w and g . p, in
-// every lane.
+// definite.  Otherwise sums: |p|^2, p . w with w = (B + lam I)^-1 p, and g . p, in every
+// lane, and w itself, like p, where |p| is within 1e-7 of the radius.
 // Unlike an eigen-decomposition, whose errors are relative to |B|, the factorisation keeps
 // the small entries of a badly scaled B (a type logit far from 0) to relative precision.
-__device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, double g_c, int lane, double& p,
-                                          double& w, double* sums) {
+__device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, double g_c, double radius, int lane,
+                                          double& p, double& w, double* sums) {
   // (lane comparisons are made afresh for each factorisation: 27 masks held across the
   // caller's loop would spill)
   asm volatile("" : "+v"(lane));
@@ -1069,17 +1069,20 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
     const double l = lane > j ? A[j] * read_lane(iown, j) : 0.0;
     q = fma(-read_lane(q, j), l, q);
   }
-  w = q * iown;
-#pragma unroll
-  for (int k = kN - 1; k > 0; --k) {
-    const double l = lane < k ? A[k] * iown : 0.0;
-    w = fma(-read_lane(w, k), l, w);
-  }
   const bool own = lane < kN;
   const double v[3] = {own ? p * p : 0.0, own ? q * q * iown : 0.0, own ? z * z * iown : 0.0};
   const double sv = wave_sums<3>(v, lane);
 #pragma unroll
   for (int i = 0; i < 3; ++i) sums[i] = read_lane(sv, wave_sums_lane<3>(i));
+  w = 0.0;
+  if (fabs(sqrt(sums[0]) - radius) <= 1e-7 * radius) {
+    w = q * iown;
+#pragma unroll
+    for (int k = kN - 1; k > 0; --k) {
+      const double l = lane < k ? A[k] * iown : 0.0;
+      w = fma(-read_lane(w, k), l, w);
+    }
+  }
   return true;
 }
 
@@ -1181,7 +1184,7 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
     int winner = -1;
     for (int round = 0; round < kTrRounds && winner < 0; ++round) {
       double p, w, sums[3], np = -1.0, newton = 0.0;
-      if (ldl_solve(B, lam, g_c, lane, p, w, sums)) {
+      if (ldl_solve(B, lam, g_c, radius, lane, p, w, sums)) {
         np = sqrt(sums[0]);
         newton = lam + (sums[0] / sums[1]) * (np - radius) / radius;
       }
@@ -1453,8 +1456,9 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
 }
 
 struct AcceptArgs {
-  const int32_t* job_src;
+  const int32_t* job_src;     // stepped sources (null: source = job); with `skipped` all sources are jobs
   int32_t n_jobs;
+  int32_t skipped;            // 1: sources not flagged in active get the skipped status
   uint8_t* active;            // stepped sources (cleared on convergence when clear_done)
   int32_t clear_done;
   const uint8_t* trial_active;
@@ -1470,39 +1474,47 @@ struct AcceptArgs {
   double eta, radius_max;
 };
 
-__global__ __launch_bounds__(64) void k_accept(AcceptArgs a) {
-  const int jj = blockIdx.x * 64 + threadIdx.x;
+// 32 lanes per source, one of its parameters each (one thread per source copied them one
+// after another: 7 us a launch, whatever the number of sources); the skipped sources' status
+// in the same launch.
+__global__ __launch_bounds__(256) void k_accept(AcceptArgs a) {
+  const int jj = blockIdx.x * 8 + (int)(threadIdx.x >> 5), k = threadIdx.x & 31;
+  static_assert(kThetaN == 32, "one lane per parameter");
   if (jj >= a.n_jobs) return;
   const int s = a.job_src ? a.job_src[jj] : jj;
-  if (!a.active[s]) return;
-  const double L = a.local0[s];
+  if (!a.active[s]) {
+    if (a.skipped && k == 0) {
+      a.status[s] = CEL_ST_SKIPPED;
+      if (a.out_local) a.out_local[s] = __longlong_as_double(0x7ff8000000000000LL);
+    }
+    return;
+  }
+  const double L = a.local0[s], Lt = a.local_trial[s], pn = a.pnorm[s], pred = a.pred[s], radius = a.radius[s];
+  const double trial = a.theta_trial[(int64_t)s * kThetaN + k];
   double Lout = L;
   if (a.trial_active[s]) {
-    const double Lt = a.local_trial[s];
-    const double pn = a.pnorm[s];
-    double r = a.radius[s];
-    int st;
+    double r = radius;
+    int st = CEL_ST_REJECTED;
     if (!isfinite(Lt)) {
       r = 0.25 * pn;
-      st = CEL_ST_REJECTED;
     } else {
-      const double rho = (Lt - L) / a.pred[s];
+      const double rho = (Lt - L) / pred;
       if (rho < 0.25) r = 0.25 * pn;
       else if (rho > 0.75 && pn >= 0.99 * r) r = fmin(2.0 * r, a.radius_max);
       if (rho > a.eta) {
         st = CEL_ST_ACCEPTED;
-        for (int k = 0; k < kThetaN; ++k) a.theta[(int64_t)s * kThetaN + k] = a.theta_trial[(int64_t)s * kThetaN + k];
+        a.theta[(int64_t)s * kThetaN + k] = trial;
         Lout = Lt;
-      } else {
-        st = CEL_ST_REJECTED;
       }
     }
-    a.radius[s] = r;
-    a.status[s] = st;
-  } else if (a.clear_done) {
+    if (k == 0) {
+      a.radius[s] = r;
+      a.status[s] = st;
+    }
+  } else if (a.clear_done && k == 0) {
     a.active[s] = 0;   // converged or non-finite: done for this colour class
   }
-  if (a.out_local) a.out_local[s] = Lout;
+  if (a.out_local && k == 0) a.out_local[s] = Lout;
 }
 
 __global__ __launch_bounds__(256) void k_skipped(const uint8_t* __restrict__ mask, int S, int32_t* status,
@@ -1603,10 +1615,11 @@ static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_
 // them once per class), so that only the class's own tables are rebuilt; or both.
 enum class Made { kNothing, kMaps, kAll };
 
-// One Newton iteration of colour class `cls` on the sources flagged in `active`.
+// One Newton iteration of colour class `cls` on the sources flagged in `active`; with
+// mark_skipped (all flagged sources are the class's) the others get the skipped status.
 static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radius, uint8_t* active, int cls,
                                        int32_t* status, double* out_local, bool clear_done, hipStream_t sm,
-                                       Made made = Made::kNothing) {
+                                       Made made = Made::kNothing, bool mark_skipped = false) {
   const bool fp64 = p->opt.pixel_fp64 || p->opt.hessian_fp64;
   const int nsrc = (int)p->class_src[cls].size();
   if (nsrc == 0) return hipSuccess;
@@ -1667,8 +1680,9 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   if (e != hipSuccess) return e;
   AcceptArgs aa;
   std::memset(&aa, 0, sizeof(aa));
-  aa.job_src = p->d_class_src[cls];
-  aa.n_jobs = nsrc;
+  aa.job_src = mark_skipped ? nullptr : p->d_class_src[cls];
+  aa.n_jobs = mark_skipped ? p->S : nsrc;
+  aa.skipped = mark_skipped ? 1 : 0;
   aa.active = active;
   aa.clear_done = clear_done ? 1 : 0;
   aa.trial_active = p->d_trial_active;
@@ -1683,7 +1697,7 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   aa.out_local = out_local;
   aa.eta = p->opt.eta;
   aa.radius_max = p->opt.radius_max;
-  hipLaunchKernelGGL(k_accept, dim3((nsrc + 63) / 64), dim3(64), 0, sm, aa);
+  hipLaunchKernelGGL(k_accept, dim3((aa.n_jobs + 7) / 8), dim3(256), 0, sm, aa);
   return hipGetLastError();
 }
 
@@ -1735,17 +1749,17 @@ extern "C" cel_status cel_newton_step(cel_ctx* ctx, const cel_plan* cplan, doubl
   const bool maps_once = !p->opt.hessian_fd;
   if (maps_once && e == hipSuccess && cls >= 0)
     e = prep_base(p, theta, sm, p->opt.pixel_fp64 || p->opt.hessian_fp64, p->d_mask);
-  if (cls == p->n_colours) {
+  const bool one = maps_once && cls >= 0;   // one batch holds every stepped source
+  if (one) {
     if (e == hipSuccess)
-      e = enqueue_newton_class(p, theta, radius, p->d_mask, cls, step_status, elbo_local, false, sm, Made::kAll);
+      e = enqueue_newton_class(p, theta, radius, p->d_mask, cls, step_status, elbo_local, false, sm, Made::kAll, true);
   } else {
     for (int c : used) {
       if (e != hipSuccess) break;
-      e = enqueue_newton_class(p, theta, radius, p->d_mask, c, step_status, elbo_local, false, sm,
-                               maps_once ? Made::kAll : Made::kNothing);
+      e = enqueue_newton_class(p, theta, radius, p->d_mask, c, step_status, elbo_local, false, sm);
     }
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !one) {
     hipLaunchKernelGGL(k_skipped, dim3((p->S + 255) / 256), dim3(256), 0, sm, p->d_mask, p->S, step_status,
                        elbo_local);
     e = hipGetLastError();
