@@ -1026,9 +1026,14 @@ __device__ __forceinline__ double wave_max(double v) {
 // the small entries of a badly scaled B (a type logit far from 0) to relative precision.
 __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, double g_c, double radius, int lane,
                                           double& p, double& w, double* sums) {
-  // (lane comparisons are made afresh for each factorisation: 27 masks held across the
-  // caller's loop would spill)
-  asm volatile("" : "+v"(lane));
+  // The lane's index, made to look new at every step (`x`: a value formed there): comparisons
+  // with it are then made where they are used, where 27 masks held in scalar registers would
+  // leave the lane reads one register pair, and a wait each.
+  auto lane_at = [&](double x) {
+    int l = lane;
+    asm("" : "+v"(l) : "v"(__double2loint(x)));
+    return l;
+  };
   const int cc = lane < kN ? lane : 0;
   double A[kN], z = g_c, iown = 0.0;
 #pragma unroll
@@ -1041,8 +1046,9 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
   double d = read_lane(A[0], 0), inv = reciprocal(d), dmin = d;
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
-    const double l = lane > j ? A[j] * inv : 0.0;   // L[c][j] (lanes past 26 repeat column 0's rows)
-    if (lane == j) iown = inv;
+    const int ln = lane_at(inv);
+    const double l = ln > j ? A[j] * inv : 0.0;   // L[c][j] (lanes past 26 repeat column 0's rows)
+    iown = ln == j ? inv : iown;
     const double zj = read_lane(z, j);
     if (j + 1 < kN) {   // the next pivot first: its reciprocal is the chain's latency
       A[j + 1] = fma(-read_lane(A[j + 1], j), l, A[j + 1]);
@@ -1050,8 +1056,18 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
       dmin = fmin(dmin, d);
       inv = reciprocal(d);
     }
+    constexpr int kRun = 8;   // lane reads issued together, ahead of the products that wait for them
 #pragma unroll
-    for (int r = j + 2; r < kN; ++r) A[r] = fma(-read_lane(A[r], j), l, A[r]);
+    for (int r0 = j + 2; r0 < kN; r0 += kRun) {
+      double v[kRun];
+#pragma unroll
+      for (int u = 0; u < kRun; ++u)
+        if (r0 + u < kN) v[u] = read_lane(A[r0 + u], j);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kRun; ++u)
+        if (r0 + u < kN) A[r0 + u] = fma(-v[u], l, A[r0 + u]);
+    }
     z = fma(-zj, l, z);
   }
   if (!(dmin > 1e-290)) return false;
@@ -1060,13 +1076,13 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
   p = z * iown;
 #pragma unroll
   for (int k = kN - 1; k > 0; --k) {
-    const double l = lane < k ? A[k] * iown : 0.0;   // L[k][c]
+    const double l = lane_at(p) < k ? A[k] * iown : 0.0;   // L[k][c]
     p = fma(-read_lane(p, k), l, p);
   }
   double q = p;
 #pragma unroll
   for (int j = 0; j < kN - 1; ++j) {
-    const double l = lane > j ? A[j] * read_lane(iown, j) : 0.0;
+    const double l = lane_at(q) > j ? A[j] * read_lane(iown, j) : 0.0;
     q = fma(-read_lane(q, j), l, q);
   }
   const bool own = lane < kN;
@@ -1079,7 +1095,7 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
     w = q * iown;
 #pragma unroll
     for (int k = kN - 1; k > 0; --k) {
-      const double l = lane < k ? A[k] * iown : 0.0;
+      const double l = lane_at(w) < k ? A[k] * iown : 0.0;
       w = fma(-read_lane(w, k), l, w);
     }
   }
