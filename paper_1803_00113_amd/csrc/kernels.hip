@@ -32,11 +32,13 @@ __device__ __forceinline__ void load_theta(const double* theta, const double* th
                                            int v, double h, double* th, int trial_v, int fd) {
   const double* src = (v == trial_v && theta_trial) ? theta_trial + (int64_t)s * kThetaN
                                                     : theta + (int64_t)v * vstride + (int64_t)s * kThetaN;
-  // the perturbed coordinate is selected arithmetically so that th stays in registers
-  const int kp = (fd && v >= 1 && v <= kParamN) ? v - 1 : -1;
-  const int km = (fd && v > kParamN && v <= 2 * kParamN) ? v - 1 - kParamN : -1;
 #pragma unroll
-  for (int k = 0; k < kThetaN; ++k) th[k] = src[k] + (k == kp ? h : 0.0) - (k == km ? h : 0.0);
+  for (int k = 0; k < kThetaN; ++k) th[k] = src[k];
+  if (!fd || v < 1 || v > 2 * kParamN) return;
+  // the perturbed coordinate is selected arithmetically so that th stays in registers
+  const int kp = v <= kParamN ? v - 1 : -1, km = v > kParamN ? v - 1 - kParamN : -1;
+#pragma unroll
+  for (int k = 0; k < kThetaN; ++k) th[k] = th[k] + (k == kp ? h : 0.0) - (k == km ? h : 0.0);
 }
 
 // Galaxy covariance Sigma_s = R^T diag(r^2, axis^2 r^2) R, R = [[c,-s],[s,c]] (Section 2.1.2)
@@ -48,7 +50,10 @@ __device__ __forceinline__ void galaxy_cov(double angle, double radius, double a
 }
 
 // ----------------------------------------------------------------------------------------
-// k_prep_tables: one wavefront per (variant, patch)
+// k_prep_tables: one wavefront per (variant, patch).  Small launches last the latency of its
+// FP64 chain (6.4 us), large ones its VALU issue (10000 patches 22 us; 8.2 and 27.2 when the
+// perturbed coordinate was selected for every parameter of every launch, broadcasts went
+// through LDS and a second pass wrote the unused fourth PSF component's records).
 
 template <typename T>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 1))) void k_prep_tables(
@@ -81,7 +86,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   if (lane >= 11 && lane <= 13) eval = 1.0 / (1.0 + eval);
   double ex[14];
 #pragma unroll
-  for (int l = 0; l < 14; ++l) ex[l] = __shfl(eval, l, 64);
+  for (int l = 0; l < 14; ++l) ex[l] = read_lane(eval, l);
   double sig[3];
   galaxy_cov(th[23], ex[10], ex[12], sig);
   // pixel-frame galaxy covariance S = A Sigma A^T
@@ -115,16 +120,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   double L[2], kk[2], ee[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    L[i] = im.iota * __shfl(ev2, i, 64);
-    ee[i] = __shfl(ev2, 2 + i, 64);
+    L[i] = im.iota * read_lane(ev2, i);
+    ee[i] = read_lane(ev2, 2 + i);
     kk[i] = w[i] * L[i] * L[i] * ee[i];
   }
   // component cuts below scale with the flux: log2 of L0, L1 and the sky minimum, one per lane
   const double smin = a.sky_min ? a.sky_min[pi_] : 0.0;
   const double larg = lane == 0 ? L[0] : lane == 1 ? L[1] : smin;
   const double lg = log2(larg);
-  const double cut_gal = density_cut_log2<T>(L[0], smin, __shfl(lg, 0, 64), __shfl(lg, 2, 64));
-  const double cut_star = density_cut_log2<T>(L[1], smin, __shfl(lg, 1, 64), __shfl(lg, 2, 64));
+  const double cut_gal = density_cut_log2<T>(L[0], smin, read_lane(lg, 0), read_lane(lg, 2));
+  const double cut_star = density_cut_log2<T>(L[1], smin, read_lane(lg, 1), read_lane(lg, 2));
   if (lane == 0) {
     tb->hdr[8] = (T)ee[0];
     tb->hdr[9] = (T)ee[1];
@@ -139,17 +144,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     tb->hdr[10] = (T)mux;
     tb->hdr[11] = (T)muy;
   }
-  // components: 4 star slots then 4 x 16 galaxy slots
-  const int n_slots = (a.records & kRecUsedType) && w[0] == 0.0 ? kMaxPsf : kMaxPsf + kMaxPsf * 2 * kMaxProf;
+  // components: K star slots then K x 16 galaxy slots, one per lane (K <= 3: one pass)
+  const int n_slots = (a.records & kRecUsedType) && w[0] == 0.0 ? K : K + K * 2 * kMaxProf;
   for (int c = lane; c < n_slots; c += 64) {
-    // a star slot (c < kMaxPsf) or a galaxy slot: the same 2x2 algebra, one code path
-    const bool star = c < kMaxPsf;
-    const int g = c - kMaxPsf;
+    // a star slot (c < K) or a galaxy slot: the same 2x2 algebra, one code path
+    const bool star = c < K;
+    const int g = c - K;
     const int k = star ? c : g / (2 * kMaxProf), j = star ? 0 : g % (2 * kMaxProf);
     const bool isdev = j >= kMaxProf;
     const int jj = isdev ? j - kMaxProf : j;
     const int nj = isdev ? a.prof->n_dev : a.prof->n_exp;
-    const bool used = k < K && (star || jj < nj);
+    const bool used = star || jj < nj;
     double tau = 0.0, Pxx = 0.0, Pxy = 0.0, Pyy = 0.0, lw = kNegHuge, rc2 = -1.0;
     if (used) {   // (an iteration whose slots are all unused skips the math)
       const int pj = isdev ? a.prof->n_exp + jj : jj;
