@@ -15,10 +15,9 @@ namespace celmi {
 // error 8e-18; 0.8 ulp with the evaluation's rounding), scaled by 2^n.  0 below 2^-1100
 // (-infinity included), NaN stays NaN; x must not exceed 2^31.  About 18 operations against
 // the library's 26.
-__device__ __forceinline__ double exp2_fp64(double x) {
-  constexpr double kMagic = 6755399441055744.0;   // 1.5 * 2^52: x + kMagic holds n in its low bits
-  const double t = x + kMagic;
-  const double f = x - (t - kMagic);
+constexpr double kExp2Magic = 6755399441055744.0;   // 1.5 * 2^52: x + it holds n in the low bits
+// 2^f 2^n for |f| <= 1/2, n in the low bits of t
+__device__ __forceinline__ double exp2_reduced(double f, double t) {
   double r = 4.4549605981865186e-10;
   r = fma(f, r, 7.072585949269223e-09);
   r = fma(f, r, 1.0178062445845774e-07);
@@ -30,8 +29,18 @@ __device__ __forceinline__ double exp2_fp64(double x) {
   r = fma(f, r, 5.55041086648216e-02);
   r = fma(f, r, 2.4022650695910097e-01);
   r = fma(f, r, 6.931471805599453e-01);
-  r = __builtin_amdgcn_ldexp(fma(f, r, 1.0), __double2loint(t));
+  return __builtin_amdgcn_ldexp(fma(f, r, 1.0), __double2loint(t));
+}
+__device__ __forceinline__ double exp2_fp64(double x) {
+  const double t = x + kExp2Magic;
+  const double r = exp2_reduced(x - (t - kExp2Magic), t);
   return x < -1100.0 ? 0.0 : r;
+}
+// 2^(q h) for a factor h = hi + lo: no rounding of the product or of h
+__device__ __forceinline__ double exp2_fp64(double q, double hi, double lo) {
+  const double t = fma(q, hi, kExp2Magic);
+  const double r = exp2_reduced(fma(q, lo, fma(q, hi, -(t - kExp2Magic))), t);
+  return q * hi < -1100.0 ? 0.0 : r;
 }
 
 template <typename T> __device__ __forceinline__ T fexp2(T x);

@@ -17,7 +17,7 @@
 // parameter; the covariance's inverse and normaliser are formed once per component and
 // iteration; the exponential is exp2_fp64.  4000 fits of K = 3 on 51 x 51 knots, 30
 // iterations: 3.54 ms before (one column-free loop for every K, divisions and library exponentials
-// per knot), 1.22 ms after, about 30 operations per component and knot.
+// per knot), 1.30 ms after, about 32 operations per component and knot.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -77,10 +77,11 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fit(PsfFitArgs a) {
   extern __shared__ double wts[];   // side * side
   __shared__ double red[kPsfWaves][kPsfSums];
   __shared__ double mean[2];
-  // a component's weight / (2 pi sqrt(det)), mean, covariance yy, -2 xy and xx, and the
-  // exponent's factor -log2(e) / (2 det): applied last, so that a knot's exponent carries one
-  // common rounding, the factor's
-  __shared__ double cf[K][7];
+  // a component's density: mean, covariance yy, -2 xy and xx, and, each in two parts, the
+  // exponent's factor -log2(e) / (2 det) and weight / (2 pi sqrt(det)): a knot's rounding
+  // averages out over the knots, a component's would shift the whole fit
+  enum { kMx, kMy, kYY, kXY, kXX, kH, kHLo, kW, kWLo, kCf };
+  __shared__ double cf[K][kCf];
   const int f = blockIdx.x;
   const int tid = threadIdx.x;
   const int n = a.fit_img[f];
@@ -157,25 +158,36 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fit(PsfFitArgs a) {
   for (int it = 0; it < a.n_iter; ++it) {
     if (tid < K) {
       const double det = mix[3] * mix[5] - mix[4] * mix[4];
-      cf[tid][0] = mix[0] / (2.0 * M_PI * sqrt(det));
-      cf[tid][1] = mix[1];
-      cf[tid][2] = mix[2];
-      cf[tid][3] = mix[5];
-      cf[tid][4] = -2.0 * mix[4];
-      cf[tid][5] = mix[3];
-      cf[tid][6] = -0.5 * kLog2e / det;
+      // -log2(e) / 2 and 2 pi as sums of two doubles
+      constexpr double kL = -0.5 * kLog2e, kLLo = -0.5 * 2.0355273740931033e-17;
+      constexpr double kP = 2.0 * M_PI, kPLo = 2.4492935982947064e-16;
+      const double h = kL / det;
+      const double r = sqrt(det), r_lo = fma(-r, r, det) / (2.0 * r);
+      const double n = kP * r, n_lo = fma(kP, r, -n) + kP * r_lo + kPLo * r;
+      const double w = mix[0] / n;
+      cf[tid][kMx] = mix[1];
+      cf[tid][kMy] = mix[2];
+      cf[tid][kYY] = mix[5];
+      cf[tid][kXY] = -2.0 * mix[4];
+      cf[tid][kXX] = mix[3];
+      cf[tid][kH] = h;
+      cf[tid][kHLo] = (fma(-h, det, kL) + kLLo) / det;
+      cf[tid][kW] = w;
+      cf[tid][kWLo] = (fma(-w, n, mix[0]) - w * n_lo) / n;
     }
     __syncthreads();   // cf is written; red is free again
-    double e0[K], e1[K], e2[K], h[K], wn[K], ym[K], s0[K], s1[K], s2[K];
+    double e0[K], e1[K], e2[K], h[K], h_lo[K], wn[K], wn_lo[K], ym[K], s0[K], s1[K], s2[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const double ex = dx - cf[k][1];
-      wn[k] = cf[k][0];
-      ym[k] = cf[k][2];
-      e0[k] = cf[k][3] * ex * ex;
-      e1[k] = cf[k][4] * ex;
-      e2[k] = cf[k][5];
-      h[k] = cf[k][6];
+      const double ex = dx - cf[k][kMx];
+      ym[k] = cf[k][kMy];
+      e0[k] = cf[k][kYY] * ex * ex;
+      e1[k] = cf[k][kXY] * ex;
+      e2[k] = cf[k][kXX];
+      h[k] = cf[k][kH];
+      h_lo[k] = cf[k][kHLo];
+      wn[k] = cf[k][kW];
+      wn_lo[k] = cf[k][kWLo];
       s0[k] = s1[k] = s2[k] = 0.0;
     }
     dy = row0 - c;
@@ -184,13 +196,15 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fit(PsfFitArgs a) {
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         const double ey = dy - ym[k];
-        comp[k] = wn[k] * exp2_fp64(h[k] * fma(ey, fma(e2[k], ey, e1[k]), e0[k]));
+        const double e = exp2_fp64(fma(ey, fma(e2[k], ey, e1[k]), e0[k]), h[k], h_lo[k]);
+        comp[k] = fma(wn[k], e, wn_lo[k] * e);
         tot += comp[k];
       }
-      const double t = tot > 0.0 ? quotient(wts[p], tot) : 0.0;
+      if (!(tot > 0.0)) continue;
+      const double t = quotient(wts[p], tot);
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const double r = tot > 0.0 ? comp[k] * t : 0.0, ry = r * dy;
+        const double r = comp[k] * t, ry = r * dy;
         s0[k] += r;
         s1[k] += ry;
         s2[k] = fma(ry, dy, s2[k]);
