@@ -454,78 +454,71 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
     if (!valid) Tm = cE = cV = TEE = TEV = 0;
     tsum += (double)Tm;
     town += own ? (double)Tm : 0.0;
-    // z-derivatives of f1 (zero outside mu) and of d
-    T g1z[6], dz[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      g1z[j] = j < 2 ? o.g1[j] : (T)0;
-      dz[j] = fma(L0, o.g0[j], -(L1 * g1z[j]));
-    }
-    // the (z, z) block: with E_zz = w0 L0 h0 + w1 L1 h1 and
-    //   V_zz = 2 (k0 (g0 g0^T + f0 h0) + k1 (g1 g1^T + f1 h1) + w01 (dz dz^T + d (L0 h0 - L1 h1))),
-    // c_E E_zz + c_V V_zz = rho0 h0 + rho1 h1 + 2 c_V (k0 g0 g0^T + k1 g1 g1^T + w01 dz dz^T),
-    // rho0 = c_E w0 L0 + 2 c_V (k0 f0 + w01 L0 d), rho1 = c_E w1 L1 + 2 c_V (k1 f1 - w01 L1 d)
-    // (g1 and h1 vanish outside the centre coordinates z < 2)
+    // The z-derivatives of E_s and V_s are the vectors g0 and g1 (g1 and h1 vanish outside the
+    // centre coordinates z < 2) with weights fixed per pixel, and so is everything built of
+    // them:
+    //   E_z = al0 g0 + al1 g1,  V_z = be0 g0 + be1 g1,  d_z = L0 g0 - L1 g1,
+    //   al_i = w_i L_i,  be0 = 2 (k0 f0 + w01 d L0),  be1 = 2 (k1 f1 - w01 d L1).
+    // T_EE E_u E_v + T_EV (E_u V_v + V_u E_v) = E_u a_v + c_u E_v with a = T_EE E + T_EV V,
+    // c = T_EV V; a_z = A0 g0 + A1 g1, c_z = C0 g0 + C1 g1.
     const T cV2 = (T)2 * cV;
-    const T rho0 = fma(cE, w0 * L0, cV2 * fma(k0, f0, w01 * L0 * d));
-    const T rho1 = fma(cE, w1 * L1, cV2 * fma(k1, f1, -w01 * L1 * d));
-    T ag[6], cd[6], bg[2];
+    const T ea0 = e0 * a0, ea1 = e1 * a1, w01d = w01 * d;
+    const T al0 = w0 * L0, al1 = w1 * L1;
+    const T be0 = (T)2 * fma(k0, f0, w01d * L0), be1 = (T)2 * fma(k1, f1, -(w01d * L1));
+    const T A0 = fma(TEE, al0, TEV * be0), A1 = fma(TEE, al1, TEV * be1), C0 = TEV * be0, C1 = TEV * be1;
+    // the (z, z) block: with E_zz = w0 L0 h0 + w1 L1 h1 and
+    //   V_zz = 2 (k0 (g0 g0^T + f0 h0) + k1 (g1 g1^T + f1 h1) + w01 (d_z d_z^T + d (L0 h0 - L1 h1))),
+    // c_E E_zz + c_V V_zz = rho0 h0 + rho1 h1 + 2 c_V (k0 g0 g0^T + k1 g1 g1^T + w01 d_z d_z^T),
+    // rho_i = c_E al_i + c_V be_i; altogether
+    //   rho0 h0 + rho1 h1 + s00 g0 g0^T + s01 (g0 g1^T + g1 g0^T) + s11 g1 g1^T
+    const T rho0 = fma(cE, al0, cV * be0), rho1 = fma(cE, al1, cV * be1);
+    const T s00 = fma(cV2, fma(w01 * L0, L0, k0), al0 * (A0 + C0));
+    const T s11 = fma(cV2, fma(w01 * L1, L1, k1), al1 * (A1 + C1));
+    const T s01 = fma(-cV2, w01 * L0 * L1, fma(C0, al1, al0 * A1));
+    T Pz[6], Rz[2];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      ag[j] = cV2 * k0 * o.g0[j];
-      cd[j] = cV2 * w01 * dz[j];
+    for (int i = 0; i < 6; ++i) Pz[i] = s00 * o.g0[i];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      Pz[i] = fma(s01, o.g1[i], Pz[i]);
+      Rz[i] = fma(s01, o.g0[i], s11 * o.g1[i]);
     }
-    bg[0] = cV2 * k1 * g1z[0];
-    bg[1] = cV2 * k1 * g1z[1];
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
 #pragma unroll
       for (int j = i; j < 6; ++j) {
         T q = Q[qidx(5 + i, 5 + j)];
         q = fma(rho0, o.h0[zidx(i, j)], q);
+        q = fma(Pz[i], o.g0[j], q);
         if (i < 2 && j < 2) {
           q = fma(rho1, o.h1[i + j], q);
-          q = fma(bg[i], g1z[j], q);
+          q = fma(Rz[i], o.g1[j], q);
         }
-        q = fma(ag[i], o.g0[j], q);
-        q = fma(cd[i], dz[j], q);
         Q[qidx(5 + i, 5 + j)] = q;
       }
     }
-    T Eu[kPrim], Vu[kPrim];
-    Eu[0] = -d;
-    Eu[1] = w0 * f0;
-    Eu[2] = w1 * f1;
-    Eu[3] = 0;
-    Eu[4] = 0;
-    const T ea0 = e0 * a0, ea1 = e1 * a1, w01d = w01 * d;
-    Vu[0] = fma(oma2 * d, d, fma(ea1, a1, -(ea0 * a0)));
-    Vu[1] = (T)2 * fma(w0 * ea0, f0, w01d * f0);
-    Vu[2] = (T)2 * fma(w1 * ea1, f1, -(w01d * f1));
-    Vu[3] = w0 * a0 * a0;
-    Vu[4] = w1 * a1 * a1;
+    // the amplitude coordinates u < 5 (E_u vanishes in the two variances u = 3, 4)
+    const T Eu[3] = {-d, w0 * f0, w1 * f1};
+    const T Vu[5] = {fma(oma2 * d, d, fma(ea1, a1, -(ea0 * a0))), (T)2 * fma(w0 * ea0, f0, w01d * f0),
+                     (T)2 * fma(w1 * ea1, f1, -(w01d * f1)), w0 * a0 * a0, w1 * a1 * a1};
+    T av[5], cu[5];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      Eu[5 + j] = fma(w0 * L0, o.g0[j], w1 * L1 * g1z[j]);
-      Vu[5 + j] = (T)2 * fma(k0 * f0, o.g0[j], fma(k1 * f1, g1z[j], w01d * dz[j]));
-    }
-    // T_EE E_u E_v + T_EV (E_u V_v + V_u E_v) = E_u a_v + c_u E_v with a = T_EE E + T_EV V,
-    // c = T_EV V
-    T av[kPrim], cu[kPrim];
-#pragma unroll
-    for (int u = 0; u < kPrim; ++u) {
-      G[u] = fma(cE, Eu[u], fma(cV, Vu[u], G[u]));
-      av[u] = fma(TEE, Eu[u], TEV * Vu[u]);
+    for (int u = 0; u < 5; ++u) {
+      G[u] = fma(cV, Vu[u], G[u]);
       cu[u] = TEV * Vu[u];
+      av[u] = cu[u];
+      if (u < 3) {
+        G[u] = fma(cE, Eu[u], G[u]);
+        av[u] = fma(TEE, Eu[u], cu[u]);
+      }
     }
 #pragma unroll
-    for (int u = 0; u < kPrim; ++u) {
+    for (int u = 0; u < 5; ++u) {
 #pragma unroll
-      for (int v = u; v < kPrim; ++v) {
-        // E_u vanishes in the two amplitude-variance coordinates (u = 3, 4)
+      for (int v = u; v < 5; ++v) {
         T q = Q[qidx(u, v)];
-        if (v != 3 && v != 4) q = fma(cu[u], Eu[v], q);
-        if (u != 3 && u != 4) q = fma(Eu[u], av[v], q);
+        if (v < 3) q = fma(cu[u], Eu[v], q);
+        if (u < 3) q = fma(Eu[u], av[v], q);
         Q[qidx(u, v)] = q;
       }
     }
@@ -544,30 +537,41 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
     add(1, 3, cV2, w0 * a0 * f0);
     add(2, 2, cV2, fma(w1, e1, w01) * f11);
     add(2, 4, cV2, w1 * a1 * f1);
-    // the (amplitude, z) pairs are linear in g0, g1 and dz with weights fixed per pixel:
-    //   Q[0][z] += c_E (-dz) + c_V (-2 L0^2 e0 f0 g0 + 2 L1^2 e1 f1 g1 + 2 (1 - 2a) d dz)
-    //   Q[1][z] += c_E w0 g0 + c_V (4 w0 L0 e0 f0 g0 + 2 w01 (f0 dz + d g0))
-    //   Q[2][z] += c_E w1 g1 + c_V (4 w1 L1 e1 f1 g1 - 2 w01 (f1 dz + d g1))
-    //   Q[3][z] += c_V 2 w0 L0^2 f0 g0,  Q[4][z] += c_V 2 w1 L1^2 f1 g1
-    const T p0 = -(cV2 * L0 * ea0), b0 = cV2 * L1 * ea1, c0 = fma(cV2 * oma2, d, -cE);
-    const T p1 = fma(cE, w0, cV2 * fma((T)2 * w0, ea0, w01d)), c1 = cV2 * w01 * f0;
-    const T b2 = fma(cE, w1, cV2 * fma((T)2 * w1, ea1, -w01d)), c2 = -(cV2 * w01 * f1);
-    const T a3 = cV2 * w0 * L0 * a0, b4 = cV2 * w1 * L1 * a1;
+    // the (amplitude, z) pairs: E_u a_z + c_u E_z and the second derivatives
+    //   c_E (-d_z) + c_V (-2 L0^2 e0 f0 g0 + 2 L1^2 e1 f1 g1 + 2 (1 - 2a) d d_z)      (u = 0)
+    //   c_E w0 g0 + c_V (4 w0 L0 e0 f0 g0 + 2 w01 (f0 d_z + d g0))                    (u = 1)
+    //   c_E w1 g1 + c_V (4 w1 L1 e1 f1 g1 - 2 w01 (f1 d_z + d g1))                    (u = 2)
+    //   c_V 2 w0 L0^2 f0 g0 (u = 3),  c_V 2 w1 L1^2 f1 g1 (u = 4)
+    // as t0 g0 + t1 g1
+    const T c0 = fma(cV2 * oma2, d, -cE), c1 = cV2 * w01 * f0, c2 = -(cV2 * w01 * f1);
+    T t0[5], t1[5];
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+      t0[u] = cu[u] * al0;
+      t1[u] = cu[u] * al1;
+      if (u < 3) {
+        t0[u] = fma(Eu[u], A0, t0[u]);
+        t1[u] = fma(Eu[u], A1, t1[u]);
+      }
+    }
+    t0[0] += fma(c0, L0, -(cV2 * L0 * ea0));
+    t1[0] += fma(-c0, L1, cV2 * L1 * ea1);
+    t0[1] += fma(c1, L0, fma(cE, w0, cV2 * fma((T)2 * w0, ea0, w01d)));
+    t1[1] = fma(-c1, L1, t1[1]);
+    t0[2] = fma(c2, L0, t0[2]);
+    t1[2] += fma(-c2, L1, fma(cE, w1, cV2 * fma((T)2 * w1, ea1, -w01d)));
+    t0[3] = fma(cV2, al0 * a0, t0[3]);
+    t1[4] = fma(cV2, al1 * a1, t1[4]);
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-      const T g0j = o.g0[j], dzj = dz[j];
-      T q0 = fma(p0, g0j, fma(c0, dzj, Q[qidx(0, 5 + j)]));
-      T q1 = fma(p1, g0j, fma(c1, dzj, Q[qidx(1, 5 + j)]));
-      T q2 = fma(c2, dzj, Q[qidx(2, 5 + j)]);
-      if (j < 2) {
-        q0 = fma(b0, g1z[j], q0);
-        q2 = fma(b2, g1z[j], q2);
-        Q[qidx(4, 5 + j)] = fma(b4, g1z[j], Q[qidx(4, 5 + j)]);
+      G[5 + j] = fma(rho0, o.g0[j], G[5 + j]);
+      if (j < 2) G[5 + j] = fma(rho1, o.g1[j], G[5 + j]);
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        T q = fma(t0[u], o.g0[j], Q[qidx(u, 5 + j)]);
+        if (j < 2) q = fma(t1[u], o.g1[j], q);
+        Q[qidx(u, 5 + j)] = q;
       }
-      Q[qidx(0, 5 + j)] = q0;
-      Q[qidx(1, 5 + j)] = q1;
-      Q[qidx(2, 5 + j)] = q2;
-      Q[qidx(3, 5 + j)] = fma(a3, g0j, Q[qidx(3, 5 + j)]);
     }
     if constexpr (W > 1) {
 #pragma unroll
