@@ -338,11 +338,9 @@ struct HessArgs {
 // table; the records are now formed once per item in LDS): Hessians of 200 sources (3.7e6
 // active pixels) 397 -> 304 us per call, a Newton step of 339 sources 964 -> 775 us.
 //
-// W = 1: one wavefront per work item.  W = kHessWaves: that many per item, a pass of 64 pixels
-// each, for launches whose items leave the chip idle; as in the pixel kernel they add to the
+// W = 1: one wavefront per work item.  W > 1: that many per item, a pass of 64 pixels each, for launches whose items leave the chip idle; as in the pixel kernel they add to the
 // item's per-lane sums in turn, in the order of one wavefront, and the products are written
 // out fused, so that an item's sums do not depend on the launch's size.
-constexpr int kHessWaves = 8;
 template <typename T, int NEXP, int NDEV, int W>
 __global__ __launch_bounds__(64 * W)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void k_hess(HessArgs a) {
@@ -1584,15 +1582,20 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   ha.hslots = p->d_hslots;
   ha.active = active;
   ha.img_npsf = p->d_npsf;
-  // kHessWaves wavefronts per item while the items are at most two per compute unit: 115 items
-  // 74 us with one, 25 with eight; 260 items 66 / 37; 1885 items 72 / 150.  (Not the double
-  // form, whose sums alone fill a wavefront's registers.)
-  constexpr int kHessWideItems = 512;
+  // Wavefronts per item by the launch's items, measured with 1 / 4 / 8 (us): 420 items 67 / 33 /
+  // 38, 920 items 75 / 49 / 70, 1820 items 83 / 81 / 126, 3425 items 115 / 134 / 232; 115 items
+  // 74 / - / 24.  (Not the double form, whose sums alone fill a wavefront's registers.)
   const bool std_prof = p->nexp == 6 && p->ndev == 8;
   if constexpr (sizeof(T) == 4) {
-    if (n_items <= kHessWideItems) {
-      if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, kHessWaves>), dim3(n_items), dim3(64 * kHessWaves), 0, sm, ha);
-      else hipLaunchKernelGGL((k_hess<T, 8, 8, kHessWaves>), dim3(n_items), dim3(64 * kHessWaves), 0, sm, ha);
+    constexpr int kItems8 = 256, kItems4 = 1536;
+    if (n_items <= kItems8) {
+      if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, 8>), dim3(n_items), dim3(64 * 8), 0, sm, ha);
+      else hipLaunchKernelGGL((k_hess<T, 8, 8, 8>), dim3(n_items), dim3(64 * 8), 0, sm, ha);
+      return hipGetLastError();
+    }
+    if (n_items <= kItems4) {
+      if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, 4>), dim3(n_items), dim3(64 * 4), 0, sm, ha);
+      else hipLaunchKernelGGL((k_hess<T, 8, 8, 4>), dim3(n_items), dim3(64 * 4), 0, sm, ha);
       return hipGetLastError();
     }
   }

@@ -155,21 +155,23 @@ def test_footprint_bounds_the_plan_allocation(opts, variants, fp64):
 @pytest.mark.parametrize("opts", [dict(), dict(chunk_pixels=64), dict(chunk_pixels=1088), dict(pixels_per_lane=1),
                                   dict(pixels_per_lane=4, map_pixels_per_lane=2), dict(pixel_fp64=True)])
 def test_small_launch_equals_large(opts):
-    """A few sources alone (launches that give a work item several wavefronts) and among many
-    (one wavefront per item): objective, gradient, Hessian and Newton step bit for bit."""
+    """A few sources alone and among more (launches that give a work item several wavefronts)
+    and among many (one wavefront per item): objective, gradient, Hessian and Newton step bit
+    for bit."""
     say(f"case: small launch vs large, {opts}")
     from paper_1803_00113_amd import api
-    probs = [gen.crop_patches(gen.config5_request(4001, n_sources=3), 75), gen.config5_request(4002, n_sources=200)]
-    merged = serve.merge(probs)
-    merged.pixels = np.concatenate([p.pixels for p in probs])
+    small, mid, large = (gen.config5_request(4001 + i, n_sources=m) for i, m in enumerate((3, 25, 200)))
+    small = gen.crop_patches(small, 75)
     ctx = api.Context(0, **opts)
-    n, res = probs[0].n_sources, []
-    for prob, theta in ((probs[0], probs[0].theta0), (merged, np.vstack([p.theta0 for p in probs]))):
+    n, res = small.n_sources, []
+    for probs in ([small], [small, mid], [small, large]):
+        prob, theta = serve.merge(probs), np.vstack([p.theta0 for p in probs])
+        prob.pixels = np.concatenate([p.pixels for p in probs])
         plan = api.Plan(ctx, prob)
         out = [t[:n] for t in api.elbo_eval(plan, theta)[1:] + api.elbo_grad(plan, theta)[1:] + api.elbo_hessian(plan, theta)]
         th = torch.as_tensor(theta, device="cuda").contiguous()
         r = torch.ones(plan.S, dtype=torch.float64, device="cuda")
         st, loc = api.newton_step(plan, th, r, plan.colours == plan.colours[0])
         res.append(out + [th[:n], r[:n], st[:n], torch.nan_to_num(loc[:n])])
-    for x, y in zip(*res):
-        assert torch.equal(x, y)
+    for x, y, z in zip(*res):
+        assert torch.equal(x, y) and torch.equal(x, z)
