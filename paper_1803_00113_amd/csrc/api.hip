@@ -462,7 +462,7 @@ cel_status ensure_newton(cel_plan* p) {
   // (the per-source pixel counts and colours were uploaded with the plan)
   if ((st = track(p, &p->d_theta_trial, S1 * kThetaN)) || (st = track(p, &p->d_pred, S1)) ||
       (st = track(p, &p->d_step_norm, S1)) || (st = track(p, &p->d_trial_active, S1)) ||
-      (st = track(p, &p->d_mask, S1)) || (st = track(p, &p->d_counter, 1)) ||
+      (st = track(p, &p->d_mask, S1)) || (st = track(p, &p->d_cur, S1)) || (st = track(p, &p->d_counter, 1)) ||
       (st = track(p, &p->d_hslots, T1 * 80)) ||
       (st = track(p, &p->d_step_src, S1)) || (st = track(p, &p->d_step_patches, P1)) ||
       (st = track(p, &p->d_step_tasks, T1)) ||
@@ -978,7 +978,7 @@ static hipError_t launch_maps_t(cel_plan* p, const Table<T>* tables, hipStream_t
 template <typename T>
 static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* theta_trial, int v0, int nv,
                                bool grad, int cls, const uint8_t* active, hipStream_t sm, bool prep_base,
-                               double* local_out, double* grad_out) {
+                               double* local_out, double* grad_out, const uint8_t* cur = nullptr) {
   Table<T>* tables = reinterpret_cast<Table<T>*>(sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f);
   hipError_t e = hipSuccess;
   PrepArgs pa;
@@ -1016,6 +1016,7 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   const int vstart = (v0 == 0 && prep_base) ? 1 : 0;   // variant 0 already prepared
   if (nv - vstart > 0) {
     pa.variant0 = v0 + vstart;
+    pa.cur = cur;
     const int np = cls >= 0 ? (int)p->class_patches[cls].size() : p->P;
     e = launch_prep_tables<T>(pa, np, nv - vstart, sm);
     if (e != hipSuccess) return e;
@@ -1038,6 +1039,7 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   fa.active = active;
   fa.variant0 = v0;
   fa.img_npsf = p->d_npsf;
+  fa.cur = cur;
   // (the difference Hessian's iterate is evaluated by the gradient pass: its trial the same way)
   const FusedMode mode = grad ? kGradient : theta_trial && !p->opt.hessian_fd ? kTrial : kObjective;
   e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, mode, n_items, nv, sm);
@@ -1171,40 +1173,13 @@ hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64
   return fp64 ? prep_base_t<double>(p, theta, sm, stepped) : prep_base_t<float>(p, theta, sm, stepped);
 }
 
-template <typename T>
-static hipError_t prep_class_t(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm) {
-  const int np = (int)p->class_patches[cls].size();
-  if (np == 0) return hipSuccess;
-  PrepArgs pa;
-  std::memset(&pa, 0, sizeof(pa));
-  pa.theta = theta;
-  pa.fd_step = p->opt.fd_step;
-  pa.patch_list = p->d_class_patches[cls];
-  pa.patches = p->d_patches;
-  pa.images = p->d_images;
-  pa.prof = p->d_prof;
-  pa.tables = sizeof(T) == 8 ? (void*)p->tables_d : (void*)p->tables_f;
-  pa.n_patches = p->P;
-  pa.active = active;
-  pa.trial_variant = p->trial_variant;
-  pa.fd = p->fd_mode;
-  pa.sky_min = p->d_skymin;
-  pa.patch_psf = p->d_patch_psf;
-  pa.records = p->opt.map_pixels_per_lane == -1 ? kRecRuns : 0;
-  return launch_prep_tables<T>(pa, np, 1, sm);
-}
-
-hipError_t prep_class(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm, bool fp64) {
-  return fp64 ? prep_class_t<double>(p, theta, cls, active, sm) : prep_class_t<float>(p, theta, cls, active, sm);
-}
-
 hipError_t eval_any(cel_plan* p, const double* theta, const double* theta_trial, int v0, int nv, bool grad, int cls,
                     const uint8_t* active, hipStream_t sm, bool prep_base, bool fp64, double* local_out,
-                    double* grad_out) {
+                    double* grad_out, const uint8_t* cur) {
   return fp64 ? enqueue_eval<double>(p, theta, theta_trial, v0, nv, grad, cls, active, sm, prep_base, local_out,
-                                     grad_out)
+                                     grad_out, cur)
               : enqueue_eval<float>(p, theta, theta_trial, v0, nv, grad, cls, active, sm, prep_base, local_out,
-                                    grad_out);
+                                    grad_out, cur);
 }
 
 }  // namespace celmi

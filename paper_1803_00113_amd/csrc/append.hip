@@ -81,7 +81,7 @@ cel_status drop_scratch(Growth& g) {
   p->pt_cap = 0;
   if (p->newton_ready) {
     for (void* b : {(void*)p->d_theta_trial, (void*)p->d_pred, (void*)p->d_step_norm, (void*)p->d_trial_active,
-                    (void*)p->d_mask, (void*)p->d_counter, (void*)p->d_hslots, (void*)p->d_step_src,
+                    (void*)p->d_mask, (void*)p->d_cur, (void*)p->d_counter, (void*)p->d_hslots, (void*)p->d_step_src,
                     (void*)p->d_step_patches, (void*)p->d_step_tasks, (void*)p->d_hess})
       g.old_blocks.push_back(b);
     p->newton_ready = false;

@@ -123,6 +123,8 @@ struct FusedArgs {
   const uint8_t* active;       // per source (nullptr = all)
   int32_t variant0;            // variant index of blockIdx.y == 0
   const int32_t* img_npsf;     // PSF components per image
+  const uint8_t* cur;          // per source: the variant holding its iterate's tables; its own here is
+                               // the other (nullptr = blockIdx.y's variant)
   double unscale[2];           // set by the launcher: 1/c and 1/c^2 for the centre and covariance sums
 };
 

@@ -25,6 +25,8 @@ struct PrepArgs {
   int32_t records;             // extra table records: kRecRuns (rq), kRecUsedType
   const uint8_t* active_v;     // per (launch variant, source), row stride active_v_stride (null = all)
   int64_t active_v_stride;
+  const uint8_t* cur;          // per source: the variant holding its iterate's tables; written here is the
+                               // other (null = the launch's variant)
 };
 constexpr int kRecRuns = 2;
 constexpr int kRecUsedType = 4;   // no records of a type of weight exactly 0 (point candidates)

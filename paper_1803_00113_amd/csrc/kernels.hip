@@ -66,7 +66,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   const cel_image& im = a.images[P.img];
   double th[kThetaN];
   load_theta(a.theta, a.theta_trial, a.theta_vstride, P.src, v, a.fd_step, th, a.trial_variant, a.fd);
-  Table<T>* tb = reinterpret_cast<Table<T>*>(a.tables) + (int64_t)v * a.n_patches + pi_;
+  const int vt = a.cur ? 1 - uniform_byte(a.cur, P.src) : v;
+  Table<T>* tb = reinterpret_cast<Table<T>*>(a.tables) + (int64_t)vt * a.n_patches + pi_;
   const int lane = threadIdx.x;
   // position in patch-local pixel coordinates: mu = A u + b - (x0, y0)
   const double mux = im.A[0][0] * th[0] + im.A[0][1] * th[1] + im.b[0] - P.x0;
@@ -567,7 +568,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
   const DTask task = a.tasks[t];
   const DPatch P = a.patches[task.patch];
   if (a.active && !a.active[P.src]) return;
-  const Table<T>* __restrict__ tb = a.own + (int64_t)v * a.variant_stride + task.patch;
+  const int vt = a.cur ? 1 - uniform_byte(a.cur, P.src) : v;
+  const Table<T>* __restrict__ tb = a.own + (int64_t)vt * a.variant_stride + task.patch;
   const int K = a.img_npsf[P.img];
   const int lane = threadIdx.x & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   // the galaxy components' records of this patch, staged in LDS once per work item

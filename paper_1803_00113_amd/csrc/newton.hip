@@ -328,6 +328,8 @@ struct HessArgs {
   double* hslots;              // [n_tasks][kHSlots]
   const uint8_t* active;
   const int32_t* img_npsf;
+  const uint8_t* cur;          // per source: the variant holding its tables (null = 0)
+  int64_t variant_stride;
 };
 
 // The float form is held to at most 168 VGPRs, three wavefronts per SIMD (its live set fits
@@ -350,7 +352,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
   const DTask task = a.tasks[t];
   const DPatch P = a.patches[task.patch];
   if (a.active && !a.active[P.src]) return;
-  const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.tables) + task.patch;
+  const Table<T>* __restrict__ tb = reinterpret_cast<const Table<T>*>(a.tables) +
+                                    (a.cur ? uniform_byte(a.cur, P.src) * a.variant_stride : 0) + task.patch;
   const int K = a.img_npsf[P.img];
   const int lane = threadIdx.x & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   // the galaxy components' records, one component per lane
@@ -1490,6 +1493,7 @@ struct AcceptArgs {
   int32_t* status;
   double* out_local;          // may be null
   double eta, radius_max;
+  uint8_t* cur;               // an accepted source's tables are its trial's (may be null)
 };
 
 // 32 lanes per source, one of its parameters each (one thread per source copied them one
@@ -1528,6 +1532,7 @@ __global__ __launch_bounds__(256) void k_accept(AcceptArgs a) {
     if (k == 0) {
       a.radius[s] = r;
       a.status[s] = st;
+      if (a.cur && st == CEL_ST_ACCEPTED) a.cur[s] ^= 1;
     }
   } else if (a.clear_done && k == 0) {
     a.active[s] = 0;   // converged or non-finite: done for this colour class
@@ -1543,14 +1548,17 @@ __global__ __launch_bounds__(256) void k_skipped(const uint8_t* __restrict__ mas
   if (out_local) out_local[s] = __longlong_as_double(0x7ff8000000000000LL);
 }
 
-// fills: radius <- r0 for all sources; active <- (colour == c) for one class
+// fills: radius <- r0 for all sources; active <- (colour == c) for one class, its tables in
+// variant 0
 __global__ __launch_bounds__(256) void k_fill_radius(double* radius, int S, double r0) {
   const int s = blockIdx.x * 256 + threadIdx.x;
   if (s < S) radius[s] = r0;
 }
-__global__ __launch_bounds__(256) void k_set_active(uint8_t* active, const int32_t* __restrict__ colour, int S, int c) {
+__global__ __launch_bounds__(256) void k_set_active(uint8_t* active, uint8_t* cur, const int32_t* __restrict__ colour, int S, int c) {
   const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s < S) active[s] = colour[s] == c ? 1 : 0;
+  if (s >= S) return;
+  active[s] = colour[s] == c ? 1 : 0;
+  cur[s] = 0;
 }
 __global__ __launch_bounds__(256) void k_count_active(const uint8_t* __restrict__ active, const int32_t* __restrict__ list,
                                                       int n, int32_t* out) {
@@ -1568,7 +1576,7 @@ __global__ __launch_bounds__(256) void k_count_active(const uint8_t* __restrict_
 
 template <typename T>
 static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, const uint8_t* active,
-                                hipStream_t sm) {
+                                const uint8_t* cur, hipStream_t sm) {
   if (n_items <= 0) return hipSuccess;
   HessArgs ha;
   std::memset(&ha, 0, sizeof(ha));
@@ -1582,6 +1590,8 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   ha.hslots = p->d_hslots;
   ha.active = active;
   ha.img_npsf = p->d_npsf;
+  ha.cur = cur;
+  ha.variant_stride = p->P;
   // Wavefronts per item by the launch's items, measured with 1 / 4 / 8 (us): 420 items 67 / 33 /
   // 38, 920 items 75 / 49 / 70, 1820 items 83 / 81 / 126, 3425 items 115 / 134 / 232; 115 items
   // 74 / - / 24.  (Not the double form, whose sums alone fill a wavefront's registers.)
@@ -1608,10 +1618,11 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
 // gradients and local objectives.  The base tables and maps must be current.
 static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_t* order, int n_items,
                                   const int32_t* srcs, int n_src, const uint8_t* active, double* local,
-                                  double* grad, double* hess, hipStream_t sm) {
+                                  double* grad, double* hess, hipStream_t sm,
+                                  const uint8_t* cur = nullptr) {
   const bool fp64 = p->opt.pixel_fp64 || p->opt.hessian_fp64;
-  hipError_t e = fp64 ? launch_hess_t<double>(p, order, n_items, active, sm)
-                      : launch_hess_t<float>(p, order, n_items, active, sm);
+  hipError_t e = fp64 ? launch_hess_t<double>(p, order, n_items, active, cur, sm)
+                      : launch_hess_t<float>(p, order, n_items, active, cur, sm);
   if (e != hipSuccess || n_src <= 0) return e;
   HessFinArgs fa;
   std::memset(&fa, 0, sizeof(fa));
@@ -1633,10 +1644,12 @@ static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_
   return hipGetLastError();
 }
 
-// What of the iterate's tables and neighbour moment maps a Newton iteration finds made: the
-// maps (none of the class's neighbours has moved since they were made: the sweep refreshes
-// them once per class), so that only the class's own tables are rebuilt; or both.
-enum class Made { kNothing, kMaps, kAll };
+// What of the iterate's tables and neighbour moment maps a Newton iteration finds made: all of
+// them, in variant 0; or, in a sweep, the maps (none of the class's neighbours has moved since
+// they were made: once per class) and each stepped source's tables in the variant that d_cur
+// names -- the trial's tables go to its other variant, and an accepted trial's are the next
+// iterate's, which spares an iteration the rebuild (8 us of a small class's 110).
+enum class Made { kNothing, kSweep, kAll };
 
 // One Newton iteration of colour class `cls` on the sources flagged in `active`; with
 // mark_skipped (all flagged sources are the class's) the others get the skipped status.
@@ -1647,15 +1660,14 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   const int nsrc = (int)p->class_src[cls].size();
   if (nsrc == 0) return hipSuccess;
   hipError_t e;
+  uint8_t* cur = made == Made::kSweep ? p->d_cur : nullptr;
   const bool analytic = !p->opt.hessian_fd;
   if (analytic) {
     // tables (and maps) at the iterate, then the exact Hessians with the gradients
-    e = made == Made::kAll    ? hipSuccess
-        : made == Made::kMaps ? prep_class(p, theta, cls, active, sm, fp64)
-                              : prep_base(p, theta, sm, fp64);
+    e = made == Made::kNothing ? prep_base(p, theta, sm, fp64) : hipSuccess;
     if (e == hipSuccess)
       e = enqueue_hessian(p, theta, p->d_class_tasks[cls], (int)p->class_tasks[cls].size(), p->d_class_src[cls], nsrc,
-                          active, p->v_local, p->v_grad, p->d_hess, sm);
+                          active, p->v_local, p->v_grad, p->d_hess, sm, cur);
   } else {
     // gradients at the iterate and at the 54 central-difference points, then the Hessians
     e = eval_any(p, theta, nullptr, 0, 2 * kParamN + 1, true, cls, active, sm, true, fp64);
@@ -1699,7 +1711,8 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   hipLaunchKernelGGL(k_trsolve, dim3(nsrc), dim3(64 * kTrWaves), 0, sm, ta);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // objective at the trial points
-  e = eval_any(p, theta, p->d_theta_trial, p->trial_variant, 1, false, cls, p->d_trial_active, sm, false, fp64);
+  e = eval_any(p, theta, p->d_theta_trial, p->trial_variant, 1, false, cls, p->d_trial_active, sm, false, fp64, nullptr,
+               nullptr, cur);
   if (e != hipSuccess) return e;
   AcceptArgs aa;
   std::memset(&aa, 0, sizeof(aa));
@@ -1720,6 +1733,7 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   aa.out_local = out_local;
   aa.eta = p->opt.eta;
   aa.radius_max = p->opt.radius_max;
+  aa.cur = cur;
   hipLaunchKernelGGL(k_accept, dim3((aa.n_jobs + 7) / 8), dim3(256), 0, sm, aa);
   return hipGetLastError();
 }
@@ -1821,7 +1835,7 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
   hipError_t e = hipSuccess;
   const int S = p->S;
   if (S > 0 && o.start_colour == 0) {   // a fresh pass: every status starts as skipped
-    hipLaunchKernelGGL(k_set_active, dim3((S + 255) / 256), dim3(256), 0, sm, p->d_mask, p->d_colour, S, -1);
+    hipLaunchKernelGGL(k_set_active, dim3((S + 255) / 256), dim3(256), 0, sm, p->d_mask, p->d_cur, p->d_colour, S, -1);
     e = hipGetLastError();
     if (e == hipSuccess)
       hipLaunchKernelGGL(k_skipped, dim3((S + 255) / 256), dim3(256), 0, sm, p->d_mask, S, status, nullptr);
@@ -1848,7 +1862,7 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
       }
       ++classes;
       const int nsrc = (int)p->class_src[c].size();
-      hipLaunchKernelGGL(k_set_active, dim3((S + 255) / 256), dim3(256), 0, sm, p->d_mask, p->d_colour, S, c);
+      hipLaunchKernelGGL(k_set_active, dim3((S + 255) / 256), dim3(256), 0, sm, p->d_mask, p->d_cur, p->d_colour, S, c);
       if ((e = hipGetLastError()) != hipSuccess) break;
       // the neighbours of this class keep their parameters during its iterations: their
       // moment maps are made once here (analytic Hessian path)
@@ -1866,7 +1880,7 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
           e = hipStreamBeginCapture(sm, hipStreamCaptureModeThreadLocal);
           if (e != hipSuccess) break;
           hipError_t e2 = enqueue_newton_class(p, theta, radius, p->d_mask, c, status, nullptr, true, sm,
-                                                maps_once ? Made::kMaps : Made::kNothing);
+                                                maps_once ? Made::kSweep : Made::kNothing);
           e = hipStreamEndCapture(sm, &graph);
           if (e2 != hipSuccess) e = e2;
           if (e != hipSuccess) break;
@@ -1883,7 +1897,7 @@ extern "C" cel_status cel_sweep(cel_ctx* ctx, const cel_plan* cplan, double* the
       for (int it = 0; it < o.max_newton_iters && e == hipSuccess; ++it) {
         if (exec) e = hipGraphLaunch(exec, sm);
         else e = enqueue_newton_class(p, theta, radius, p->d_mask, c, status, nullptr, true, sm,
-                                                maps_once ? Made::kMaps : Made::kNothing);
+                                                maps_once ? Made::kSweep : Made::kNothing);
         ++steps;
         if (e != hipSuccess) break;
         if ((it + 1) % check_every == 0 || it + 1 == o.max_newton_iters) {

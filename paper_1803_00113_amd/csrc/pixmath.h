@@ -203,6 +203,12 @@ __device__ __forceinline__ double wave_sums(const U* v, int lane) {
   }
 }
 
+// flags[i] for a wavefront-uniform i, known to be uniform (bytes come by vector loads, and a
+// pointer formed from one would make every load through it a vector load too)
+__device__ __forceinline__ int uniform_byte(const uint8_t* flags, int i) {
+  return __builtin_amdgcn_readfirstlane((int)flags[i]);
+}
+
 // the lane that wave_sums leaves holding the sum of value q (the lowest such lane)
 template <int M, int O = 32>
 __host__ __device__ constexpr int wave_sums_lane(int q) {

@@ -103,6 +103,7 @@ struct cel_plan {
   int32_t* d_colour = nullptr;
   uint8_t* d_trial_active = nullptr;
   uint8_t* d_mask = nullptr;
+  uint8_t* d_cur = nullptr;        // per source: which of its two table variants is its iterate's (sweeps)
   int32_t* d_counter = nullptr;
   uint8_t* h_mask = nullptr;      // pinned
   int32_t* h_lists = nullptr;     // pinned, S + P + n_tasks entries
@@ -167,19 +168,17 @@ cel_status plan_alloc(cel_plan* p, size_t bytes, void** ptr);
 // give a block the plan owns back to the context (no work may still use it)
 void plan_untrack(cel_plan* p, void* ptr);
 // (local_out / grad_out: where variant 0's local objectives and gradients go when nv == 1;
-// null = the plan's per-variant arrays)
+// null = the plan's per-variant arrays; cur: the trial's tables go to the variant that does not
+// hold its iterate's)
 hipError_t eval_any(cel_plan* p, const double* theta, const double* theta_trial, int v0, int nv, bool grad, int cls,
                     const uint8_t* active, hipStream_t sm, bool prep_base, bool fp64, double* local_out = nullptr,
-                    double* grad_out = nullptr);
+                    double* grad_out = nullptr, const uint8_t* cur = nullptr);
 hipError_t plain_eval(cel_plan* p, const double* theta, hipStream_t sm, bool fp64);
 // component tables at the iterate for every patch and the neighbour moment maps; stepped: per
 // source, the pairwise non-overlapping sources about to be stepped (device, null = none),
 // whose maps no one reads: a third of the map pass for the largest colour class of the
 // 1000-source batch (107 / 81 us)
 hipError_t prep_base(cel_plan* p, const double* theta, hipStream_t sm, bool fp64, const uint8_t* stepped = nullptr);
-// component tables at the iterate for the patches of colour class cls only (sources flagged
-// in active); the maps are left as they are
-hipError_t prep_class(cel_plan* p, const double* theta, int cls, const uint8_t* active, hipStream_t sm, bool fp64);
 // record a phase boundary event (k = 0..4) of the current evaluation when timing is on
 void phase_mark(cel_plan* p, int k, hipStream_t sm);
 cel_status ensure_newton(cel_plan* p);

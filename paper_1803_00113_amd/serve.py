@@ -87,7 +87,7 @@ def footprint_bytes(prob, variants=VARIANTS_EXACT, fp64=False, chunk=CHUNK):
     # Newton steps
     tables = _al(P * TABLE_F) + (_al(variants * P * TABLE_D) if fp64 else _al(variants * P * TABLE_F))
     sums = sum(_al(nv * T * 128) + 2 * _al(nv * S * 8) + _al(nv * S * 256) for nv in (1, variants))
-    newton = (_al(S * 256) + 2 * _al(S * 8) + 2 * _al(S) + 256 + _al(T * 640) + _al(S * 4) + _al(P * 4)
+    newton = (_al(S * 256) + 2 * _al(S * 8) + 3 * _al(S) + 256 + _al(T * 640) + _al(S * 4) + _al(P * 4)
               + _al(T * 4) + _al(S * 5832))
     return pack + pixels + tables + sums + newton + SLACK
 
