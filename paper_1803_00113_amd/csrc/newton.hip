@@ -1114,13 +1114,14 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
 // psi(lam) = 1/|p(lam)| increasing, concave and nearly linear right of the pole, the Newton
 // points of psi = 1/radius lie left of the root (Nocedal & Wright, Algorithm 4.3) and the
 // secant through a point on either side right of it: together they bracket it ever more
-// tightly, and the next multipliers are both of them and two points between.  What this
+// tightly.  The next multipliers are both of them, the cubic lam(psi) through the two points'
+// values and slopes, and a point in the bracket's larger part.  What this
 // cannot certify -- no root (the hard case), or a step that lies along directions of almost
 // no gradient, where the hard case's rule decides -- goes to the eigen-decomposition below.
 // A point with |p| within 1e-7 of the radius is moved onto the boundary along dp/dlam.
-// One factorisation and its solves take 7 us (2400 issue slots, a third of them lane reads);
-// three to five rounds for most sources.  The eigen-decomposition alone, one wavefront:
-// 113 us for 3 sources, 131 us for 339; this: 43 us and 84 us.
+// One factorisation and its solves take 6-7 us (2200 issue slots, a third of them lane
+// reads); three to five rounds for most sources.  The eigen-decomposition alone, one
+// wavefront: 113 us for 3 sources, 131 us for 339; this: 33 us and 70 us.
 //
 // Eigen-decomposition (first wavefront): one-sided (Hestenes) Jacobi on
 // W = B + c I, c = 1.001 |B|_F (positive definite, so its singular vectors are B's
@@ -1130,7 +1131,7 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
 // -- exchange columns with one shuffle per entry, and orthogonalise each pair by the
 // rotation that diagonalises its 2x2 Gram block.  Sweeps stop when a whole sweep finds
 // every pair orthogonal to 1e-15; then lambda_k = |w_k| - c and v_k = w_k / |w_k|.
-constexpr int kTrWaves = 4;
+constexpr int kTrWaves = 4;   // (the four multipliers of a round)
 constexpr int kTrRounds = 40;
 
 __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
@@ -1198,7 +1199,8 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
     double lo = wave_max(dia), hi = 1.001 * (gnorm / radius + wave_max(low));
     // bracket: lo not right of the root, hi not left of it, near and far the best Newton and
     // secant points; the closest points of each side with known norms (0: none)
-    double near = lo, far = hi, ll = 0.0, nl = 0.0, nr = 0.0;
+    // and Newton points
+    double near = lo, far = hi, ll = 0.0, nl = 0.0, tl = 0.0, nr = 0.0, tr = 0.0;
     // the first multipliers: 0 (unless the diagonal rules it out) and fractions of |g| / radius
     const bool zero = lo == 0.0;
     double lam = wave == 0 && zero ? 0.0 : lo + ldexp(gnorm / radius, 2 * wave - 2 * kTrWaves + 2);
@@ -1226,12 +1228,14 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
           if (lw <= hi) {
             hi = lw;
             nr = nw;
+            tr = rs[w][1];
           }
         } else {
           lo = fmax(lo, lw);
           if (nw >= 0.0 && lw >= ll) {
             ll = lw;
             nl = nw;
+            tl = rs[w][1];
           }
         }
         if (nw >= 0.0) {
@@ -1246,9 +1250,12 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
       if (winner < 0 && ibest >= 0 && best <= 1e-7 * radius) winner = ibest;
       near = fmax(near, lo);
       far = fmin(far, hi);
+      double mid = 0.0;   // the cubic's value at psi = 1 / radius; t: its place between the points
       if (nl > 0.0 && nr > 0.0) {
-        const double pl = 1.0 / nl, pr = 1.0 / nr;
-        far = fmin(far, ll + (1.0 / radius - pl) / (pr - pl) * (hi - ll));
+        const double pl = 1.0 / nl, pr = 1.0 / nr, t = (1.0 / radius - pl) / (pr - pl), u = 1.0 - t;
+        far = fmin(far, ll + t * (hi - ll));
+        // slopes dlam/dt by the Newton points, (tl - ll) / t and (hi - tr) / u
+        mid = u * u * ((1.0 + 2.0 * t) * ll + (tl - ll)) + t * t * ((3.0 - 2.0 * t) * hi - (hi - tr));
       }
       if (winner < 0 && !(far - near > 4.0 * DBL_EPSILON * far)) {
         if (!(hi - lo > 4.0 * DBL_EPSILON * hi)) break;   // bracket closed
@@ -1277,12 +1284,15 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
         if (ok && go && lane < kThetaN)
           a.theta_trial[(int64_t)s * kThetaN + lane] = a.theta[(int64_t)s * kThetaN + lane] + (lane < kN ? p : 0.0);
       }
-      if (nl > 0.0 && nr > 0.0 && near > lo)
-        lam = wave == 0 ? near : wave == 1 ? far : near + (far - near) * ((wave - 1) / (double)(kTrWaves - 1));
-      else if (nr > 0.0)   // nothing positive definite left of the root yet
+      if (nl > 0.0 && nr > 0.0 && near > lo) {
+        const double third = (far - near) / 3.0, half = near + 1.5 * third;
+        if (!(mid > near && mid < far)) mid = half;
+        lam = wave == 0 ? near : wave == 1 ? far : wave == 2 ? mid : mid < half ? far - third : near + third;
+      } else if (nr > 0.0) {   // nothing positive definite left of the root yet
         lam = near + (far - near) * ldexp(1.0, -2 * wave - 1);
-      else                 // nothing right of it
+      } else {                 // nothing right of it
         lam = fmin(fmax(near, 1e-9 * far) * ldexp(1.0, 2 * wave + 1), far);
+      }
     }
     __syncthreads();
     if (winner >= 0 && outcome != 3) return;
