@@ -88,13 +88,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   double ex[14];
 #pragma unroll
   for (int l = 0; l < 14; ++l) ex[l] = read_lane(eval, l);
-  double sig[3];
-  galaxy_cov(th[23], ex[10], ex[12], sig);
+  // (a star candidate's galaxy records are not read: neither its shape nor they are formed)
+  const bool galaxy = !(a.records & kRecUsedType) || 1.0 - ex[11] != 0.0;
   // pixel-frame galaxy covariance S = A Sigma A^T
-  const double a00 = im.A[0][0], a01 = im.A[0][1], a10 = im.A[1][0], a11 = im.A[1][1];
-  const double t00 = a00 * sig[0] + a01 * sig[1], t01 = a00 * sig[1] + a01 * sig[2];
-  const double t10 = a10 * sig[0] + a11 * sig[1], t11 = a10 * sig[1] + a11 * sig[2];
-  const double Sxx = t00 * a00 + t01 * a01, Sxy = t00 * a10 + t01 * a11, Syy = t10 * a10 + t11 * a11;
+  double Sxx = 0.0, Sxy = 0.0, Syy = 0.0;
+  if (galaxy) {
+    double sig[3];
+    galaxy_cov(th[23], ex[10], ex[12], sig);
+    const double a00 = im.A[0][0], a01 = im.A[0][1], a10 = im.A[1][0], a11 = im.A[1][1];
+    const double t00 = a00 * sig[0] + a01 * sig[1], t01 = a00 * sig[1] + a01 * sig[2];
+    const double t10 = a10 * sig[0] + a11 * sig[1], t11 = a10 * sig[1] + a11 * sig[2];
+    Sxx = t00 * a00 + t01 * a01;
+    Sxy = t00 * a10 + t01 * a11;
+    Syy = t10 * a10 + t11 * a11;
+  }
   const int K = im.n_psf;
   // the PSF mixture of this patch: its own where the PSF varies over the image
   const double(*psf)[6] = a.patch_psf ? reinterpret_cast<const double(*)[6]>(a.patch_psf + (int64_t)pi_ * kMaxPsf * 6)
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     tb->hdr[11] = (T)muy;
   }
   // components: K star slots then K x 16 galaxy slots, one per lane (K <= 3: one pass)
-  const int n_slots = (a.records & kRecUsedType) && w[0] == 0.0 ? K : K + K * 2 * kMaxProf;
+  const int n_slots = galaxy ? K + K * 2 * kMaxProf : K;
   for (int c = lane; c < n_slots; c += 64) {
     // a star slot (c < K) or a galaxy slot: the same 2x2 algebra, one code path
     const bool star = c < K;
