@@ -12,12 +12,10 @@ namespace celmi {
 
 // 2^x in FP64: x = n + f with n the nearest integer, 2^f = 1 + f g(f) with g the polynomial
 // of degree 10 interpolating (2^f - 1) / f at the Chebyshev nodes of [-1/2, 1/2] (relative
-// error 8e-18; 0.8 ulp with the evaluation's rounding), scaled by 2^n.  0 below 2^-1100
-// (-infinity included), NaN stays NaN; x must not exceed 2^31.  About 18 operations against
-// the library's 26.
-constexpr double kExp2Magic = 6755399441055744.0;   // 1.5 * 2^52: x + it holds n in the low bits
-// 2^f 2^n for |f| <= 1/2, n in the low bits of t
-__device__ __forceinline__ double exp2_reduced(double f, double t) {
+// error 8e-18; 0.8 ulp with the evaluation's rounding), scaled by 2^n (n saturates as an
+// integer: overflow to infinity, underflow to 0).  0 at -infinity; infinity or NaN at
+// +infinity; NaN stays NaN.  About 18 operations against the library's 26.
+__device__ __forceinline__ double exp2_reduced(double f, double n) {
   double r = 4.4549605981865186e-10;
   r = fma(f, r, 7.072585949269223e-09);
   r = fma(f, r, 1.0178062445845774e-07);
@@ -29,17 +27,15 @@ __device__ __forceinline__ double exp2_reduced(double f, double t) {
   r = fma(f, r, 5.55041086648216e-02);
   r = fma(f, r, 2.4022650695910097e-01);
   r = fma(f, r, 6.931471805599453e-01);
-  return __builtin_amdgcn_ldexp(fma(f, r, 1.0), __double2loint(t));
+  return __builtin_amdgcn_ldexp(fma(f, r, 1.0), (int)n);
 }
 __device__ __forceinline__ double exp2_fp64(double x) {
-  const double t = x + kExp2Magic;
-  const double r = exp2_reduced(x - (t - kExp2Magic), t);
+  const double n = rint(x), r = exp2_reduced(x - n, n);
   return x < -1100.0 ? 0.0 : r;
 }
 // 2^(q h) for a factor h = hi + lo: no rounding of the product or of h
 __device__ __forceinline__ double exp2_fp64(double q, double hi, double lo) {
-  const double t = fma(q, hi, kExp2Magic);
-  const double r = exp2_reduced(fma(q, lo, fma(q, hi, -(t - kExp2Magic))), t);
+  const double n = rint(q * hi), r = exp2_reduced(fma(q, lo, fma(q, hi, -n)), n);
   return q * hi < -1100.0 ? 0.0 : r;
 }
 
