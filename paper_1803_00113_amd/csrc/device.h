@@ -36,7 +36,6 @@ enum Slot {
 // hdr: L0, L1, w0, w1, k0, k1, w01, pi  (E_s = w0 L0 f0 + w1 L1 f1,
 //      V_s = k0 f0^2 + k1 f1^2 + w01 (L0 f0 - L1 f1)^2, f0 = pi f_dev + (1 - pi) f_exp)
 // star[k]: mean_x, mean_y, P_xx, P_xy, P_yy, log2 weight (weight includes the normaliser)
-// gal[k][j]: P_xx, P_xy, P_yy, log2 weight  (j < n_exp: exponential, then de Vaucouleurs)
 // rc2s[k], rc2[k][j]: squared distance from the component's centre beyond which flux times
 // density stays below 2^-30 (float tables) or 2^-60 (double) of the patch's smallest sky
 // value (bounded through the covariance's largest eigenvalue); -1 = negligible everywhere
@@ -44,6 +43,7 @@ enum Slot {
 // hdr[10..11]: the source centre mu in patch-local pixels
 // sq[k], gq[k][j]: (-log2(e)/2 (P_xx, P_xy, P_yy), log2 weight) -- the exponent of a
 //   component at offset d from its centre is q0 dx^2 + q1 (2 dx dy) + q2 dy^2 + q3
+//   (j < n_exp: exponential profile, then de Vaucouleurs)
 //   (values-only evaluation: neighbour maps, Hessian)
 // rq[k][0], rq[k][1 + j]: exp(-P_xx) of the star and of galaxy component j = 2^(2 q0), the
 //   factor by which the ratio of a component's values at consecutive columns changes

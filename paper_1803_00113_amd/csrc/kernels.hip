@@ -5,9 +5,11 @@
 //                  stored in the pixel precision) -- light kernels of Section 2.1.2
 //                  (equation hsi) convolved with the image PSF (Section 2.2.3), flux
 //                  moments of equation conditional
+//   k_maps         per run of a patch's overlap box: the source's moments E_s, V_s, read by
+//                  its neighbours
 //   k_fused        per work item (a run of <= chunk pixels of one patch): for every pixel
 //                  the own source's mixture value and partial derivatives, every
-//                  overlapping neighbour's value, E_q[lambda] and V_q[lambda] (equations
+//                  overlapping neighbour's moments, E_q[lambda] and V_q[lambda] (equations
 //                  conditional, vareq), the delta-method pixel term (equation
 //                  eq:log_p_last, Section 4.2.2) and its adjoint coefficients; FP64 sums
 //                  reduced across the wavefront into one slot row per work item

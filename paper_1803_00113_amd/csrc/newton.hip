@@ -1,17 +1,19 @@
 // Trust-region Newton block step and block coordinate ascent (Sections 4.3-4.4).
 //
 // One Newton iteration on a set of pairwise non-overlapping sources (a colour class):
-//   1. component tables of every source at the current iterate (variant 0), and of each
-//      stepped source at theta +/- h e_k for the 27 parameters (variants 1..54)
-//   2. the fused pixel kernel and finalisation for those 55 variants: L_s and gradients
-//   3. k_trsolve, one wavefront per source: the Hessian -- its pixel part by central
-//      differences of the pixel gradient (symmetrised), its KL part analytically, since the
-//      tight colour-prior mixture makes the KL's higher derivatives far too large for
-//      differencing -- convergence tests, eigen-decomposition of -H by cyclic
-//      Jacobi in LDS (FP64), the trust-region subproblem (boundary multiplier by
-//      bisection on |p(lambda)| = radius, hard case along the lowest eigenvector), and
-//      the trial point
-//   4. the objective at the trial points (variant 55)
+//   1. component tables of the stepped sources at the current iterate (in a sweep an accepted
+//      trial's tables are kept for it)
+//   2. the objective, gradient and exact Hessian: k_hess per work item, k_hess_finalize per
+//      source.  On request instead the Hessian's pixel part by central differences of the
+//      pixel gradient (variants 1..54 at theta +/- h e_k, k_fd_hessian), its KL part
+//      analytically, since the tight colour-prior mixture makes the KL's higher derivatives
+//      far too large for differencing
+//   3. k_trsolve, kTrWaves wavefronts per source: convergence tests and the trust-region
+//      subproblem in FP64, its multiplier by L D L^T factorisations of B + lambda I for
+//      several lambda at a time; where none gives the step (the hard case) the
+//      eigen-decomposition of B = -H by one-sided Jacobi and the secular equation; the
+//      trial point
+//   4. the objective at the trial points (last variant)
 //   5. k_accept: ratio of actual to predicted gain, acceptance and radius update
 // Trust-region constants (the paper prints none): accept if rho > eta (0.1); radius
 // shrinks to |p|/4 if rho < 1/4 and doubles (to at most radius_max) if rho > 3/4 with the
@@ -340,9 +342,10 @@ struct HessArgs {
 // table; the records are now formed once per item in LDS): Hessians of 200 sources (3.7e6
 // active pixels) 397 -> 304 us per call, a Newton step of 339 sources 964 -> 775 us.
 //
-// W = 1: one wavefront per work item.  W > 1: that many per item, a pass of 64 pixels each, for launches whose items leave the chip idle; as in the pixel kernel they add to the
-// item's per-lane sums in turn, in the order of one wavefront, and the products are written
-// out fused, so that an item's sums do not depend on the launch's size.
+// W = 1: one wavefront per work item.  W > 1: that many per item, a pass of 64 pixels each,
+// for launches whose items leave the chip idle; as in the pixel kernel they add to the item's
+// per-lane sums in turn, in the order of one wavefront, and the products are written out
+// fused, so that an item's sums do not depend on the launch's size.
 template <typename T, int NEXP, int NDEV, int W>
 __global__ __launch_bounds__(64 * W)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void k_hess(HessArgs a) {
