@@ -62,14 +62,12 @@ __device__ __forceinline__ double block_sum(const double (&v)[L], double (*red)[
   return t;
 }
 
-// s / tot for s >= 0 and tot > 0: the hardware reciprocal with two Newton steps; a quotient
-// whose reciprocal could leave the normal range is divided out.
-__device__ __forceinline__ double quotient(double s, double tot) {
-  if (tot < 1e-290) return s / tot;
-  double y = __builtin_amdgcn_rcp(tot);
-  y = fma(fma(-tot, y, 1.0), y, y);
-  y = fma(fma(-tot, y, 1.0), y, y);
-  return s * y;
+// 1 / x for x in the range whose reciprocal is a normal number: the hardware's approximation
+// with two Newton steps.
+__device__ __forceinline__ double reciprocal(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
 }
 
 template <int K>
@@ -201,7 +199,15 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fit(PsfFitArgs a) {
         tot += comp[k];
       }
       if (!(tot > 0.0)) continue;
-      const double t = quotient(wts[p], tot);
+      // the responsibilities comp / tot (at most 1) times the knot's weight, by one quotient
+      // weight / tot wherever that is far from the largest number (or tot from the smallest)
+      const double s = wts[p];
+      double t = s * reciprocal(tot);
+      if (tot < 1e-290 || t > 1e300) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) comp[k] = comp[k] / tot * s;
+        t = 1.0;
+      }
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         const double r = comp[k] * t, ry = r * dy;

@@ -160,3 +160,26 @@ def test_psf_fit_grid_sizes(side, K):
         img = OP.psf_image(eig[0], coef[0], size[0, 0], size[0, 1], xy[f, 0], xy[f, 1])
         assert _scale_err(out[f, :K], OP.fit_mixture(img, K, 6)).max() <= 1e-9
         assert np.all(out[f, K:] == 0)
+
+
+@pytest.mark.parametrize("K,sigma,scale", [(1, 0.655, 1.0), (1, 0.66, 1e6), (1, 0.67, 1e12), (2, 0.565, 1.0),
+                                           (2, 0.575, 1e12)])
+def test_psf_fit_far_knot_of_tiny_density(K, sigma, scale):
+    """A PSF narrower than the knots' spacing with light in one far knot, where the mixture's
+    density is near the smallest numbers (1e-320 to 1e-303, below the knot's weight over the
+    largest number): the knot's responsibilities are at most 1 and the fit is the oracle's
+    (float64 on both sides: 1e-9)."""
+    say(f"case: psf fit, far knot, K={K} sigma={sigma} scale={scale:g}")
+    side, n_iter = 51, 5
+    dx, dy = OP.knot_offsets(side)
+    img = np.exp(-0.5 * (dx ** 2 + dy ** 2) / sigma ** 2)
+    img[img < 1e-20] = 0.0
+    img[side // 2, side - 1] = 1e-7
+    img *= scale
+    coef = np.zeros((1, 1, 6))
+    coef[0, 0, 0] = 1.0
+    out = api.psf_fit_at(api.Context(0), img[None, None], coef, np.array([[100.0, 100.0]]), np.zeros(1, np.int32),
+                         np.array([[50.0, 50.0]]), K, n_iter).cpu().numpy()
+    want = OP.fit_mixture(img, K, n_iter)
+    say(f"  {out[0, :K]}")
+    assert np.all(np.isfinite(want)) and _scale_err(out[0, :K], want).max() <= 1e-9
