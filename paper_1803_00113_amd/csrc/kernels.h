@@ -59,11 +59,8 @@ struct FinalizeArgs {
 
 template <typename T>
 hipError_t launch_prep_tables(const PrepArgs& a, int n_patches_launch, int n_variants, hipStream_t st);
-// What the pixel kernel forms: the objective, bit for bit that of kGradient; with the gradient
-// sums; or the objective of a trial point, by the shorter value evaluation.
-enum FusedMode { kObjective = 0, kGradient = 1, kTrial = 2 };
 template <typename T>
-hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, FusedMode mode, int n_items,
+hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool grad, int n_items,
                         int n_variants, hipStream_t st);
 template <typename T>
 hipError_t launch_maps(const MapArgs& a, int nexp, int ndev, int ppl, int n_items, hipStream_t st);

@@ -555,22 +555,17 @@ __global__ __launch_bounds__(64) void k_maps_runs(MapArgs a) {
   }
 }
 
-// MODE kTrial forms the exponents of a trial point from the pixel's monomials (6 issue slots
-// per component and pixel against 9 of kObjective, which takes kGradient's): the objective at
-// the iterate that it is compared with comes from the Hessian kernel either way.  12860 items
-// 76 -> 67 us.
 // W = 1: one wavefront per work item.  W = kFlush: as many wavefronts per item as it has pixel
 // groups between flushes, a group each, for launches whose items leave the chip idle; the
 // wavefronts add to the item's per-lane sums in turn, through LDS, in the order in which one
 // wavefront would, so that an item's sums do not depend on the launch's size.
 constexpr int kFlush = 4;   // pixel groups between flushes of the per-lane sums
-template <typename T, int PPL, int MODE, int NEXP, int NDEV, int W>
+template <typename T, int PPL, bool GRAD, int NEXP, int NDEV, int W>
 __global__ __launch_bounds__(64 * W)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) : 1))) void k_fused(
     FusedArgs<T> a) {
 #pragma clang fp contract(off)
   static_assert(W == 1 || W == kFlush, "a flush after every pass of the workgroup");
-  constexpr bool GRAD = MODE == kGradient;
   const int v = a.variant0 + blockIdx.y;
   const int wi = a.order_offset + xcd_position((int)blockIdx.x, (int)gridDim.x);
   const int t = a.order ? a.order[wi] : wi;
@@ -640,15 +635,11 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
     run_box<int>(base, max(min(base + group_px, task.pix_end), base + 1), P.w, ibox);
     const T box[4] = {(T)ibox[0], (T)ibox[1], (T)ibox[2], (T)ibox[3]};
     if (W == 1) __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
-    if constexpr (MODE == kTrial) {
-      eval_values<T, PPL, NEXP, NDEV>(tb, rec, any ? K : 0, px, py, box, f0, f1);
-    } else {
-      eval_own<T, PPL, NEXP, NDEV, GRAD>(tb, rec, any ? K : 0, px, py, box, o);
+    eval_own<T, PPL, NEXP, NDEV, GRAD>(tb, rec, any ? K : 0, px, py, box, o);
 #pragma unroll
-      for (int i = 0; i < PPL; ++i) {
-        f1[i] = o.f1[i];
-        f0[i] = fma(pi, o.fd[i], ((T)1 - pi) * o.fe[i]);
-      }
+    for (int i = 0; i < PPL; ++i) {
+      f1[i] = o.f1[i];
+      f0[i] = fma(pi, o.fd[i], ((T)1 - pi) * o.fe[i]);
     }
     T E[PPL], V[PPL], d[PPL];
     bool own[PPL];
@@ -1265,7 +1256,7 @@ static bool wide_maps(int64_t n_items) {
   return n_items <= (sizeof(T) == 8 ? 512 : 1024);
 }
 
-template <typename T, int PPL, int MODE>
+template <typename T, int PPL, bool GRAD>
 static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int n_items, int n_var,
                                  hipStream_t st) {
   dim3 grid(n_items, n_var);
@@ -1274,34 +1265,26 @@ static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int 
   k.unscale[1] = 1.0 / (kExpScale * kExpScale);
   const bool wide = wide_pixels<T>((int64_t)n_items * n_var);
   if (nexp == 6 && ndev == 8) {
-    if (wide) hipLaunchKernelGGL((k_fused<T, PPL, MODE, 6, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
-    else hipLaunchKernelGGL((k_fused<T, PPL, MODE, 6, 8, 1>), grid, dim3(64), 0, st, k);
+    if (wide) hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
+    else hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, 1>), grid, dim3(64), 0, st, k);
   } else {
-    if (wide) hipLaunchKernelGGL((k_fused<T, PPL, MODE, 8, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
-    else hipLaunchKernelGGL((k_fused<T, PPL, MODE, 8, 8, 1>), grid, dim3(64), 0, st, k);
+    if (wide) hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 8, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
+    else hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 8, 8, 1>), grid, dim3(64), 0, st, k);
   }
   return hipGetLastError();
 }
 
-template <typename T, int PPL>
-static hipError_t fused_mode(const FusedArgs<T>& a, int nexp, int ndev, FusedMode mode, int n_items, int n_var,
-                             hipStream_t st) {
-  switch (mode) {
-    case kObjective: return fused_dispatch<T, PPL, kObjective>(a, nexp, ndev, n_items, n_var, st);
-    case kGradient: return fused_dispatch<T, PPL, kGradient>(a, nexp, ndev, n_items, n_var, st);
-    case kTrial: return fused_dispatch<T, PPL, kTrial>(a, nexp, ndev, n_items, n_var, st);
-  }
-  return hipErrorInvalidValue;
-}
-
 template <typename T>
-hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, FusedMode mode, int n_items,
+hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool grad, int n_items,
                         int n_variants, hipStream_t st) {
   if (n_items <= 0 || n_variants <= 0) return hipSuccess;
-  switch (ppl) {
-    case 1: return fused_mode<T, 1>(a, nexp, ndev, mode, n_items, n_variants, st);
-    case 2: return fused_mode<T, 2>(a, nexp, ndev, mode, n_items, n_variants, st);
-    case 4: return fused_mode<T, 4>(a, nexp, ndev, mode, n_items, n_variants, st);
+  switch (ppl * 2 + (grad ? 1 : 0)) {
+    case 2: return fused_dispatch<T, 1, false>(a, nexp, ndev, n_items, n_variants, st);
+    case 3: return fused_dispatch<T, 1, true>(a, nexp, ndev, n_items, n_variants, st);
+    case 4: return fused_dispatch<T, 2, false>(a, nexp, ndev, n_items, n_variants, st);
+    case 5: return fused_dispatch<T, 2, true>(a, nexp, ndev, n_items, n_variants, st);
+    case 8: return fused_dispatch<T, 4, false>(a, nexp, ndev, n_items, n_variants, st);
+    case 9: return fused_dispatch<T, 4, true>(a, nexp, ndev, n_items, n_variants, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1518,9 +1501,9 @@ template hipError_t launch_background<float>(const PointArgs<float>&, int, hipSt
 template hipError_t launch_background<double>(const PointArgs<double>&, int, hipStream_t);
 template hipError_t launch_point<float>(const PointArgs<float>&, int, int, int, int, hipStream_t);
 template hipError_t launch_point<double>(const PointArgs<double>&, int, int, int, int, hipStream_t);
-template hipError_t launch_fused<float>(const FusedArgs<float>&, int, int, int, FusedMode, int, int,
+template hipError_t launch_fused<float>(const FusedArgs<float>&, int, int, int, bool, int, int,
                                         hipStream_t);
-template hipError_t launch_fused<double>(const FusedArgs<double>&, int, int, int, FusedMode, int, int,
+template hipError_t launch_fused<double>(const FusedArgs<double>&, int, int, int, bool, int, int,
                                          hipStream_t);
 
 }  // namespace celmi

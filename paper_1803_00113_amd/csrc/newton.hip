@@ -1723,7 +1723,9 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   ta.err = p->d_err;
   hipLaunchKernelGGL(k_trsolve, dim3(nsrc), dim3(64 * kTrWaves), 0, sm, ta);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // objective at the trial points
+  // objective at the trial points, by the objective's own pixel form, so that an accepted source's
+  // L_s is the number that an evaluation at the new iterate gives (exponents from the pixel's
+  // monomials instead: 12860 items 76 -> 67 us, but other last bits)
   e = eval_any(p, theta, p->d_theta_trial, p->trial_variant, 1, false, cls, p->d_trial_active, sm, false, fp64, nullptr,
                nullptr, cur);
   if (e != hipSuccess) return e;

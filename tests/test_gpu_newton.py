@@ -227,3 +227,21 @@ def test_step_hard_case(radius):
             held = 2.0 ** -53 * float(np.abs(g[s, :27]) @ np.abs(th0[s, :27]))
             assert np.linalg.norm(p) <= radius * (1 + 1e-9)
             assert abs(value(p) - value(po)) <= 1e-10 * abs(value(po)) + held
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_step_local_objective_is_the_evaluations(fp64):
+    """elbo_local of an accepted source is L_s at the returned theta, the same number as
+    elbo_eval gives there (bit for bit: no source it overlaps has moved)."""
+    say(f"case: elbo_local of a step against elbo_eval, fp64={fp64}")
+    for prob in (tiny(), gen.crop_patches(gen.subset(gen.config2(n_sources=20), images=[0, 5]), 20)):
+        plan = api.Plan(api.Context(0, pixel_fp64=fp64), prob)
+        for radius in (0.05, 1.0):
+            th = torch.as_tensor(prob.theta0, device="cuda").contiguous().clone()
+            r = torch.full((prob.n_sources,), radius, dtype=torch.float64, device="cuda")
+            st, loc = api.newton_step(plan, th, r, plan.colours == 0)
+            at = api.elbo_eval(plan, th)[1]
+            moved = st == _ffi.ST_ACCEPTED
+            say(f"  S={prob.n_sources} radius {radius}: accepted {int(moved.sum())}, "
+                f"largest difference {float((loc - at)[moved].abs().max()):.3e}")
+            assert int(moved.sum()) > 0 and torch.equal(loc[moved], at[moved])
