@@ -62,8 +62,8 @@ __device__ __forceinline__ double block_sum(const double (&v)[L], double (*red)[
   return t;
 }
 
-// 1 / x for x in the range whose reciprocal is a normal number: the hardware's approximation
-// with two Newton steps.
+// 1 / x: the hardware's approximation with two Newton steps (not a finite number where 1 / x
+// is not).
 __device__ __forceinline__ double reciprocal(double x) {
   double y = __builtin_amdgcn_rcp(x);
   y = fma(fma(-x, y, 1.0), y, y);
@@ -200,10 +200,10 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fit(PsfFitArgs a) {
       }
       if (!(tot > 0.0)) continue;
       // the responsibilities comp / tot (at most 1) times the knot's weight, by one quotient
-      // weight / tot wherever that is far from the largest number (or tot from the smallest)
+      // weight / tot unless that (or 1 / tot) leaves the range
       const double s = wts[p];
       double t = s * reciprocal(tot);
-      if (tot < 1e-290 || t > 1e300) {
+      if (!(t <= 1e300)) {
 #pragma unroll
         for (int k = 0; k < K; ++k) comp[k] = comp[k] / tot * s;
         t = 1.0;
