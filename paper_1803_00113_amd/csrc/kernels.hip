@@ -958,6 +958,7 @@ __global__ __launch_bounds__(128) void k_finalize(FinalizeArgs a) {
     const double* slots = a.slots + (int64_t)vv * a.slot_variant_stride;
     const int pend = a.patch_ptr[s + 1];
     for (int pb = a.patch_ptr[s]; pb < pend; pb += 64) {
+      wave_lds_sync();   // (more than 64 patches: the previous ones' sums have been read)
       // the patches' slot sums over their work items: lane 16 g + q takes slot q of every
       // fourth patch, two patches and four items' loads at a time (one load after another
       // was most of the kernel's time: up to 18 items a patch)

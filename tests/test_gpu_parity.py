@@ -260,3 +260,17 @@ def test_invalid_problems_rejected():
     plan = api.Plan(ctx, prob)
     with pytest.raises(ValueError):
         api.elbo_grad(plan, np.zeros((3, 32)))
+
+
+@pytest.mark.parametrize("epochs", [12, 13, 27])
+def test_sources_of_many_patches(epochs):
+    """Sources of 60, 65 and 135 patches: the finalisation takes a source's patches 64 at a
+    time (below one batch, one patch into the second, and into the third)."""
+    say(f"case: {5 * epochs} patches per source")
+    prob = gen._grouped(f"many_{epochs}", 90 + epochs, 3, 9, 12, epochs, "powerlaw")
+    assert np.bincount(prob.patch_src).max() == 5 * epochs
+    o_tot, o_loc, o_g = E.elbo_total_and_grad(E.Model(prob), prob.theta0)
+    _, tot, loc, g = run(prob)
+    check(prob, tot, loc, g, o_tot, o_loc, o_g)
+    _, tot, loc, g = run(prob, pixel_fp64=True)
+    check(prob, tot, loc, g, o_tot, o_loc, o_g, rtol_e=1e-10, rtol_g=1e-8)
