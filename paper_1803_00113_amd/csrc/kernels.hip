@@ -685,78 +685,81 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
         }
       }
     }
-    if constexpr (W > 1) {   // this wavefront's turn: take over the sums of those before it
-      for (int w = 0; w < wave; ++w) __syncthreads();
-      if (GRAD)
+    // the wavefronts' turns (W = 1: one): each takes over the sums of those before it and hands
+    // them on; every wavefront meets at the barrier after each turn
+    for (int turn = 0; turn < W; ++turn) {
+      if (turn == wave) {
+        if constexpr (W > 1) {
+          if (GRAD)
 #pragma unroll
-        for (int q = 0; q < S_T; ++q) part[q] = wave > 0 ? chain[q][lane] : (T)0;
-      if (wave > 0 || group > 0) {
-        acc_t = chain_t[0][lane];
-        acc_own = chain_t[1][lane];
+            for (int q = 0; q < S_T; ++q) part[q] = wave > 0 ? chain[q][lane] : (T)0;
+          acc_t = wave > 0 || group > 0 ? chain_t[0][lane] : 0.0;
+          acc_own = wave > 0 || group > 0 ? chain_t[1][lane] : 0.0;
+        }
+        // pixel term (centred: the data constant x log x - x - log x! is added per patch in
+        // FP64) and adjoint coefficients
+#pragma unroll
+        for (int i = 0; i < PPL; ++i) {
+          const T x = xv[i];
+          const T invE = frcp<T>(E[i]);
+          const T xr = x * invE * invE;
+          T Tm = fma((T)-0.5 * xr, V[i], (x > (T)0 ? x_log_ratio<T>(x, E[i]) : (T)0) - (E[i] - x));
+          if (!valid[i]) Tm = (T)0;
+          acc_t += (double)Tm;
+          acc_own += own[i] ? (double)Tm : 0.0;
+          if (GRAD) {
+            T cE = fma(xr * invE, V[i], (x - E[i]) * invE);
+            T cV = (T)-0.5 * xr;
+            if (!valid[i]) cE = cV = (T)0;
+            const T cV2 = (T)2 * cV, omp = (T)1 - pi, wd = w01 * d[i];
+            const T rho0 = fma(cE * w0, L0, cV2 * fma(k0, f0[i], wd * L0));
+            const T rho1 = fma(cE * w1, L1, cV2 * fma(k1, f1[i], -(wd * L1)));
+            const T g0x = fma(pi, o.gdx[i], omp * o.gex[i]), g0y = fma(pi, o.gdy[i], omp * o.gey[i]);
+            const T s0xx = fma(pi, o.sdxx[i], omp * o.sexx[i]);
+            const T s0xy = (T)2 * fma(pi, o.sdxy[i], omp * o.sexy[i]);
+            const T s0yy = fma(pi, o.sdyy[i], omp * o.seyy[i]);
+            const T cVf0 = cV * f0[i], cVf1 = cV * f1[i];
+            part[S_CE_F0] = fma(cE, f0[i], part[S_CE_F0]);
+            part[S_CE_F1] = fma(cE, f1[i], part[S_CE_F1]);
+            part[S_CV_F00] = fma(cVf0, f0[i], part[S_CV_F00]);
+            part[S_CV_F11] = fma(cVf1, f1[i], part[S_CV_F11]);
+            part[S_CV_F01] = fma(cVf0, f1[i], part[S_CV_F01]);
+            part[S_MU_X] = fma(rho0, g0x, fma(rho1, o.g1x[i], part[S_MU_X]));
+            part[S_MU_Y] = fma(rho0, g0y, fma(rho1, o.g1y[i], part[S_MU_Y]));
+            part[S_S_XX] = fma(rho0, s0xx, part[S_S_XX]);
+            part[S_S_XY] = fma(rho0, s0xy, part[S_S_XY]);
+            part[S_S_YY] = fma(rho0, s0yy, part[S_S_YY]);
+            part[S_PI] = fma(rho0, o.fd[i] - o.fe[i], part[S_PI]);
+          }
+        }
+        if constexpr (W > 1) {
+          if (GRAD)
+#pragma unroll
+            for (int q = 0; q < S_T; ++q) chain[q][lane] = part[q];
+          chain_t[0][lane] = acc_t;
+          chain_t[1][lane] = acc_own;
+        }
+        // flush: after kFlush groups or the item's last (W > 1: by the last wavefront)
+        if (GRAD && (W > 1 ? wave == W - 1 : group % kFlush == kFlush - 1 || base + step >= task.pix_end)) {
+          const bool first = W > 1 ? group == 0 : group < kFlush;
+          // the 11 wavefront sums together, then lane 0 reads each from the lane holding it and
+          // stores it scaled back (the centre sums carry the records' scale c, the covariance
+          // sums c^2); no per-lane slot index or address lives across the pixel loop
+          const double sq = wave_sums<S_T, 32, T>(part, lane);
+          // (the factors come with the kernel arguments, in scalar registers: no vector registers
+          // hold them across the pixel loop)
+          const double* unscale = a.unscale;
+#pragma unroll
+          for (int q = 0; q < S_T; ++q) {
+            part[q] = (T)0;
+            const double s = read_lane(sq, wave_sums_lane<S_T>(q));
+            const double v = (q == S_MU_X || q == S_MU_Y) ? s * unscale[0]
+                             : (q == S_S_XX || q == S_S_XY || q == S_S_YY) ? s * unscale[1] : s;
+            if (lane == 0) out[q] = first ? v : out[q] + v;
+          }
+        }
       }
-    }
-    // pixel term (centred: the data constant x log x - x - log x! is added per patch in
-    // FP64) and adjoint coefficients
-#pragma unroll
-    for (int i = 0; i < PPL; ++i) {
-      const T x = xv[i];
-      const T invE = frcp<T>(E[i]);
-      const T xr = x * invE * invE;
-      T Tm = fma((T)-0.5 * xr, V[i], (x > (T)0 ? x_log_ratio<T>(x, E[i]) : (T)0) - (E[i] - x));
-      if (!valid[i]) Tm = (T)0;
-      acc_t += (double)Tm;
-      acc_own += own[i] ? (double)Tm : 0.0;
-      if (GRAD) {
-        T cE = fma(xr * invE, V[i], (x - E[i]) * invE);
-        T cV = (T)-0.5 * xr;
-        if (!valid[i]) cE = cV = (T)0;
-        const T cV2 = (T)2 * cV, omp = (T)1 - pi, wd = w01 * d[i];
-        const T rho0 = fma(cE * w0, L0, cV2 * fma(k0, f0[i], wd * L0));
-        const T rho1 = fma(cE * w1, L1, cV2 * fma(k1, f1[i], -(wd * L1)));
-        const T g0x = fma(pi, o.gdx[i], omp * o.gex[i]), g0y = fma(pi, o.gdy[i], omp * o.gey[i]);
-        const T s0xx = fma(pi, o.sdxx[i], omp * o.sexx[i]);
-        const T s0xy = (T)2 * fma(pi, o.sdxy[i], omp * o.sexy[i]);
-        const T s0yy = fma(pi, o.sdyy[i], omp * o.seyy[i]);
-        const T cVf0 = cV * f0[i], cVf1 = cV * f1[i];
-        part[S_CE_F0] = fma(cE, f0[i], part[S_CE_F0]);
-        part[S_CE_F1] = fma(cE, f1[i], part[S_CE_F1]);
-        part[S_CV_F00] = fma(cVf0, f0[i], part[S_CV_F00]);
-        part[S_CV_F11] = fma(cVf1, f1[i], part[S_CV_F11]);
-        part[S_CV_F01] = fma(cVf0, f1[i], part[S_CV_F01]);
-        part[S_MU_X] = fma(rho0, g0x, fma(rho1, o.g1x[i], part[S_MU_X]));
-        part[S_MU_Y] = fma(rho0, g0y, fma(rho1, o.g1y[i], part[S_MU_Y]));
-        part[S_S_XX] = fma(rho0, s0xx, part[S_S_XX]);
-        part[S_S_XY] = fma(rho0, s0xy, part[S_S_XY]);
-        part[S_S_YY] = fma(rho0, s0yy, part[S_S_YY]);
-        part[S_PI] = fma(rho0, o.fd[i] - o.fe[i], part[S_PI]);
-      }
-    }
-    if constexpr (W > 1) {
-      if (GRAD)
-#pragma unroll
-        for (int q = 0; q < S_T; ++q) chain[q][lane] = part[q];
-      chain_t[0][lane] = acc_t;
-      chain_t[1][lane] = acc_own;
-      for (int w = wave; w < W; ++w) __syncthreads();
-    }
-    // flush: after kFlush groups or the item's last (W > 1: by the last wavefront)
-    if (GRAD && (W > 1 ? wave == W - 1 : group % kFlush == kFlush - 1 || base + step >= task.pix_end)) {
-      const bool first = W > 1 ? group == 0 : group < kFlush;
-      // the 11 wavefront sums together, then lane 0 reads each from the lane holding it and
-      // stores it scaled back (the centre sums carry the records' scale c, the covariance
-      // sums c^2); no per-lane slot index or address lives across the pixel loop
-      const double sq = wave_sums<S_T, 32, T>(part, lane);
-      // (the factors come with the kernel arguments, in scalar registers: no vector registers
-      // hold them across the pixel loop)
-      const double* unscale = a.unscale;
-#pragma unroll
-      for (int q = 0; q < S_T; ++q) {
-        part[q] = (T)0;
-        const double s = read_lane(sq, wave_sums_lane<S_T>(q));
-        const double v = (q == S_MU_X || q == S_MU_Y) ? s * unscale[0]
-                         : (q == S_S_XX || q == S_S_XY || q == S_S_YY) ? s * unscale[1] : s;
-        if (lane == 0) out[q] = first ? v : out[q] + v;
-      }
+      if constexpr (W > 1) __syncthreads();
     }
     // next group: advance each lane's coordinates by step pixels
 #pragma unroll
@@ -770,7 +773,11 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
       py[i] = r;
     }
   }
-  if (W > 1 && wave != W - 1) return;
+  if constexpr (W > 1) {
+    if (wave != W - 1) return;
+    acc_t = group > 0 ? chain_t[0][lane] : 0.0;
+    acc_own = group > 0 ? chain_t[1][lane] : 0.0;
+  }
   const double acc[2] = {acc_t, acc_own};
   const double s_t = wave_sums<2>(acc, lane);   // lane 0: the pixel term, lane 32: the owned part
   const int tslot = wave_sums_slot<2>(lane);

@@ -431,160 +431,168 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
         if (Qp.src < P.src) own = false;
       }
     }
-    if constexpr (W > 1) {   // this wavefront's turn: take over the sums of those before it
-      for (int w = 0; w < wave; ++w) __syncthreads();
-      if (wave > 0 || pass > task.pix_begin) {
+    auto add_pixels = [&] {
+      const T f0 = o.f0, f1 = o.f1;
+      const T a0 = L0 * f0, a1 = L1 * f1, d = a0 - a1;
+      const T Es = fma(w0, a0, w1 * a1);
+      const T k0 = w0 * L0 * L0 * e0, k1 = w1 * L1 * L1 * e1;
+      const T Vs = fma(k0 * f0, f0, fma(k1 * f1, f1, w01 * d * d));
+      const T E = Eb + Es, V = Vb + Vs, x = xv;
+      const T invE = frcp<T>(E);
+      const T xr = x * invE * invE;
+      T Tm = fma((T)-0.5 * xr, V, (x > (T)0 ? x_log_ratio<T>(x, E) : (T)0) - (E - x));
+      T cE = fma(xr * invE, V, (x - E) * invE);
+      T cV = (T)-0.5 * xr;
+      T TEE = -fma((T)3 * xr * V * invE, invE, xr);
+      T TEV = xr * invE;
+      if (!valid) Tm = cE = cV = TEE = TEV = 0;
+      tsum += (double)Tm;
+      town += own ? (double)Tm : 0.0;
+      // The z-derivatives of E_s and V_s are the vectors g0 and g1 (g1 and h1 vanish outside the
+      // centre coordinates z < 2) with weights fixed per pixel, and so is everything built of
+      // them:
+      //   E_z = al0 g0 + al1 g1,  V_z = be0 g0 + be1 g1,  d_z = L0 g0 - L1 g1,
+      //   al_i = w_i L_i,  be0 = 2 (k0 f0 + w01 d L0),  be1 = 2 (k1 f1 - w01 d L1).
+      // T_EE E_u E_v + T_EV (E_u V_v + V_u E_v) = E_u a_v + c_u E_v with a = T_EE E + T_EV V,
+      // c = T_EV V; a_z = A0 g0 + A1 g1, c_z = C0 g0 + C1 g1.
+      const T cV2 = (T)2 * cV;
+      const T ea0 = e0 * a0, ea1 = e1 * a1, w01d = w01 * d;
+      const T al0 = w0 * L0, al1 = w1 * L1;
+      const T be0 = (T)2 * fma(k0, f0, w01d * L0), be1 = (T)2 * fma(k1, f1, -(w01d * L1));
+      const T A0 = fma(TEE, al0, TEV * be0), A1 = fma(TEE, al1, TEV * be1), C0 = TEV * be0, C1 = TEV * be1;
+      // the (z, z) block: with E_zz = w0 L0 h0 + w1 L1 h1 and
+      //   V_zz = 2 (k0 (g0 g0^T + f0 h0) + k1 (g1 g1^T + f1 h1) + w01 (d_z d_z^T + d (L0 h0 - L1 h1))),
+      // c_E E_zz + c_V V_zz = rho0 h0 + rho1 h1 + 2 c_V (k0 g0 g0^T + k1 g1 g1^T + w01 d_z d_z^T),
+      // rho_i = c_E al_i + c_V be_i; altogether
+      //   rho0 h0 + rho1 h1 + s00 g0 g0^T + s01 (g0 g1^T + g1 g0^T) + s11 g1 g1^T
+      const T rho0 = fma(cE, al0, cV * be0), rho1 = fma(cE, al1, cV * be1);
+      const T s00 = fma(cV2, fma(w01 * L0, L0, k0), al0 * (A0 + C0));
+      const T s11 = fma(cV2, fma(w01 * L1, L1, k1), al1 * (A1 + C1));
+      const T s01 = fma(-cV2, w01 * L0 * L1, fma(C0, al1, al0 * A1));
+      T Pz[6], Rz[2];
 #pragma unroll
-        for (int u = 0; u < kPrim; ++u) G[u] = chain[u][lane];
+      for (int i = 0; i < 6; ++i) Pz[i] = s00 * o.g0[i];
 #pragma unroll
-        for (int u = 0; u < kHQ; ++u) Q[u] = chain[kPrim + u][lane];
-        tsum = chain_t[0][lane];
-        town = chain_t[1][lane];
+      for (int i = 0; i < 2; ++i) {
+        Pz[i] = fma(s01, o.g1[i], Pz[i]);
+        Rz[i] = fma(s01, o.g0[i], s11 * o.g1[i]);
       }
-    }
-    const T f0 = o.f0, f1 = o.f1;
-    const T a0 = L0 * f0, a1 = L1 * f1, d = a0 - a1;
-    const T Es = fma(w0, a0, w1 * a1);
-    const T k0 = w0 * L0 * L0 * e0, k1 = w1 * L1 * L1 * e1;
-    const T Vs = fma(k0 * f0, f0, fma(k1 * f1, f1, w01 * d * d));
-    const T E = Eb + Es, V = Vb + Vs, x = xv;
-    const T invE = frcp<T>(E);
-    const T xr = x * invE * invE;
-    T Tm = fma((T)-0.5 * xr, V, (x > (T)0 ? x_log_ratio<T>(x, E) : (T)0) - (E - x));
-    T cE = fma(xr * invE, V, (x - E) * invE);
-    T cV = (T)-0.5 * xr;
-    T TEE = -fma((T)3 * xr * V * invE, invE, xr);
-    T TEV = xr * invE;
-    if (!valid) Tm = cE = cV = TEE = TEV = 0;
-    tsum += (double)Tm;
-    town += own ? (double)Tm : 0.0;
-    // The z-derivatives of E_s and V_s are the vectors g0 and g1 (g1 and h1 vanish outside the
-    // centre coordinates z < 2) with weights fixed per pixel, and so is everything built of
-    // them:
-    //   E_z = al0 g0 + al1 g1,  V_z = be0 g0 + be1 g1,  d_z = L0 g0 - L1 g1,
-    //   al_i = w_i L_i,  be0 = 2 (k0 f0 + w01 d L0),  be1 = 2 (k1 f1 - w01 d L1).
-    // T_EE E_u E_v + T_EV (E_u V_v + V_u E_v) = E_u a_v + c_u E_v with a = T_EE E + T_EV V,
-    // c = T_EV V; a_z = A0 g0 + A1 g1, c_z = C0 g0 + C1 g1.
-    const T cV2 = (T)2 * cV;
-    const T ea0 = e0 * a0, ea1 = e1 * a1, w01d = w01 * d;
-    const T al0 = w0 * L0, al1 = w1 * L1;
-    const T be0 = (T)2 * fma(k0, f0, w01d * L0), be1 = (T)2 * fma(k1, f1, -(w01d * L1));
-    const T A0 = fma(TEE, al0, TEV * be0), A1 = fma(TEE, al1, TEV * be1), C0 = TEV * be0, C1 = TEV * be1;
-    // the (z, z) block: with E_zz = w0 L0 h0 + w1 L1 h1 and
-    //   V_zz = 2 (k0 (g0 g0^T + f0 h0) + k1 (g1 g1^T + f1 h1) + w01 (d_z d_z^T + d (L0 h0 - L1 h1))),
-    // c_E E_zz + c_V V_zz = rho0 h0 + rho1 h1 + 2 c_V (k0 g0 g0^T + k1 g1 g1^T + w01 d_z d_z^T),
-    // rho_i = c_E al_i + c_V be_i; altogether
-    //   rho0 h0 + rho1 h1 + s00 g0 g0^T + s01 (g0 g1^T + g1 g0^T) + s11 g1 g1^T
-    const T rho0 = fma(cE, al0, cV * be0), rho1 = fma(cE, al1, cV * be1);
-    const T s00 = fma(cV2, fma(w01 * L0, L0, k0), al0 * (A0 + C0));
-    const T s11 = fma(cV2, fma(w01 * L1, L1, k1), al1 * (A1 + C1));
-    const T s01 = fma(-cV2, w01 * L0 * L1, fma(C0, al1, al0 * A1));
-    T Pz[6], Rz[2];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) Pz[i] = s00 * o.g0[i];
+      for (int i = 0; i < 6; ++i) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      Pz[i] = fma(s01, o.g1[i], Pz[i]);
-      Rz[i] = fma(s01, o.g0[i], s11 * o.g1[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-#pragma unroll
-      for (int j = i; j < 6; ++j) {
-        T q = Q[qidx(5 + i, 5 + j)];
-        q = fma(rho0, o.h0[zidx(i, j)], q);
-        q = fma(Pz[i], o.g0[j], q);
-        if (i < 2 && j < 2) {
-          q = fma(rho1, o.h1[i + j], q);
-          q = fma(Rz[i], o.g1[j], q);
+        for (int j = i; j < 6; ++j) {
+          T q = Q[qidx(5 + i, 5 + j)];
+          q = fma(rho0, o.h0[zidx(i, j)], q);
+          q = fma(Pz[i], o.g0[j], q);
+          if (i < 2 && j < 2) {
+            q = fma(rho1, o.h1[i + j], q);
+            q = fma(Rz[i], o.g1[j], q);
+          }
+          Q[qidx(5 + i, 5 + j)] = q;
         }
-        Q[qidx(5 + i, 5 + j)] = q;
       }
-    }
-    // the amplitude coordinates u < 5 (E_u vanishes in the two variances u = 3, 4)
-    const T Eu[3] = {-d, w0 * f0, w1 * f1};
-    const T Vu[5] = {fma(oma2 * d, d, fma(ea1, a1, -(ea0 * a0))), (T)2 * fma(w0 * ea0, f0, w01d * f0),
-                     (T)2 * fma(w1 * ea1, f1, -(w01d * f1)), w0 * a0 * a0, w1 * a1 * a1};
-    T av[5], cu[5];
-#pragma unroll
-    for (int u = 0; u < 5; ++u) {
-      G[u] = fma(cV, Vu[u], G[u]);
-      cu[u] = TEV * Vu[u];
-      av[u] = cu[u];
-      if (u < 3) {
-        G[u] = fma(cE, Eu[u], G[u]);
-        av[u] = fma(TEE, Eu[u], cu[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 5; ++u) {
-#pragma unroll
-      for (int v = u; v < 5; ++v) {
-        T q = Q[qidx(u, v)];
-        if (v < 3) q = fma(cu[u], Eu[v], q);
-        if (u < 3) q = fma(Eu[u], av[v], q);
-        Q[qidx(u, v)] = q;
-      }
-    }
-    // second derivatives of E_s and V_s
-    auto add = [&](int u, int v, T x, T y) { Q[qidx(u, v)] = fma(x, y, Q[qidx(u, v)]); };
-    const T f00 = f0 * f0, f11 = f1 * f1;
-    add(0, 0, cV2, -(d * d));
-    add(0, 1, cE, -f0);
-    add(0, 1, cV2, fma(oma2 * d, f0, -(ea0 * f0)));
-    add(0, 2, cE, f1);
-    add(0, 2, cV2, fma(-(oma2 * d), f1, ea1 * f1));
-    add(0, 3, cV, -(a0 * a0));
-    add(0, 4, cV, a1 * a1);
-    add(1, 1, cV2, fma(w0, e0, w01) * f00);
-    add(1, 2, cV2, -(w01 * f0 * f1));
-    add(1, 3, cV2, w0 * a0 * f0);
-    add(2, 2, cV2, fma(w1, e1, w01) * f11);
-    add(2, 4, cV2, w1 * a1 * f1);
-    // the (amplitude, z) pairs: E_u a_z + c_u E_z and the second derivatives
-    //   c_E (-d_z) + c_V (-2 L0^2 e0 f0 g0 + 2 L1^2 e1 f1 g1 + 2 (1 - 2a) d d_z)      (u = 0)
-    //   c_E w0 g0 + c_V (4 w0 L0 e0 f0 g0 + 2 w01 (f0 d_z + d g0))                    (u = 1)
-    //   c_E w1 g1 + c_V (4 w1 L1 e1 f1 g1 - 2 w01 (f1 d_z + d g1))                    (u = 2)
-    //   c_V 2 w0 L0^2 f0 g0 (u = 3),  c_V 2 w1 L1^2 f1 g1 (u = 4)
-    // as t0 g0 + t1 g1
-    const T c0 = fma(cV2 * oma2, d, -cE), c1 = cV2 * w01 * f0, c2 = -(cV2 * w01 * f1);
-    T t0[5], t1[5];
-#pragma unroll
-    for (int u = 0; u < 5; ++u) {
-      t0[u] = cu[u] * al0;
-      t1[u] = cu[u] * al1;
-      if (u < 3) {
-        t0[u] = fma(Eu[u], A0, t0[u]);
-        t1[u] = fma(Eu[u], A1, t1[u]);
-      }
-    }
-    t0[0] += fma(c0, L0, -(cV2 * L0 * ea0));
-    t1[0] += fma(-c0, L1, cV2 * L1 * ea1);
-    t0[1] += fma(c1, L0, fma(cE, w0, cV2 * fma((T)2 * w0, ea0, w01d)));
-    t1[1] = fma(-c1, L1, t1[1]);
-    t0[2] = fma(c2, L0, t0[2]);
-    t1[2] += fma(-c2, L1, fma(cE, w1, cV2 * fma((T)2 * w1, ea1, -w01d)));
-    t0[3] = fma(cV2, al0 * a0, t0[3]);
-    t1[4] = fma(cV2, al1 * a1, t1[4]);
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      G[5 + j] = fma(rho0, o.g0[j], G[5 + j]);
-      if (j < 2) G[5 + j] = fma(rho1, o.g1[j], G[5 + j]);
+      // the amplitude coordinates u < 5 (E_u vanishes in the two variances u = 3, 4)
+      const T Eu[3] = {-d, w0 * f0, w1 * f1};
+      const T Vu[5] = {fma(oma2 * d, d, fma(ea1, a1, -(ea0 * a0))), (T)2 * fma(w0 * ea0, f0, w01d * f0),
+                       (T)2 * fma(w1 * ea1, f1, -(w01d * f1)), w0 * a0 * a0, w1 * a1 * a1};
+      T av[5], cu[5];
 #pragma unroll
       for (int u = 0; u < 5; ++u) {
-        T q = fma(t0[u], o.g0[j], Q[qidx(u, 5 + j)]);
-        if (j < 2) q = fma(t1[u], o.g1[j], q);
-        Q[qidx(u, 5 + j)] = q;
+        G[u] = fma(cV, Vu[u], G[u]);
+        cu[u] = TEV * Vu[u];
+        av[u] = cu[u];
+        if (u < 3) {
+          G[u] = fma(cE, Eu[u], G[u]);
+          av[u] = fma(TEE, Eu[u], cu[u]);
+        }
       }
-    }
-    if constexpr (W > 1) {
 #pragma unroll
-      for (int u = 0; u < kPrim; ++u) chain[u][lane] = G[u];
+      for (int u = 0; u < 5; ++u) {
 #pragma unroll
-      for (int u = 0; u < kHQ; ++u) chain[kPrim + u][lane] = Q[u];
-      chain_t[0][lane] = tsum;
-      chain_t[1][lane] = town;
-      for (int w = wave; w < W; ++w) __syncthreads();
+        for (int v = u; v < 5; ++v) {
+          T q = Q[qidx(u, v)];
+          if (v < 3) q = fma(cu[u], Eu[v], q);
+          if (u < 3) q = fma(Eu[u], av[v], q);
+          Q[qidx(u, v)] = q;
+        }
+      }
+      // second derivatives of E_s and V_s
+      auto add = [&](int u, int v, T x, T y) { Q[qidx(u, v)] = fma(x, y, Q[qidx(u, v)]); };
+      const T f00 = f0 * f0, f11 = f1 * f1;
+      add(0, 0, cV2, -(d * d));
+      add(0, 1, cE, -f0);
+      add(0, 1, cV2, fma(oma2 * d, f0, -(ea0 * f0)));
+      add(0, 2, cE, f1);
+      add(0, 2, cV2, fma(-(oma2 * d), f1, ea1 * f1));
+      add(0, 3, cV, -(a0 * a0));
+      add(0, 4, cV, a1 * a1);
+      add(1, 1, cV2, fma(w0, e0, w01) * f00);
+      add(1, 2, cV2, -(w01 * f0 * f1));
+      add(1, 3, cV2, w0 * a0 * f0);
+      add(2, 2, cV2, fma(w1, e1, w01) * f11);
+      add(2, 4, cV2, w1 * a1 * f1);
+      // the (amplitude, z) pairs: E_u a_z + c_u E_z and the second derivatives
+      //   c_E (-d_z) + c_V (-2 L0^2 e0 f0 g0 + 2 L1^2 e1 f1 g1 + 2 (1 - 2a) d d_z)      (u = 0)
+      //   c_E w0 g0 + c_V (4 w0 L0 e0 f0 g0 + 2 w01 (f0 d_z + d g0))                    (u = 1)
+      //   c_E w1 g1 + c_V (4 w1 L1 e1 f1 g1 - 2 w01 (f1 d_z + d g1))                    (u = 2)
+      //   c_V 2 w0 L0^2 f0 g0 (u = 3),  c_V 2 w1 L1^2 f1 g1 (u = 4)
+      // as t0 g0 + t1 g1
+      const T c0 = fma(cV2 * oma2, d, -cE), c1 = cV2 * w01 * f0, c2 = -(cV2 * w01 * f1);
+      T t0[5], t1[5];
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        t0[u] = cu[u] * al0;
+        t1[u] = cu[u] * al1;
+        if (u < 3) {
+          t0[u] = fma(Eu[u], A0, t0[u]);
+          t1[u] = fma(Eu[u], A1, t1[u]);
+        }
+      }
+      t0[0] += fma(c0, L0, -(cV2 * L0 * ea0));
+      t1[0] += fma(-c0, L1, cV2 * L1 * ea1);
+      t0[1] += fma(c1, L0, fma(cE, w0, cV2 * fma((T)2 * w0, ea0, w01d)));
+      t1[1] = fma(-c1, L1, t1[1]);
+      t0[2] = fma(c2, L0, t0[2]);
+      t1[2] += fma(-c2, L1, fma(cE, w1, cV2 * fma((T)2 * w1, ea1, -w01d)));
+      t0[3] = fma(cV2, al0 * a0, t0[3]);
+      t1[4] = fma(cV2, al1 * a1, t1[4]);
+#pragma unroll
+      for (int j = 0; j < 6; ++j) {
+        G[5 + j] = fma(rho0, o.g0[j], G[5 + j]);
+        if (j < 2) G[5 + j] = fma(rho1, o.g1[j], G[5 + j]);
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+          T q = fma(t0[u], o.g0[j], Q[qidx(u, 5 + j)]);
+          if (j < 2) q = fma(t1[u], o.g1[j], q);
+          Q[qidx(u, 5 + j)] = q;
+        }
+      }
+    };
+    if constexpr (W == 1) {
+      add_pixels();
+    } else {
+      // the wavefronts' turns: each takes over the sums of those before it and hands them on;
+      // every wavefront meets at the barrier after each turn
+      for (int turn = 0; turn < W; ++turn) {
+        if (turn == wave) {
+          if (wave > 0 || pass > task.pix_begin) {
+#pragma unroll
+            for (int u = 0; u < kPrim; ++u) G[u] = chain[u][lane];
+#pragma unroll
+            for (int u = 0; u < kHQ; ++u) Q[u] = chain[kPrim + u][lane];
+            tsum = chain_t[0][lane];
+            town = chain_t[1][lane];
+          }
+          add_pixels();
+#pragma unroll
+          for (int u = 0; u < kPrim; ++u) chain[u][lane] = G[u];
+#pragma unroll
+          for (int u = 0; u < kHQ; ++u) chain[kPrim + u][lane] = Q[u];
+          chain_t[0][lane] = tsum;
+          chain_t[1][lane] = town;
+        }
+        __syncthreads();
+      }
     }
     col += step_cols;
     row += step_rows;
