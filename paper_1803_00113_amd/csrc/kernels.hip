@@ -18,6 +18,7 @@
 //                  kleq, the GMM colour bound and Supplement A) on a second wavefront
 //   k_total        one workgroup: fixed-order sum of the per-source owned objectives
 #include <math.h>
+#include <stddef.h>
 
 #include <type_traits>
 
@@ -215,17 +216,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 // ----------------------------------------------------------------------------------------
 // k_fused: the per-pixel hot loop
 
-// Copy the galaxy components' exponent records of the K PSF components of one table into
-// LDS (THREADS threads; 16-byte vectors).  Each component's record is then one broadcast LDS
-// read rather than a scalar-cache load: the tables of the wavefronts resident on a compute
-// unit exceed its scalar cache.
+// The galaxy components' exponent records of one table in LDS.  Each component's record is then
+// one broadcast LDS read rather than a scalar-cache load: the tables of the wavefronts resident
+// on a compute unit exceed its scalar cache.
+template <typename T>
+struct alignas(sizeof(uint4)) Records {
+  T r[kMaxPsf][2 * kMaxProf][8];
+};
+
+// copy those of the K PSF components (THREADS threads)
 template <typename T, int THREADS = 64>
-__device__ __forceinline__ void stage_records(const Table<T>* __restrict__ tb, int K, int lane,
-                                              T (*rec)[2 * kMaxProf][8]) {
-  constexpr int kVec = 16 / sizeof(T);   // values per 16-byte vector
+__device__ __forceinline__ void stage_records(const Table<T>* __restrict__ tb, int K, int lane, Records<T>& rec) {
+  constexpr int kVec = sizeof(uint4) / sizeof(T);   // values per 16-byte vector
+  static_assert(alignof(Records<T>) % sizeof(uint4) == 0, "the records are written by vectors");
+  static_assert(offsetof(Table<T>, gq) % sizeof(uint4) == 0, "the table's records are read by vectors");
   const int n = K * 2 * kMaxProf * 8 / kVec;
   const uint4* src = reinterpret_cast<const uint4*>(&tb->gq[0][0][0]);
-  uint4* dst = reinterpret_cast<uint4*>(&rec[0][0][0]);
+  uint4* dst = reinterpret_cast<uint4*>(&rec.r[0][0][0]);
   for (int i = lane; i < n; i += THREADS) dst[i] = src[i];
   __syncthreads();
 }
@@ -394,7 +401,7 @@ __global__ __launch_bounds__(64 * W) void k_maps(MapArgs a) {
   const int K = a.img_npsf[P.img];
   const T L0 = tb->hdr[0], L1 = tb->hdr[1], w0 = tb->hdr[2], w1 = tb->hdr[3];
   const T k0 = tb->hdr[4], k1 = tb->hdr[5], w01 = tb->hdr[6];
-  __shared__ T rec[kMaxPsf][2 * kMaxProf][8];
+  __shared__ Records<T> rec;
   stage_records<T, 64 * W>(tb, K, threadIdx.x, rec);
   // box-local coordinates of this thread's pixels, advanced by a carry per group (patch-local:
   // plus the box corner)
@@ -419,7 +426,7 @@ __global__ __launch_bounds__(64 * W) void k_maps(MapArgs a) {
     run_box<int>(base, min(base + step, task.pix_end), bw, ibox);
     const T box[4] = {(T)(ibox[0] + task.x0), (T)(ibox[1] + task.x0), (T)(ibox[2] + task.y0),
                       (T)(ibox[3] + task.y0)};
-    eval_values<T, NP, NEXP, NDEV>(tb, rec, K, px, py, box, f0, f1);
+    eval_values<T, NP, NEXP, NDEV>(tb, rec.r, K, px, py, box, f0, f1);
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       const int idx = base + i * 64 + (int)threadIdx.x;
@@ -577,7 +584,7 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
   const int K = a.img_npsf[P.img];
   const int lane = threadIdx.x & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   // the galaxy components' records of this patch, staged in LDS once per work item
-  __shared__ T rec[kMaxPsf][2 * kMaxProf][8];
+  __shared__ Records<T> rec;
   stage_records<T, 64 * W>(tb, K, threadIdx.x, rec);
   // the per-lane sums on their way from wavefront to wavefront
   __shared__ T chain[W > 1 ? S_T : 1][64];
@@ -635,7 +642,7 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
     run_box<int>(base, max(min(base + group_px, task.pix_end), base + 1), P.w, ibox);
     const T box[4] = {(T)ibox[0], (T)ibox[1], (T)ibox[2], (T)ibox[3]};
     if (W == 1) __builtin_assume(K >= 1);   // images have 1..kMaxPsf PSF components (checked at prepare)
-    eval_own<T, PPL, NEXP, NDEV, GRAD>(tb, rec, any ? K : 0, px, py, box, o);
+    eval_own<T, PPL, NEXP, NDEV, GRAD>(tb, rec.r, any ? K : 0, px, py, box, o);
 #pragma unroll
     for (int i = 0; i < PPL; ++i) {
       f1[i] = o.f1[i];
@@ -836,7 +843,7 @@ __global__ __launch_bounds__(64) void k_point(PointArgs<T> a) {
   const int lane = threadIdx.x;
   const bool galaxy = tb->hdr[2] != (T)0;
   const T flux = galaxy ? tb->hdr[0] : tb->hdr[1];
-  __shared__ T rec[kMaxPsf][2 * kMaxProf][8];
+  __shared__ Records<T> rec;
   if (galaxy) stage_records<T>(tb, K, lane, rec);
   const T2* xs = reinterpret_cast<const T2*>(a.xs) + P.off;
   const T2* bg = reinterpret_cast<const T2*>(a.maps) + P.off;
@@ -865,7 +872,7 @@ __global__ __launch_bounds__(64) void k_point(PointArgs<T> a) {
     run_box<T>(base, min(base + step, task.pix_end), P.w, box);
     if (galaxy) {
       T f1[PPL];
-      eval_values<T, PPL, NEXP, NDEV>(tb, rec, K, px, py, box, f, f1, false);
+      eval_values<T, PPL, NEXP, NDEV>(tb, rec.r, K, px, py, box, f, f1, false);
     } else {
       for (int k = 0; k < K; ++k) {
         const T mx = tb->star[k][0], my = tb->star[k][1];
