@@ -12,9 +12,18 @@ namespace celmi {
 
 // 2^x in FP64: x = n + f with n the nearest integer, 2^f = 1 + f g(f) with g the polynomial
 // of degree 10 interpolating (2^f - 1) / f at the Chebyshev nodes of [-1/2, 1/2] (relative
-// error 8e-18; 0.8 ulp with the evaluation's rounding), scaled by 2^n (n saturates as an
-// integer: overflow to infinity, underflow to 0).  0 at -infinity; infinity or NaN at
-// +infinity; NaN stays NaN.  About 18 operations against the library's 26.
+// error 2.0e-17 with the coefficients as doubles; 0.8 ulp with the evaluation's rounding),
+// scaled by 2^n (n saturates as an integer: overflow to infinity, underflow to 0).  0 at
+// -infinity; infinity or NaN at +infinity; NaN stays NaN.  About 18 operations against the
+// library's 26.
+//
+// The conversion is the instruction's own, which saturates and takes NaN to 0; the language's
+// is undefined beyond the integers, where exponents of narrow components do lie.
+__device__ __forceinline__ int saturated_int(double n) {
+  int i;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(n));
+  return i;
+}
 __device__ __forceinline__ double exp2_reduced(double f, double n) {
   double r = 4.4549605981865186e-10;
   r = fma(f, r, 7.072585949269223e-09);
@@ -27,7 +36,7 @@ __device__ __forceinline__ double exp2_reduced(double f, double n) {
   r = fma(f, r, 5.55041086648216e-02);
   r = fma(f, r, 2.4022650695910097e-01);
   r = fma(f, r, 6.931471805599453e-01);
-  return __builtin_amdgcn_ldexp(fma(f, r, 1.0), (int)n);
+  return __builtin_amdgcn_ldexp(fma(f, r, 1.0), saturated_int(n));
 }
 __device__ __forceinline__ double exp2_fp64(double x) {
   const double n = rint(x), r = exp2_reduced(x - n, n);

@@ -183,3 +183,22 @@ def test_psf_fit_far_knot_of_tiny_density(K, sigma, scale):
     want = OP.fit_mixture(img, K, n_iter)
     say(f"  {out[0, :K]}")
     assert np.all(np.isfinite(want)) and _scale_err(out[0, :K], want).max() <= 1e-9
+
+
+@pytest.mark.parametrize("eps", [1e-8, 1e-11, 1e-20, 1e-30])
+def test_psf_fit_exponents_beyond_the_integers(eps):
+    """A point with the faintest of neighbours: the start's variance is 2 eps, and exponents
+    away from the point go to -1e9 .. -1e32, past the 32- and 64-bit integers; their densities
+    are 0 and the point keeps its mixture (the oracle's: 1e-9)."""
+    say(f"case: psf fit, exponents to {-600 / eps:.0e}")
+    side = 51
+    img = np.zeros((side, side))
+    img[25, 25] = 1.0
+    img[25, 24] = img[25, 26] = img[24, 25] = img[26, 25] = eps
+    coef = np.zeros((1, 1, 6))
+    coef[0, 0, 0] = 1.0
+    for n_iter in (0, 1):
+        out = api.psf_fit_at(api.Context(0), img[None, None], coef, np.array([[100.0, 100.0]]), np.zeros(1, np.int32),
+                             np.array([[50.0, 50.0]]), 2, n_iter).cpu().numpy()
+        want = OP.fit_mixture(img, 2, n_iter)
+        assert np.all(np.isfinite(want)) and _scale_err(out[0, :2], want).max() <= 1e-9
