@@ -31,6 +31,7 @@
 #include "kernels.h"
 #include "pixmath.h"
 #include "plan.h"
+#include "trbracket.h"
 
 namespace celmi {
 
@@ -1033,14 +1034,15 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// (B + lam I) p = g by an unpivoted L D L^T factorisation of one wavefront: lane c < 27 holds
-// column c in registers, a step broadcasts the pivot column by lane reads, and p is p_c in
-// lane c.  Returns false (uniformly) when a pivot is not positive: B + lam I is not positive
-// definite.  Otherwise sums: |p|^2, p . w with w = (B + lam I)^-1 p, and g . p, in every
-// lane, and w itself, like p, where |p| is within 1e-7 of the radius.
+// (B + D) p = g by an unpivoted L D L^T factorisation of one wavefront, D = lam I with a further
+// 1 at decoupled coordinates (`pivot`: this lane's entry): lane c < 27 holds column c in
+// registers, a step broadcasts the pivot column by lane reads, and p is p_c in lane c.  Returns
+// false (uniformly) when a pivot is not positive: B + D is not positive definite.  Otherwise
+// sums: |p|^2, p . w with w = (B + D)^-1 p, and g . p, in every lane, and w itself, like p,
+// where |p| is within 1e-7 of the radius.
 // Unlike an eigen-decomposition, whose errors are relative to |B|, the factorisation keeps
 // the small entries of a badly scaled B (a type logit far from 0) to relative precision.
-__device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, double g_c, double radius, int lane,
+__device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double pivot, double g_c, double radius, int lane,
                                           double& p, double& w, double* sums) {
   // The lane's index, made to look new at every step (`x`: a value formed there): comparisons
   // with it are then made where they are used, where 27 masks held in scalar registers would
@@ -1053,7 +1055,7 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
   const int cc = lane < kN ? lane : 0;
   double A[kN], z = g_c, iown = 0.0;
 #pragma unroll
-  for (int r = 0; r < kN; ++r) A[r] = B[r][cc] + (r == lane ? lam : 0.0);
+  for (int r = 0; r < kN; ++r) A[r] = B[r][cc] + (r == lane ? pivot : 0.0);
   auto reciprocal = [](double d) {
     double y = __builtin_amdgcn_rcp(d);
     y = fma(fma(-d, y, 1.0), y, y);
@@ -1120,19 +1122,19 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
 
 // The trust-region subproblem: max g . p - p^T B p / 2 with |p| <= radius, one workgroup of
 // kTrWaves wavefronts per source.  Its cost is the latency of a dependent FP64 chain, so the
-// wavefronts factorise B + lam I at different multipliers at once.  lam = 0 is the solution
-// if B is positive definite and |p| <= radius; else |p(lam)| = radius, and with
-// psi(lam) = 1/|p(lam)| increasing, concave and nearly linear right of the pole, the Newton
-// points of psi = 1/radius lie left of the root (Nocedal & Wright, Algorithm 4.3) and the
-// secant through a point on either side right of it: together they bracket it ever more
-// tightly.  The next multipliers are both of them, the cubic lam(psi) through the two points'
-// values and slopes, and a point in the bracket's larger part.  What this
-// cannot certify -- no root (the hard case), or a step that lies along directions of almost
-// no gradient, where the hard case's rule decides -- goes to the eigen-decomposition below.
-// A point with |p| within 1e-7 of the radius is moved onto the boundary along dp/dlam.
+// wavefronts factorise B + lam I at different multipliers at once (trbracket.h chooses them).
+// What this cannot certify -- no root (the hard case), or a step that lies along directions of
+// almost no gradient, where the hard case's rule decides -- goes to the eigen-decomposition
+// below.  A point with |p| within 1e-7 of the radius is moved onto the boundary along dp/dlam.
+// Coordinates that are zero throughout B and g (a type weight of exactly 0 or 1 leaves the other
+// type's so) are out of the factorisations, by a unit pivot: B is singular by them alone, and
+// without them lam = 0 tells at once whether the step is inside the region, to be completed
+// among them by the eigen-decomposition, or on its boundary.
 // One factorisation and its solves take 6-7 us (2200 issue slots, a third of them lane
 // reads); three to five rounds for most sources.  The eigen-decomposition alone, one
-// wavefront: 113 us for 3 sources, 131 us for 339; this: 33 us and 70 us.
+// wavefront: 113 us for 3 sources, 131 us for 339; this: 33 us and 70 us.  Where both are
+// needed the rounds come on top: one for a decoupled interior step, four for another singular
+// one, mostly at most eight (52 us).
 //
 // Eigen-decomposition (first wavefront): one-sided (Hestenes) Jacobi on
 // W = B + c I, c = 1.001 |B|_F (positive definite, so its singular vectors are B's
@@ -1142,9 +1144,6 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double lam, do
 // -- exchange columns with one shuffle per entry, and orthogonalise each pair by the
 // rotation that diagonalises its 2x2 Gram block.  Sweeps stop when a whole sweep finds
 // every pair orthogonal to 1e-15; then lambda_k = |w_k| - c and v_k = w_k / |w_k|.
-constexpr int kTrWaves = 4;   // (the four multipliers of a round)
-constexpr int kTrRounds = 40;
-
 __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
   const int s = a.job_src ? a.job_src[blockIdx.x] : (int)blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1195,30 +1194,26 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
     return;
   }
   {
-    __shared__ double res[2][kTrWaves][3];   // a wavefront's |p| (-1: not positive definite), Newton point, |p|^2/s2
+    __shared__ double res[2][kTrWaves][3];   // a wavefront's |p| (-1: not positive definite), Newton point, multiplier
     const double g_c = lane < kN ? g[lane] : 0.0;
     const double gnorm = sqrt(wave_sum<double>(g_c * g_c));
-    // right of the root: |p(lam)| <= |g| / (lam + lmin), lmin by Gershgorin's discs; left of
-    // it: the diagonal bounds lmin from above
+    // Gershgorin's discs and the diagonal bound B's least eigenvalue
     double low = 0.0, dia = 0.0;
+    bool dec = false;   // this lane's coordinate is zero throughout
     if (lane < kN) {
       double off = 0.0;
       for (int r = 0; r < kN; ++r) off += r == lane ? 0.0 : fabs(B[r][lane]);
       low = fmax(off - B[lane][lane], 0.0);
       dia = fmax(-B[lane][lane], 0.0);
+      dec = off == 0.0 && B[lane][lane] == 0.0 && g_c == 0.0;
     }
-    double lo = wave_max(dia), hi = 1.001 * (gnorm / radius + wave_max(low));
-    // bracket: lo not right of the root, hi not left of it, near and far the best Newton and
-    // secant points; the closest points of each side with known norms (0: none)
-    // and Newton points
-    double near = lo, far = hi, ll = 0.0, nl = 0.0, tl = 0.0, nr = 0.0, tr = 0.0;
-    // the first multipliers: 0 (unless the diagonal rules it out) and fractions of |g| / radius
-    const bool zero = lo == 0.0;
-    double lam = wave == 0 && zero ? 0.0 : lo + ldexp(gnorm / radius, 2 * wave - 2 * kTrWaves + 2);
-    int winner = -1;
-    for (int round = 0; round < kTrRounds && winner < 0; ++round) {
+    TrBracket br;
+    br.start(wave_max(dia), wave_max(low), gnorm, radius, __any(dec));
+    double lam = br.first(wave);
+    int winner = TrBracket::kMore;
+    for (int round = 0; round < kTrRounds && winner == TrBracket::kMore; ++round) {
       double p, w, sums[3], np = -1.0, newton = 0.0;
-      if (ldl_solve(B, lam, g_c, radius, lane, p, w, sums)) {
+      if (ldl_solve(B, lam + (dec ? 1.0 : 0.0), g_c, radius, lane, p, w, sums)) {
         np = sqrt(sums[0]);
         newton = lam + (sums[0] / sums[1]) * (np - radius) / radius;
       }
@@ -1230,48 +1225,7 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
       }
       __syncthreads();
       // every thread draws the same conclusions from the wavefronts' results
-      double best = INFINITY;
-      int ibest = -1;
-      if (round == 0 && zero && rs[0][0] >= 0.0 && rs[0][0] <= radius) winner = 0;   // the Newton step
-      for (int w = 0; w < kTrWaves && winner < 0; ++w) {
-        const double nw = rs[w][0], lw = rs[w][2];
-        if (nw >= 0.0 && nw <= radius) {
-          if (lw <= hi) {
-            hi = lw;
-            nr = nw;
-            tr = rs[w][1];
-          }
-        } else {
-          lo = fmax(lo, lw);
-          if (nw >= 0.0 && lw >= ll) {
-            ll = lw;
-            nl = nw;
-            tl = rs[w][1];
-          }
-        }
-        if (nw >= 0.0) {
-          near = fmax(near, rs[w][1]);
-          if (fabs(nw - radius) < best) {
-            best = fabs(nw - radius);
-            ibest = w;
-          }
-        }
-      }
-      // close enough to the boundary for the first-order correction below
-      if (winner < 0 && ibest >= 0 && best <= 1e-7 * radius) winner = ibest;
-      near = fmax(near, lo);
-      far = fmin(far, hi);
-      double mid = 0.0;   // the cubic's value at psi = 1 / radius; t: its place between the points
-      if (nl > 0.0 && nr > 0.0) {
-        const double pl = 1.0 / nl, pr = 1.0 / nr, t = (1.0 / radius - pl) / (pr - pl), u = 1.0 - t;
-        far = fmin(far, ll + t * (hi - ll));
-        // slopes dlam/dt by the Newton points, (tl - ll) / t and (hi - tr) / u
-        mid = u * u * ((1.0 + 2.0 * t) * ll + (tl - ll)) + t * t * ((3.0 - 2.0 * t) * hi - (hi - tr));
-      }
-      if (winner < 0 && !(far - near > 4.0 * DBL_EPSILON * far)) {
-        if (!(hi - lo > 4.0 * DBL_EPSILON * hi)) break;   // bracket closed
-        near = lo, far = hi;   // (crossed by rounding: back to what is certain)
-      }
+      winner = br.take(round, rs);
       if (winner == wave) {
         // the step, its predicted gain g.p - p^T B p / 2 (B p = g - lam p) and norm
         const bool edge = lam > 0.0 || np > radius;
@@ -1295,15 +1249,7 @@ __global__ __launch_bounds__(64 * kTrWaves) void k_trsolve(TrArgs a) {
         if (ok && go && lane < kThetaN)
           a.theta_trial[(int64_t)s * kThetaN + lane] = a.theta[(int64_t)s * kThetaN + lane] + (lane < kN ? p : 0.0);
       }
-      if (nl > 0.0 && nr > 0.0 && near > lo) {
-        const double third = (far - near) / 3.0, half = near + 1.5 * third;
-        if (!(mid > near && mid < far)) mid = half;
-        lam = wave == 0 ? near : wave == 1 ? far : wave == 2 ? mid : mid < half ? far - third : near + third;
-      } else if (nr > 0.0) {   // nothing positive definite left of the root yet
-        lam = near + (far - near) * ldexp(1.0, -2 * wave - 1);
-      } else {                 // nothing right of it
-        lam = fmin(fmax(near, 1e-9 * far) * ldexp(1.0, 2 * wave + 1), far);
-      }
+      lam = br.next(wave);
     }
     __syncthreads();
     if (winner >= 0 && outcome != 3) return;
