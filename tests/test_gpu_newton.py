@@ -245,3 +245,39 @@ def test_step_local_objective_is_the_evaluations(fp64):
             say(f"  S={prob.n_sources} radius {radius}: accepted {int(moved.sum())}, "
                 f"largest difference {float((loc - at)[moved].abs().max()):.3e}")
             assert int(moved.sum()) > 0 and torch.equal(loc[moved], at[moved])
+
+
+@pytest.mark.parametrize("radius", [0.5, 2.0])
+def test_step_hard_case_is_reached(radius):
+    """The state of test_step_hard_case is the hard case for at least one source, and its step
+    is taken: completed to the boundary, of the oracle's model value; a source whose step is
+    not taken keeps its parameters and gets a quarter of the step's length as its radius."""
+    say(f"case: trust-region hard case reached, radius {radius}")
+    prob = tiny()
+    plan = api.Plan(api.Context(0, pixel_fp64=True, hessian_fp64=True), prob)
+    th0 = prob.theta0.copy()
+    th0[:, 2] = -800.0
+    th0 = torch.as_tensor(th0, device="cuda").contiguous()
+    api.sweep(plan, th0, n_sweeps=2, max_newton_iters=50)
+    th0 = th0.cpu().numpy()
+    th0[:, 3] += 1e-2
+    H, g, _ = (t.cpu().numpy() for t in api.elbo_hessian(plan, th0))
+    th = torch.as_tensor(th0, device="cuda").contiguous()
+    r = torch.full((prob.n_sources,), radius, dtype=torch.float64, device="cuda")
+    st, _ = api.newton_step(plan, th, r, plan.colours == 0)
+    thn, rn, stn = th.cpu().numpy(), r.cpu().numpy(), st.cpu().numpy()
+    taken = 0
+    for s in np.nonzero(plan.colours == 0)[0]:
+        po, _, hard = NW.tr_subproblem(g[s, :27], H[s], radius)
+        value = lambda p: float(g[s, :27] @ p + 0.5 * p @ H[s] @ p)
+        p = thn[s, :27] - th0[s, :27]
+        if stn[s] == _ffi.ST_ACCEPTED:
+            held = 2.0 ** -53 * float(np.abs(g[s, :27]) @ np.abs(th0[s, :27]))
+            # (theta holds a coordinate of size 800 to 1e-13)
+            assert not hard or abs(np.linalg.norm(p) - radius) <= 1e-9 * radius + 1e-12
+            assert abs(value(p) - value(po)) <= 1e-10 * abs(value(po)) + held
+            taken += hard
+        else:
+            assert stn[s] == _ffi.ST_REJECTED and np.all(p == 0)
+            assert abs(rn[s] - 0.25 * np.linalg.norm(po)) <= 1e-8 * np.linalg.norm(po)
+    assert taken > 0
