@@ -335,21 +335,23 @@ struct HessArgs {
   int64_t variant_stride;
 };
 
-// The float form is held to at most 168 VGPRs, three wavefronts per SIMD (its live set fits
-// there without spilling; at the two wavefronts that 194 VGPRs allowed the kernel stalled on
-// latency).  The double form keeps its natural allocation.
+// The float form is held to three wavefronts per SIMD (153 VGPRs, nothing spilled; at the two
+// wavefronts that 194 VGPRs allowed the kernel stalled on latency).  The double form keeps its
+// natural allocation.
 // Bound by VALU issue, about 53 slots per galaxy component and pixel (84 when each second
 // derivative had its own formula and per-component constants came by scalar loads from the
 // table; the records are now formed once per item in LDS): Hessians of 200 sources (3.7e6
-// active pixels) 397 -> 304 us per call, a Newton step of 339 sources 964 -> 775 us.
+// active pixels) 397 -> 250 us per call, a Newton step of 339 sources 964 -> 622 us.
 //
 // W = 1: one wavefront per work item.  W > 1: that many per item, a pass of 64 pixels each,
 // for launches whose items leave the chip idle; as in the pixel kernel they add to the item's
 // per-lane sums in turn, in the order of one wavefront, and the products are written out
-// fused, so that an item's sums do not depend on the launch's size.
+// fused, so that an item's sums do not depend on the launch's size.  They add to the 79 sums
+// where they are, in LDS: carried through the loop over the turns in registers they took 187
+// VGPRs (two wavefronts per SIMD) where 126 do (four); 1395 items 71 -> 53 us, 425 items 29 -> 27.
 template <typename T, int NEXP, int NDEV, int W>
 __global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void k_hess(HessArgs a) {
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 4 : 3) : 1))) void k_hess(HessArgs a) {
 #pragma clang fp contract(off)
   const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
   const int t = a.order ? a.order[pos] : pos;
@@ -363,6 +365,13 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
   // the galaxy components' records, one component per lane
   __shared__ __align__(16) T rec[kMaxPsf][2 * kMaxProf][kHRec];
   static_assert(kMaxPsf * 2 * kMaxProf <= 64, "one component per lane");
+  // (W > 1) the item's per-lane sums
+  __shared__ T chain[W > 1 ? kPrim + kHQ : 1][64];
+  __shared__ double chain_t[W > 1 ? 2 : 1][64];
+  if constexpr (W > 1) {
+    for (int u = wave; u < kPrim + kHQ; u += W) chain[u][lane] = 0;
+    if (wave < 2) chain_t[wave][lane] = 0;
+  }
   if (threadIdx.x < K * 2 * kMaxProf) {
     const T* q = &tb->gq[0][0][0] + lane * 8;
     T* r = &rec[0][0][0] + lane * kHRec;
@@ -380,13 +389,13 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
   const T w01 = w0 * w1, aa = w1, oma2 = fma((T)-2, aa, (T)1);
   double tsum = 0, town = 0;
   T G[kPrim], Q[kHQ];
-  // the per-lane sums on their way from wavefront to wavefront
-  __shared__ T chain[W > 1 ? kPrim + kHQ : 1][64];
-  __shared__ double chain_t[W > 1 ? 2 : 1][64];
 #pragma unroll
   for (int u = 0; u < kPrim; ++u) G[u] = 0;
 #pragma unroll
   for (int u = 0; u < kHQ; ++u) Q[u] = 0;
+  // what the pixels are added to
+  auto Gs = [&](int u) -> T& { return W > 1 ? chain[W > 1 ? u : 0][lane] : G[u]; };
+  auto Qs = [&](int u) -> T& { return W > 1 ? chain[W > 1 ? kPrim + u : 0][lane] : Q[u]; };
   // this lane's patch-local pixel coordinates, advanced by 64 W pixels per pass with a carry
   constexpr int step = 64 * W;
   const int step_rows = step / P.w, step_cols = step - step_rows * P.w;
@@ -447,8 +456,9 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
       T TEE = -fma((T)3 * xr * V * invE, invE, xr);
       T TEV = xr * invE;
       if (!valid) Tm = cE = cV = TEE = TEV = 0;
-      tsum += (double)Tm;
-      town += own ? (double)Tm : 0.0;
+      double &t_sum = W > 1 ? chain_t[0][lane] : tsum, &t_own = W > 1 ? chain_t[W > 1][lane] : town;
+      t_sum += (double)Tm;
+      t_own += own ? (double)Tm : 0.0;
       // The z-derivatives of E_s and V_s are the vectors g0 and g1 (g1 and h1 vanish outside the
       // centre coordinates z < 2) with weights fixed per pixel, and so is everything built of
       // them:
@@ -482,14 +492,14 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
       for (int i = 0; i < 6; ++i) {
 #pragma unroll
         for (int j = i; j < 6; ++j) {
-          T q = Q[qidx(5 + i, 5 + j)];
+          T q = Qs(qidx(5 + i, 5 + j));
           q = fma(rho0, o.h0[zidx(i, j)], q);
           q = fma(Pz[i], o.g0[j], q);
           if (i < 2 && j < 2) {
             q = fma(rho1, o.h1[i + j], q);
             q = fma(Rz[i], o.g1[j], q);
           }
-          Q[qidx(5 + i, 5 + j)] = q;
+          Qs(qidx(5 + i, 5 + j)) = q;
         }
       }
       // the amplitude coordinates u < 5 (E_u vanishes in the two variances u = 3, 4)
@@ -499,11 +509,11 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
       T av[5], cu[5];
 #pragma unroll
       for (int u = 0; u < 5; ++u) {
-        G[u] = fma(cV, Vu[u], G[u]);
+        Gs(u) = fma(cV, Vu[u], Gs(u));
         cu[u] = TEV * Vu[u];
         av[u] = cu[u];
         if (u < 3) {
-          G[u] = fma(cE, Eu[u], G[u]);
+          Gs(u) = fma(cE, Eu[u], Gs(u));
           av[u] = fma(TEE, Eu[u], cu[u]);
         }
       }
@@ -511,14 +521,14 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
       for (int u = 0; u < 5; ++u) {
 #pragma unroll
         for (int v = u; v < 5; ++v) {
-          T q = Q[qidx(u, v)];
+          T q = Qs(qidx(u, v));
           if (v < 3) q = fma(cu[u], Eu[v], q);
           if (u < 3) q = fma(Eu[u], av[v], q);
-          Q[qidx(u, v)] = q;
+          Qs(qidx(u, v)) = q;
         }
       }
       // second derivatives of E_s and V_s
-      auto add = [&](int u, int v, T x, T y) { Q[qidx(u, v)] = fma(x, y, Q[qidx(u, v)]); };
+      auto add = [&](int u, int v, T x, T y) { Qs(qidx(u, v)) = fma(x, y, Qs(qidx(u, v))); };
       const T f00 = f0 * f0, f11 = f1 * f1;
       add(0, 0, cV2, -(d * d));
       add(0, 1, cE, -f0);
@@ -559,39 +569,22 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
       t1[4] = fma(cV2, al1 * a1, t1[4]);
 #pragma unroll
       for (int j = 0; j < 6; ++j) {
-        G[5 + j] = fma(rho0, o.g0[j], G[5 + j]);
-        if (j < 2) G[5 + j] = fma(rho1, o.g1[j], G[5 + j]);
+        Gs(5 + j) = fma(rho0, o.g0[j], Gs(5 + j));
+        if (j < 2) Gs(5 + j) = fma(rho1, o.g1[j], Gs(5 + j));
 #pragma unroll
         for (int u = 0; u < 5; ++u) {
-          T q = fma(t0[u], o.g0[j], Q[qidx(u, 5 + j)]);
+          T q = fma(t0[u], o.g0[j], Qs(qidx(u, 5 + j)));
           if (j < 2) q = fma(t1[u], o.g1[j], q);
-          Q[qidx(u, 5 + j)] = q;
+          Qs(qidx(u, 5 + j)) = q;
         }
       }
     };
     if constexpr (W == 1) {
       add_pixels();
     } else {
-      // the wavefronts' turns: each takes over the sums of those before it and hands them on;
-      // every wavefront meets at the barrier after each turn
+      // the wavefronts' turns; every wavefront meets at the barrier after each
       for (int turn = 0; turn < W; ++turn) {
-        if (turn == wave) {
-          if (wave > 0 || pass > task.pix_begin) {
-#pragma unroll
-            for (int u = 0; u < kPrim; ++u) G[u] = chain[u][lane];
-#pragma unroll
-            for (int u = 0; u < kHQ; ++u) Q[u] = chain[kPrim + u][lane];
-            tsum = chain_t[0][lane];
-            town = chain_t[1][lane];
-          }
-          add_pixels();
-#pragma unroll
-          for (int u = 0; u < kPrim; ++u) chain[u][lane] = G[u];
-#pragma unroll
-          for (int u = 0; u < kHQ; ++u) chain[kPrim + u][lane] = Q[u];
-          chain_t[0][lane] = tsum;
-          chain_t[1][lane] = town;
-        }
+        if (turn == wave) add_pixels();
         __syncthreads();
       }
     }
@@ -602,7 +595,15 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W > 1 ? 2 : 3) : 1))) void 
       row += 1;
     }
   }
-  if (W > 1 && wave != W - 1) return;   // the last wavefront holds the item's sums
+  if constexpr (W > 1) {   // one wavefront stores the item's sums
+    if (wave != W - 1) return;
+#pragma unroll
+    for (int u = 0; u < kPrim; ++u) G[u] = chain[u][lane];
+#pragma unroll
+    for (int u = 0; u < kHQ; ++u) Q[u] = chain[kPrim + u][lane];
+    tsum = chain_t[0][lane];
+    town = chain_t[1][lane];
+  }
   // the slot row's 79 wavefront sums, formed together in two groups (the first 64 of the 77
   // first- and second-order sums, exchanged in the pixel precision at the first step; then
   // the two objective sums with the last 13); the lane holding a sum stores it
