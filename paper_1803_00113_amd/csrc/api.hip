@@ -1040,7 +1040,7 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   fa.variant0 = v0;
   fa.img_npsf = p->d_npsf;
   fa.cur = cur;
-  e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, grad, n_items, nv, sm);
+  e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, grad, n_items, nv, item_pixels(p), sm);
   if (e != hipSuccess) return e;
   phase_mark(p, 3, sm);
   FinalizeArgs fz;
@@ -1133,7 +1133,7 @@ static hipError_t plain_eval_t(cel_plan* p, const double* theta, hipStream_t sm)
     if (pe > pb) {
       const int tb = p->patches_h[pb].task_begin, te = p->patches_h[pe - 1].task_end;
       fa.order_offset = tb;
-      e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, true, te - tb, 1, sm);
+      e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, true, te - tb, 1, item_pixels(p), sm);
     }
     fz.src_offset = s;
     if (e == hipSuccess) e = launch_finalize(fz, 1, sm);

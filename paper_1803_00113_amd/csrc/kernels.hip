@@ -24,6 +24,7 @@
 
 #include "device.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "pixmath.h"
 
 namespace celmi {
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(64 * W)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) : 1))) void k_fused(
     FusedArgs<T> a) {
 #pragma clang fp contract(off)
-  static_assert(W == 1 || W == kFlush, "a flush after every pass of the workgroup");
+  static_assert(kWideWaves == kFlush && (W == 1 || W == kFlush), "a flush after every pass of the workgroup");
   const int v = a.variant0 + blockIdx.y;
   const int wi = a.order_offset + xcd_position((int)blockIdx.x, (int)gridDim.x);
   const int t = a.order ? a.order[wi] : wi;
@@ -1257,28 +1258,14 @@ hipError_t launch_prep_tables(const PrepArgs& a, int n_patches_launch, int n_var
   return hipGetLastError();
 }
 
-// Several wavefronts per work item while the launch's items alone would leave most of the chip
-// idle and its time is one item's latency.  Pixel kernel, one wavefront per item / four: 20
-// items 27 / 12 us, 115 items (values) 25 / 11, 3610 items 49 / 45; 12570 items 106 / 134;
-// double, 3425 items 123 / 141.  Map kernel: 20 items 12.0 / 9.1, 330 items 13.2 / 10.6; 2835
-// items 24.8 / 27.0.
-template <typename T>
-static bool wide_pixels(int64_t n_items) {
-  return n_items <= (sizeof(T) == 8 ? 512 : 4096);
-}
-template <typename T>
-static bool wide_maps(int64_t n_items) {
-  return n_items <= (sizeof(T) == 8 ? 512 : 1024);
-}
-
 template <typename T, int PPL, bool GRAD>
-static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int n_items, int n_var,
+static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int n_items, int n_var, double item_pixels,
                                  hipStream_t st) {
   dim3 grid(n_items, n_var);
   FusedArgs<T> k = a;
   k.unscale[0] = 1.0 / kExpScale;
   k.unscale[1] = 1.0 / (kExpScale * kExpScale);
-  const bool wide = wide_pixels<T>((int64_t)n_items * n_var);
+  const bool wide = wide_pixels(sizeof(T) == 8, item_pixels / (64 * PPL), (int64_t)n_items * n_var);
   if (nexp == 6 && ndev == 8) {
     if (wide) hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
     else hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, 1>), grid, dim3(64), 0, st, k);
@@ -1291,22 +1278,22 @@ static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int 
 
 template <typename T>
 hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool grad, int n_items,
-                        int n_variants, hipStream_t st) {
+                        int n_variants, double item_pixels, hipStream_t st) {
   if (n_items <= 0 || n_variants <= 0) return hipSuccess;
   switch (ppl * 2 + (grad ? 1 : 0)) {
-    case 2: return fused_dispatch<T, 1, false>(a, nexp, ndev, n_items, n_variants, st);
-    case 3: return fused_dispatch<T, 1, true>(a, nexp, ndev, n_items, n_variants, st);
-    case 4: return fused_dispatch<T, 2, false>(a, nexp, ndev, n_items, n_variants, st);
-    case 5: return fused_dispatch<T, 2, true>(a, nexp, ndev, n_items, n_variants, st);
-    case 8: return fused_dispatch<T, 4, false>(a, nexp, ndev, n_items, n_variants, st);
-    case 9: return fused_dispatch<T, 4, true>(a, nexp, ndev, n_items, n_variants, st);
+    case 2: return fused_dispatch<T, 1, false>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
+    case 3: return fused_dispatch<T, 1, true>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
+    case 4: return fused_dispatch<T, 2, false>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
+    case 5: return fused_dispatch<T, 2, true>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
+    case 8: return fused_dispatch<T, 4, false>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
+    case 9: return fused_dispatch<T, 4, true>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <typename T, int PPL>
 static void maps_dispatch(const MapArgs& a, bool std_prof, int n_items, hipStream_t st) {
-  const bool wide = PPL > 1 && wide_maps<T>(n_items);
+  const bool wide = PPL > 1 && wide_maps(sizeof(T) == 8, n_items);
   if (std_prof) {
     if (wide) hipLaunchKernelGGL((k_maps<T, PPL, 6, 8, PPL>), dim3(n_items), dim3(64 * PPL), 0, st, a);
     else hipLaunchKernelGGL((k_maps<T, PPL, 6, 8, 1>), dim3(n_items), dim3(64), 0, st, a);
@@ -1516,9 +1503,9 @@ template hipError_t launch_background<float>(const PointArgs<float>&, int, hipSt
 template hipError_t launch_background<double>(const PointArgs<double>&, int, hipStream_t);
 template hipError_t launch_point<float>(const PointArgs<float>&, int, int, int, int, hipStream_t);
 template hipError_t launch_point<double>(const PointArgs<double>&, int, int, int, int, hipStream_t);
-template hipError_t launch_fused<float>(const FusedArgs<float>&, int, int, int, bool, int, int,
+template hipError_t launch_fused<float>(const FusedArgs<float>&, int, int, int, bool, int, int, double,
                                         hipStream_t);
-template hipError_t launch_fused<double>(const FusedArgs<double>&, int, int, int, bool, int, int,
+template hipError_t launch_fused<double>(const FusedArgs<double>&, int, int, int, bool, int, int, double,
                                          hipStream_t);
 
 }  // namespace celmi

@@ -29,6 +29,7 @@
 
 #include "device.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "pixmath.h"
 #include "plan.h"
 #include "trbracket.h"
@@ -1560,18 +1561,15 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   ha.img_npsf = p->d_npsf;
   ha.cur = cur;
   ha.variant_stride = p->P;
-  // Wavefronts per item by the launch's items, measured with 1 / 4 / 8 (us): 420 items 67 / 33 /
-  // 38, 920 items 75 / 49 / 70, 1820 items 83 / 81 / 126, 3425 items 115 / 134 / 232; 115 items
-  // 74 / - / 24.  (Not the double form, whose sums alone fill a wavefront's registers.)
   const bool std_prof = p->nexp == 6 && p->ndev == 8;
   if constexpr (sizeof(T) == 4) {
-    constexpr int kItems8 = 256, kItems4 = 1536;
-    if (n_items <= kItems8) {
+    const int waves = hessian_waves(item_pixels(p) / 64, n_items);
+    if (waves == 8) {
       if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, 8>), dim3(n_items), dim3(64 * 8), 0, sm, ha);
       else hipLaunchKernelGGL((k_hess<T, 8, 8, 8>), dim3(n_items), dim3(64 * 8), 0, sm, ha);
       return hipGetLastError();
     }
-    if (n_items <= kItems4) {
+    if (waves == 4) {
       if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, 4>), dim3(n_items), dim3(64 * 4), 0, sm, ha);
       else hipLaunchKernelGGL((k_hess<T, 8, 8, 4>), dim3(n_items), dim3(64 * 4), 0, sm, ha);
       return hipGetLastError();

@@ -157,6 +157,8 @@ struct cel_plan {
 };
 
 namespace celmi {
+// mean pixels of the plan's work items
+inline double item_pixels(const cel_plan* p) { return p->n_tasks > 0 ? (double)p->n_units / (double)p->n_tasks : 0.0; }
 cel_options default_options();
 void plan_release(cel_plan* p);
 void ctx_release(cel_ctx* c);

@@ -175,3 +175,11 @@ def test_small_launch_equals_large(opts):
         res.append(out + [th[:n], r[:n], st[:n], torch.nan_to_num(loc[:n])])
     for x, y, z in zip(*res):
         assert torch.equal(x, y) and torch.equal(x, z)
+
+
+@pytest.mark.parametrize("opts", [dict(chunk_pixels=128, pixels_per_lane=1), dict(chunk_pixels=256),
+                                  dict(chunk_pixels=384, pixel_fp64=True), dict(chunk_pixels=2048, pixels_per_lane=4),
+                                  dict(pixel_fp64=True, pixels_per_lane=1, map_pixels_per_lane=8)])
+def test_small_launch_equals_large_other_items(opts):
+    """The same for items of two or three pixel groups, of many, and one pixel per lane."""
+    test_small_launch_equals_large(opts)
