@@ -250,12 +250,16 @@ cel_status cel_elbo_hessian(cel_ctx* ctx, const cel_plan* plan, const double* th
  * non-overlapping (checked against the plan: CEL_EINVAL otherwise); with the exact Hessian
  * they are stepped as one batch whatever their colour classes.  Hessian exact (as
  * cel_elbo_hessian), or with options.hessian_fd by central differences of the gradient
- * (pixel part; the KL part is always exact); the subproblem is solved
- * exactly (eigen-decomposition, boundary multiplier by a safeguarded secular-equation
- * iteration, hard case completed along the lowest eigenvector).
+ * (pixel part; the KL part is always exact).  The subproblem is solved exactly: the
+ * multiplier by factorisations of B + lambda I, B = -H, at several lambda at a time; where
+ * they give no step (B singular or indefinite and no gradient along its lowest eigenvector:
+ * the hard case, completed along that vector) by B's eigen-decomposition.  A type weight of
+ * exactly 0 or 1 makes B singular in the other type's parameters.
  * theta: DEVICE [S*32] in/out; radius: DEVICE float64 [S] in/out (trust radii);
  * step_status: DEVICE int32 [S] out (CEL_ST_*); elbo_local: DEVICE float64 [S] out or
- * NULL (L_s at the returned theta, NaN for skipped sources). */
+ * NULL (L_s at the returned theta, NaN for skipped sources): of an accepted source the
+ * number that cel_elbo_eval gives there (with hessian_fp64 over float32 pixels: to the float32
+ * rounding), of another the Hessian kernel's, the same to the pixel precision's rounding. */
 cel_status cel_newton_step(cel_ctx* ctx, const cel_plan* plan, double* theta, double* radius,
                            const uint8_t* mask, int32_t* step_status, double* elbo_local, void* stream);
 

@@ -54,7 +54,8 @@ enum Slot {
 //   sums are c and c^2 times the plain ones and are divided back once per slot row.  One
 //   component's eight values are 32 bytes, copied to LDS once per work item; the exact
 //   Hessian's kernel forms its own records from them.
-// unused: keeps the table's size, on which the static scratch buffer's limit rests
+// unused: keeps the table's size, which the static form's documented need (celmi.h) counts, so
+// that the plans it refuses stay the same
 template <typename T>
 // The records the pixel kernels read for every component (header, star records, cut radii,
 // exponent records) come first and together, so that a wavefront's scalar loads of one

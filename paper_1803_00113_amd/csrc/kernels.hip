@@ -247,9 +247,9 @@ __device__ __forceinline__ void stage_records(const Table<T>* __restrict__ tb, i
 // (a point value of the type) is not evaluated: its light enters the moments only through
 // that weight.
 template <typename T, int PPL, int NEXP, int NDEV>
-__device__ __forceinline__ void eval_values(const Table<T>* __restrict__ tb, const T (*__restrict__ rec)[2 * kMaxProf][8],
-                                            int K, const T* px, const T* py, const T* box, T* f0, T* f1,
-                                            bool with_star = true) {
+__device__ __forceinline__ void eval_values(const Table<T>* __restrict__ tb,
+                                            const T (*__restrict__ rec)[2 * kMaxProf][8], int K, const T* px,
+                                            const T* py, const T* box, T* f0, T* f1, bool with_star = true) {
 #pragma clang fp contract(off)
   T fe[PPL], fd[PPL];
 #pragma unroll
@@ -830,7 +830,7 @@ __global__ __launch_bounds__(kBackgroundThreads) void k_background(PointArgs<T> 
 // derivatives' u = P d and whose objective must equal the gradient pass's bit for bit), only
 // the candidate's own type evaluated, no neighbours, no variance term.  4 pixels per lane:
 // the components' records are read once for four pixels.  94 sources x 56 candidates
-// (1.5e6 active pixels): the call 0.72 ms through the objective's pixel kernel, 0.40 ms here.
+// (1.5e6 active pixels): the call 0.72 ms through the objective's pixel kernel, 0.38 ms here.
 template <typename T, int PPL, int NEXP, int NDEV>
 __global__ __launch_bounds__(64) void k_point(PointArgs<T> a) {
   using T2 = typename std::conditional<sizeof(T) == 8, double2, float2>::type;

@@ -751,7 +751,8 @@ __global__ __launch_bounds__(64 * kHWaves) void k_hess_finalize(HessFinArgs a) {
       thr[k] = theta[k];
       gk[k] = 0.0;
     }
-    const double kv = kl_source_wave(*a.prior, thr, source_exps(thr, lane), gk, 1.0, lane);   // every lane: gk = -grad KL
+    // (every lane: gk = -grad KL)
+    const double kv = kl_source_wave(*a.prior, thr, source_exps(thr, lane), gk, 1.0, lane);
     if (lane == 0) {
       klg[kN] = kv;
 #pragma unroll
@@ -928,7 +929,8 @@ __global__ __launch_bounds__(64 * kHWaves) void k_hess_finalize(HessFinArgs a) {
           m.QJ[r][k] = v;
         }
         if (lane < kN)
-          gsum += m.jv[lane][0] * m.Gr[m.jr[lane][0]] + m.jv[lane][1] * m.Gr[m.jr[lane][1]] + m.jv[lane][2] * m.Gr[m.jr[lane][2]];
+          gsum += m.jv[lane][0] * m.Gr[m.jr[lane][0]] + m.jv[lane][1] * m.Gr[m.jr[lane][1]] +
+                  m.jv[lane][2] * m.Gr[m.jr[lane][2]];
         wave_lds_sync();
 #pragma unroll
         for (int q6 = 0; q6 < kHPer; ++q6) {
@@ -1523,7 +1525,8 @@ __global__ __launch_bounds__(256) void k_fill_radius(double* radius, int S, doub
   const int s = blockIdx.x * 256 + threadIdx.x;
   if (s < S) radius[s] = r0;
 }
-__global__ __launch_bounds__(256) void k_set_active(uint8_t* active, uint8_t* cur, const int32_t* __restrict__ colour, int S, int c) {
+__global__ __launch_bounds__(256) void k_set_active(uint8_t* active, uint8_t* cur, const int32_t* __restrict__ colour,
+                                                    int S, int c) {
   const int s = blockIdx.x * 256 + threadIdx.x;
   if (s >= S) return;
   active[s] = colour[s] == c ? 1 : 0;
@@ -1580,8 +1583,9 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   return hipGetLastError();
 }
 
-// Analytic per-source Hessians (pixel and KL parts) of the sources flagged in `active` among `srcs` (device list, n_src entries; null = 0..S-1), with their
-// gradients and local objectives.  The base tables and maps must be current.
+// Analytic per-source Hessians (pixel and KL parts) of the sources flagged in `active` among
+// `srcs` (device list, n_src entries; null = 0..S-1), with their gradients and local objectives.
+// The base tables and maps must be current.
 static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_t* order, int n_items,
                                   const int32_t* srcs, int n_src, const uint8_t* active, double* local,
                                   double* grad, double* hess, hipStream_t sm,
@@ -1610,11 +1614,12 @@ static hipError_t enqueue_hessian(cel_plan* p, const double* theta, const int32_
   return hipGetLastError();
 }
 
-// What of the iterate's tables and neighbour moment maps a Newton iteration finds made: all of
-// them, in variant 0; or, in a sweep, the maps (none of the class's neighbours has moved since
-// they were made: once per class) and each stepped source's tables in the variant that d_cur
-// names -- the trial's tables go to its other variant, and an accepted trial's are the next
-// iterate's, which spares an iteration the rebuild (8 us of a small class's 110).
+// What of the iterate's tables and neighbour moment maps a Newton iteration finds made: nothing
+// (the difference Hessian, whose gradient pass makes them); all of them, in variant 0; or, in a
+// sweep, the maps (none of the class's neighbours has moved since they were made: once per class)
+// and each stepped source's tables in the variant that d_cur names -- the trial's tables go to its
+// other variant, and an accepted trial's are the next iterate's, which spares an iteration the
+// rebuild (8 us of a small class's 110).
 enum class Made { kNothing, kSweep, kAll };
 
 // One Newton iteration of colour class `cls` on the sources flagged in `active`; with
@@ -1627,13 +1632,9 @@ static hipError_t enqueue_newton_class(cel_plan* p, double* theta, double* radiu
   if (nsrc == 0) return hipSuccess;
   hipError_t e;
   uint8_t* cur = made == Made::kSweep ? p->d_cur : nullptr;
-  const bool analytic = !p->opt.hessian_fd;
-  if (analytic) {
-    // tables (and maps) at the iterate, then the exact Hessians with the gradients
-    e = made == Made::kNothing ? prep_base(p, theta, sm, fp64) : hipSuccess;
-    if (e == hipSuccess)
-      e = enqueue_hessian(p, theta, p->d_class_tasks[cls], (int)p->class_tasks[cls].size(), p->d_class_src[cls], nsrc,
-                          active, p->v_local, p->v_grad, p->d_hess, sm, cur);
+  if (!p->opt.hessian_fd) {   // the exact Hessians with the gradients
+    e = enqueue_hessian(p, theta, p->d_class_tasks[cls], (int)p->class_tasks[cls].size(), p->d_class_src[cls], nsrc,
+                        active, p->v_local, p->v_grad, p->d_hess, sm, cur);
   } else {
     // gradients at the iterate and at the 54 central-difference points, then the Hessians
     e = eval_any(p, theta, nullptr, 0, 2 * kParamN + 1, true, cls, active, sm, true, fp64);

@@ -251,12 +251,13 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// The value `v` of the lane whose index differs in bit OFF (1, 2, 4 or 8), by data-parallel
-// moves instead of an LDS permute.  The 4 and 8 moves reverse a group of 8 or 16 lanes: they
-// are exchanges for values that the lanes of each quad (each group of 8) already share.
+// The value `v` of the lane whose index differs in bit OFF (1, 2 or 4), by data-parallel moves
+// instead of an LDS permute.  The move for 4 reverses a group of 8 lanes: it is an exchange for
+// values that the lanes of each quad already share.
 template <int OFF>
 __device__ __forceinline__ double dpp_xor(double v) {
-  constexpr int ctrl = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;
+  static_assert(OFF == 1 || OFF == 2 || OFF == 4, "");
+  constexpr int ctrl = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : 0x141;
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xF, 0xF, true);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xF, 0xF, true);
   return __hiloint2double(hi, lo);
