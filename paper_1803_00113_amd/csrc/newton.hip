@@ -1138,7 +1138,7 @@ __device__ __forceinline__ bool ldl_solve(const double (*B)[kLd], double pivot, 
 // reads); three to five rounds for most sources.  The eigen-decomposition alone, one
 // wavefront: 113 us for 3 sources, 131 us for 339; this: 33 us and 70 us.  Where both are
 // needed the rounds come on top: one for a decoupled interior step, four for another singular
-// one, mostly at most eight (52 us).
+// one, at most twelve (78 us) for most others.
 //
 // Eigen-decomposition (first wavefront): one-sided (Hestenes) Jacobi on
 // W = B + c I, c = 1.001 |B|_F (positive definite, so its singular vectors are B's

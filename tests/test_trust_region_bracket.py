@@ -7,8 +7,8 @@ multipliers at a time: the number of rounds, and what it ends with.
   * where there is no multiplier (B singular or indefinite, no gradient along the least
     eigenvalue's direction, and a short step in the others), the search gives up: in the first
     round if B and the gradient vanish in whole coordinates (a type weight of exactly 0 or 1),
-    by the fifth if B is singular, and in any case before half of an eigen-decomposition's time
-    (8 of 17 rounds) has gone, or, with rounding in the gradient's place, all of it."""
+    by the fifth if B is singular, and in any case before an eigen-decomposition's time (17
+    rounds) has gone."""
 import ctypes as C
 import os
 import shutil
@@ -132,7 +132,7 @@ def test_hard_case(lib, seed, least):
     if got >= 0:   # (rounding left a gradient along the direction: a step of almost no curvature)
         d = np.linalg.eigvalsh(B).min() + lam_w
         assert d <= 1e-6 * np.linalg.norm(g)
-    assert rounds <= (5 if least == 0.0 else 8 if got < 0 else 16)
+    assert rounds <= (5 if least == 0.0 else 12 if got < 0 else 16)
 
 
 @pytest.mark.parametrize("seed", range(20))
@@ -150,7 +150,7 @@ def test_ordinary_steps(lib, seed):
     for radius in (1e-3, 1.0, 1e3):
         rounds, got, m = search(lib, B, g, radius)
         if got < 0:   # given up: only where the root is next to the pole
-            assert rounds == 8 and lam.min() < 0 and norm(-lam.min() + 1e-4 * np.abs(lam).max()) <= radius
+            assert rounds == 12 and lam.min() < 0 and norm(-lam.min() + 1e-4 * np.abs(lam).max()) <= radius
         elif lam.min() > 0 and norm(0.0) <= radius:
             assert rounds == 1 and m == 0.0
         else:
