@@ -274,3 +274,18 @@ def test_sources_of_many_patches(epochs):
     check(prob, tot, loc, g, o_tot, o_loc, o_g)
     _, tot, loc, g = run(prob, pixel_fp64=True)
     check(prob, tot, loc, g, o_tot, o_loc, o_g, rtol_e=1e-10, rtol_g=1e-8)
+
+
+@pytest.mark.parametrize("epochs,side,chunk", [(1, 24, 64), (2, 12, 64), (2, 30, 64), (6, 24, 64), (13, 16, 64), (13, 16, 512)])
+def test_finalisation_of_patches_and_items(epochs, side, chunk):
+    """Sources of 5 to 65 patches of 1 to 15 work items: the finalisation sums a patch's items
+    by lanes or by groups of lanes, by how many there are of either."""
+    say(f"case: {5 * epochs} patches of side {side}, {chunk}-pixel items")
+    prob = gen._grouped(f"items_{epochs}_{side}", 190 + epochs, 3, side, side + 3, epochs, "powerlaw")
+    o_tot, o_loc, o_g = E.elbo_total_and_grad(E.Model(prob), prob.theta0)
+    plan, tot, loc, g = run(prob, chunk_pixels=chunk)
+    check(prob, tot, loc, g, o_tot, o_loc, o_g)
+    t, l = api.elbo_eval(plan, prob.theta0)
+    assert t.item() == tot and np.array_equal(l.cpu().numpy(), loc)
+    _, tot, loc, g = run(prob, chunk_pixels=chunk, pixel_fp64=True)
+    check(prob, tot, loc, g, o_tot, o_loc, o_g, rtol_e=1e-10, rtol_g=1e-8)
