@@ -201,12 +201,12 @@ __global__ __launch_bounds__(kPsfThreads) void k_psf_fit(PsfFitArgs a) {
       if (!(tot > 0.0)) continue;
       // the responsibilities comp / tot (at most 1) times the knot's weight, by one quotient
       // weight / tot unless that (or 1 / tot) leaves the range
-      const double s = wts[p];
-      double t = s * reciprocal(tot);
+      double t = wts[p] * reciprocal(tot);
       if (!(t <= 1e300)) {
+        t = reciprocal(tot * 0x1p600);
 #pragma unroll
-        for (int k = 0; k < K; ++k) comp[k] = comp[k] / tot * s;
-        t = 1.0;
+        for (int k = 0; k < K; ++k) comp[k] = comp[k] * 0x1p600 * t;
+        t = wts[p];
       }
 #pragma unroll
       for (int k = 0; k < K; ++k) {
