@@ -570,7 +570,7 @@ __global__ __launch_bounds__(64) void k_maps_runs(MapArgs a) {
 constexpr int kFlush = 4;   // pixel groups between flushes of the per-lane sums
 template <typename T, int PPL, bool GRAD, int NEXP, int NDEV, int W>
 __global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) : 1))) void k_fused(
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? 6 : 1))) void k_fused(
     FusedArgs<T> a) {
 #pragma clang fp contract(off)
   static_assert(kWideWaves == kFlush && (W == 1 || W == kFlush), "a flush after every pass of the workgroup");
@@ -601,23 +601,34 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
 #pragma unroll
   for (int q = 0; q < S_T; ++q) part[q] = (T)0;
   double* out = a.slots + (int64_t)blockIdx.y * a.slot_variant_stride + (int64_t)t * kSlots;
-  // patch-local coordinates of this lane's pixels, advanced by 64*PPL*W pixels per pass:
-  // one integer division at the start, then a carry
+  // patch-local coordinates of this lane's pixels: one integer division at the start, then
+  // advanced by 64*PPL pixels per group with a carry (W > 1: a division per pass, so that the
+  // wavefronts' turns need not carry them along)
   const int group_px = 64 * PPL, step = group_px * W;
   const int step_rows = step / P.w, step_cols = step - step_rows * P.w;
   T px[PPL], py[PPL];
+  auto store_objective = [&] {
+    const double acc[2] = {acc_t, acc_own};
+    const double s_t = wave_sums<2>(acc, lane);   // lane 0: the pixel term, lane 32: the owned part
+    const int tslot = wave_sums_slot<2>(lane);
+    if (tslot >= 0) out[S_T + tslot] = s_t;
+  };
+  auto coordinates = [&](int base) {
 #pragma unroll
-  for (int i = 0; i < PPL; ++i) {
-    const int idx = task.pix_begin + wave * group_px + i * 64 + lane;
-    const int row = idx / P.w;
-    px[i] = (T)(idx - row * P.w);
-    py[i] = (T)row;
-  }
+    for (int i = 0; i < PPL; ++i) {
+      const int idx = base + i * 64 + lane;
+      const int row = idx / P.w;
+      px[i] = (T)(idx - row * P.w);
+      py[i] = (T)row;
+    }
+  };
+  if constexpr (W == 1) coordinates(task.pix_begin);
   const T wT = (T)P.w, srT = (T)step_rows, scT = (T)step_cols;
   int group = 0;
 
   for (int pass = task.pix_begin; pass < task.pix_end; pass += step, ++group) {
     const int base = pass + wave * group_px;   // (W > 1: past the item's end for its last wavefronts)
+    if constexpr (W > 1) coordinates(base);
     T xv[PPL], sky[PPL];
     bool valid[PPL];
 #pragma unroll
@@ -693,103 +704,126 @@ __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && PPL < 4 ? (W > 1 ? 4 : 6) :
         }
       }
     }
-    // the wavefronts' turns (W = 1: one): each takes over the sums of those before it and hands
-    // them on; every wavefront meets at the barrier after each turn
-    for (int turn = 0; turn < W; ++turn) {
-      if (turn == wave) {
-        if constexpr (W > 1) {
-          if (GRAD)
+    // pixel term (centred: the data constant x log x - x - log x! is added per patch in FP64) and
+    // adjoint coefficients
+    struct Terms {
+      T Tm, cE, cVf0, cVf1, rho0, rho1, g0x, g0y, s0xx, s0xy, s0yy, df;
+    };
+    auto terms = [&](int i) {
+      Terms t;
+      const T x = xv[i];
+      const T invE = frcp<T>(E[i]);
+      const T xr = x * invE * invE;
+      t.Tm = fma((T)-0.5 * xr, V[i], (x > (T)0 ? x_log_ratio<T>(x, E[i]) : (T)0) - (E[i] - x));
+      if (!valid[i]) t.Tm = (T)0;
+      if (GRAD) {
+        t.cE = fma(xr * invE, V[i], (x - E[i]) * invE);
+        T cV = (T)-0.5 * xr;
+        if (!valid[i]) t.cE = cV = (T)0;
+        const T cV2 = (T)2 * cV, omp = (T)1 - pi, wd = w01 * d[i];
+        t.rho0 = fma(t.cE * w0, L0, cV2 * fma(k0, f0[i], wd * L0));
+        t.rho1 = fma(t.cE * w1, L1, cV2 * fma(k1, f1[i], -(wd * L1)));
+        t.g0x = fma(pi, o.gdx[i], omp * o.gex[i]);
+        t.g0y = fma(pi, o.gdy[i], omp * o.gey[i]);
+        t.s0xx = fma(pi, o.sdxx[i], omp * o.sexx[i]);
+        t.s0xy = (T)2 * fma(pi, o.sdxy[i], omp * o.sexy[i]);
+        t.s0yy = fma(pi, o.sdyy[i], omp * o.seyy[i]);
+        t.cVf0 = cV * f0[i];
+        t.cVf1 = cV * f1[i];
+        t.df = o.fd[i] - o.fe[i];
+      }
+      return t;
+    };
+    auto add = [&](int i, const Terms& t) {
+      acc_t += (double)t.Tm;
+      acc_own += own[i] ? (double)t.Tm : 0.0;
+      if (GRAD) {
+        part[S_CE_F0] = fma(t.cE, f0[i], part[S_CE_F0]);
+        part[S_CE_F1] = fma(t.cE, f1[i], part[S_CE_F1]);
+        part[S_CV_F00] = fma(t.cVf0, f0[i], part[S_CV_F00]);
+        part[S_CV_F11] = fma(t.cVf1, f1[i], part[S_CV_F11]);
+        part[S_CV_F01] = fma(t.cVf0, f1[i], part[S_CV_F01]);
+        part[S_MU_X] = fma(t.rho0, t.g0x, fma(t.rho1, o.g1x[i], part[S_MU_X]));
+        part[S_MU_Y] = fma(t.rho0, t.g0y, fma(t.rho1, o.g1y[i], part[S_MU_Y]));
+        part[S_S_XX] = fma(t.rho0, t.s0xx, part[S_S_XX]);
+        part[S_S_XY] = fma(t.rho0, t.s0xy, part[S_S_XY]);
+        part[S_S_YY] = fma(t.rho0, t.s0yy, part[S_S_YY]);
+        part[S_PI] = fma(t.rho0, t.df, part[S_PI]);
+      }
+    };
+    // flush of the per-lane sums: the 11 wavefront sums together, then lane 0 reads each from the
+    // lane holding it and stores it scaled back (the centre sums carry the records' scale c, the
+    // covariance sums c^2); no per-lane slot index or address lives across the pixel loop
+    auto flush = [&](bool first) {
+      const double sq = wave_sums<S_T, 32, T>(part, lane);
+      // (the factors come with the kernel arguments, in scalar registers: no vector registers
+      // hold them across the pixel loop)
+      const double* unscale = a.unscale;
 #pragma unroll
-            for (int q = 0; q < S_T; ++q) part[q] = wave > 0 ? chain[q][lane] : (T)0;
-          acc_t = wave > 0 || group > 0 ? chain_t[0][lane] : 0.0;
-          acc_own = wave > 0 || group > 0 ? chain_t[1][lane] : 0.0;
-        }
-        // pixel term (centred: the data constant x log x - x - log x! is added per patch in
-        // FP64) and adjoint coefficients
+      for (int q = 0; q < S_T; ++q) {
+        part[q] = (T)0;
+        const double s = read_lane(sq, wave_sums_lane<S_T>(q));
+        const double v = (q == S_MU_X || q == S_MU_Y) ? s * unscale[0]
+                         : (q == S_S_XX || q == S_S_XY || q == S_S_YY) ? s * unscale[1] : s;
+        if (lane == 0) out[q] = first ? v : out[q] + v;
+      }
+    };
+    if constexpr (W == 1) {
 #pragma unroll
-        for (int i = 0; i < PPL; ++i) {
-          const T x = xv[i];
-          const T invE = frcp<T>(E[i]);
-          const T xr = x * invE * invE;
-          T Tm = fma((T)-0.5 * xr, V[i], (x > (T)0 ? x_log_ratio<T>(x, E[i]) : (T)0) - (E[i] - x));
-          if (!valid[i]) Tm = (T)0;
-          acc_t += (double)Tm;
-          acc_own += own[i] ? (double)Tm : 0.0;
-          if (GRAD) {
-            T cE = fma(xr * invE, V[i], (x - E[i]) * invE);
-            T cV = (T)-0.5 * xr;
-            if (!valid[i]) cE = cV = (T)0;
-            const T cV2 = (T)2 * cV, omp = (T)1 - pi, wd = w01 * d[i];
-            const T rho0 = fma(cE * w0, L0, cV2 * fma(k0, f0[i], wd * L0));
-            const T rho1 = fma(cE * w1, L1, cV2 * fma(k1, f1[i], -(wd * L1)));
-            const T g0x = fma(pi, o.gdx[i], omp * o.gex[i]), g0y = fma(pi, o.gdy[i], omp * o.gey[i]);
-            const T s0xx = fma(pi, o.sdxx[i], omp * o.sexx[i]);
-            const T s0xy = (T)2 * fma(pi, o.sdxy[i], omp * o.sexy[i]);
-            const T s0yy = fma(pi, o.sdyy[i], omp * o.seyy[i]);
-            const T cVf0 = cV * f0[i], cVf1 = cV * f1[i];
-            part[S_CE_F0] = fma(cE, f0[i], part[S_CE_F0]);
-            part[S_CE_F1] = fma(cE, f1[i], part[S_CE_F1]);
-            part[S_CV_F00] = fma(cVf0, f0[i], part[S_CV_F00]);
-            part[S_CV_F11] = fma(cVf1, f1[i], part[S_CV_F11]);
-            part[S_CV_F01] = fma(cVf0, f1[i], part[S_CV_F01]);
-            part[S_MU_X] = fma(rho0, g0x, fma(rho1, o.g1x[i], part[S_MU_X]));
-            part[S_MU_Y] = fma(rho0, g0y, fma(rho1, o.g1y[i], part[S_MU_Y]));
-            part[S_S_XX] = fma(rho0, s0xx, part[S_S_XX]);
-            part[S_S_XY] = fma(rho0, s0xy, part[S_S_XY]);
-            part[S_S_YY] = fma(rho0, s0yy, part[S_S_YY]);
-            part[S_PI] = fma(rho0, o.fd[i] - o.fe[i], part[S_PI]);
+      for (int i = 0; i < PPL; ++i) add(i, terms(i));
+      if (GRAD && (group % kFlush == kFlush - 1 || base + step >= task.pix_end)) flush(group < kFlush);
+    } else {
+      // the wavefronts' turns: each takes over the sums of those before it and hands them on, the
+      // last flushes them; every wavefront meets at the barrier after each turn
+      Terms t[PPL];
+#pragma unroll
+      for (int i = 0; i < PPL; ++i) t[i] = terms(i);
+#pragma unroll 1
+      for (int turn = 0; turn < W; ++turn) {
+        if (turn == wave) {
+          if (GRAD) {   // (the first starts from zeros: the last one's flush took the sums)
+            if (wave > 0) {
+#pragma unroll
+              for (int q = 0; q < S_T; ++q) part[q] = chain[q][lane];
+            } else {
+#pragma unroll
+              for (int q = 0; q < S_T; ++q) part[q] = (T)0;
+            }
           }
-        }
-        if constexpr (W > 1) {
-          if (GRAD)
+          if (wave > 0 || group > 0) {
+            acc_t = chain_t[0][lane];
+            acc_own = chain_t[1][lane];
+          }
 #pragma unroll
-            for (int q = 0; q < S_T; ++q) chain[q][lane] = part[q];
+          for (int i = 0; i < PPL; ++i) add(i, t[i]);
           chain_t[0][lane] = acc_t;
           chain_t[1][lane] = acc_own;
-        }
-        // flush: after kFlush groups or the item's last (W > 1: by the last wavefront)
-        if (GRAD && (W > 1 ? wave == W - 1 : group % kFlush == kFlush - 1 || base + step >= task.pix_end)) {
-          const bool first = W > 1 ? group == 0 : group < kFlush;
-          // the 11 wavefront sums together, then lane 0 reads each from the lane holding it and
-          // stores it scaled back (the centre sums carry the records' scale c, the covariance
-          // sums c^2); no per-lane slot index or address lives across the pixel loop
-          const double sq = wave_sums<S_T, 32, T>(part, lane);
-          // (the factors come with the kernel arguments, in scalar registers: no vector registers
-          // hold them across the pixel loop)
-          const double* unscale = a.unscale;
+          if (wave == W - 1) {
+            if (GRAD) flush(group == 0);
+            if (pass + step >= task.pix_end) store_objective();
+          } else if (GRAD) {
 #pragma unroll
-          for (int q = 0; q < S_T; ++q) {
-            part[q] = (T)0;
-            const double s = read_lane(sq, wave_sums_lane<S_T>(q));
-            const double v = (q == S_MU_X || q == S_MU_Y) ? s * unscale[0]
-                             : (q == S_S_XX || q == S_S_XY || q == S_S_YY) ? s * unscale[1] : s;
-            if (lane == 0) out[q] = first ? v : out[q] + v;
+            for (int q = 0; q < S_T; ++q) chain[q][lane] = part[q];
           }
         }
+        __syncthreads();
       }
-      if constexpr (W > 1) __syncthreads();
     }
-    // next group: advance each lane's coordinates by step pixels
+    if constexpr (W == 1) {   // next group: advance each lane's coordinates by step pixels
 #pragma unroll
-    for (int i = 0; i < PPL; ++i) {
-      T c = px[i] + scT, r = py[i] + srT;
-      if (c >= wT) {
-        c -= wT;
-        r += (T)1;
+      for (int i = 0; i < PPL; ++i) {
+        T c = px[i] + scT, r = py[i] + srT;
+        if (c >= wT) {
+          c -= wT;
+          r += (T)1;
+        }
+        px[i] = c;
+        py[i] = r;
       }
-      px[i] = c;
-      py[i] = r;
     }
   }
-  if constexpr (W > 1) {
-    if (wave != W - 1) return;
-    acc_t = group > 0 ? chain_t[0][lane] : 0.0;
-    acc_own = group > 0 ? chain_t[1][lane] : 0.0;
-  }
-  const double acc[2] = {acc_t, acc_own};
-  const double s_t = wave_sums<2>(acc, lane);   // lane 0: the pixel term, lane 32: the owned part
-  const int tslot = wave_sums_slot<2>(lane);
-  if (tslot >= 0) out[S_T + tslot] = s_t;
+  if (W > 1 && (group > 0 || wave != W - 1)) return;
+  store_objective();
   if (GRAD && task.pix_begin >= task.pix_end && lane == 0)
     for (int q = 0; q < S_T; ++q) out[q] = 0.0;
 }
