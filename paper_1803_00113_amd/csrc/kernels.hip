@@ -1011,12 +1011,13 @@ __global__ __launch_bounds__(128) void k_finalize(FinalizeArgs a) {
       // The patches' slot sums over their work items (contiguous: patch after patch).  With few
       // items per patch a lane sums its own patch's, one item's 13 loads after another's; else
       // lane 16 g + q takes slot q of every fourth patch, two patches and four items' loads at a
-      // time.  A round of the one costs two thirds of a round of the other.  The numbers are the
+      // time.  A round of the one costs two thirds of a round of the other, so the lanes have it
+      // from 17 patches on, and below that while a patch has few items.  The numbers are the
       // same.  Gradient, lanes / groups: 75 patches of 1 item 8.7 / 13.0 us, of 5 items 13.2 / 17.7,
       // 30 of 11 items 12.7 / 13.5, 5 of 12 items 13.5 (the lane form of an earlier kernel) / 9.2.
       const int np = min(pend - pb, 64), items = a.patches[pb + np - 1].task_end - a.patches[pb].task_begin;
-      const int mean = (items + np - 1) / np;
-      if (2 * mean <= 3 * ((np + 7) / 8) * ((mean + 3) / 4)) {
+      const int rounds = (np + 7) / 8;
+      if (rounds > 2 || 2 * items <= 3 * rounds * np) {
         const int p = min(pb + lane, pend - 1), t1 = a.patches[p].task_end;
         auto add = [&](auto first) {
           constexpr int Q = decltype(first)::value;
