@@ -12,6 +12,7 @@
 
 #include "device.h"
 #include "kernels.h"
+#include "launch_rules.h"
 #include "plan.h"
 
 using namespace celmi;
@@ -633,9 +634,11 @@ cel_status build_tiling(cel_plan* p) {
   p->tasks_h.reserve(n_items);
   std::vector<uint64_t> keys;
   keys.reserve(n_items);
+  for (int64_t& g : p->n_groups) g = 0;
   for (int i = 0; i < p->P; ++i) {
     DPatch& d = p->patches_h[i];
     const int n = d.w * d.h;
+    for (int k = 0; k < 3; ++k) p->n_groups[k] += patch_groups(n, CH, 64 << k);
     d.task_begin = (int)p->tasks_h.size();
     for (int b = 0; b < n; b += CH) {
       DTask t;
@@ -1040,7 +1043,8 @@ static hipError_t enqueue_eval(cel_plan* p, const double* theta, const double* t
   fa.variant0 = v0;
   fa.img_npsf = p->d_npsf;
   fa.cur = cur;
-  e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, grad, n_items, nv, item_pixels(p), sm);
+  e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, grad, n_items, nv,
+                      item_groups(p, p->opt.pixels_per_lane), sm);
   if (e != hipSuccess) return e;
   phase_mark(p, 3, sm);
   FinalizeArgs fz;
@@ -1133,7 +1137,8 @@ static hipError_t plain_eval_t(cel_plan* p, const double* theta, hipStream_t sm)
     if (pe > pb) {
       const int tb = p->patches_h[pb].task_begin, te = p->patches_h[pe - 1].task_end;
       fa.order_offset = tb;
-      e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, true, te - tb, 1, item_pixels(p), sm);
+      e = launch_fused<T>(fa, p->nexp, p->ndev, p->opt.pixels_per_lane, true, te - tb, 1,
+                          item_groups(p, p->opt.pixels_per_lane), sm);
     }
     fz.src_offset = s;
     if (e == hipSuccess) e = launch_finalize(fz, 1, sm);

@@ -225,6 +225,7 @@ extern "C" cel_status cel_plan_append(cel_ctx* ctx, cel_plan* p, const cel_probl
   p->P += q->P;
   p->n_units += q->n_units;
   p->n_tasks += q->n_tasks;
+  for (int k = 0; k < 3; ++k) p->n_groups[k] += q->n_groups[k];
   p->n_colours = C1;
   const int S = p->S, N = p->N, P = p->P;
   const int64_t U = p->n_units, T = p->n_tasks;

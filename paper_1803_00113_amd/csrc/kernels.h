@@ -61,7 +61,7 @@ template <typename T>
 hipError_t launch_prep_tables(const PrepArgs& a, int n_patches_launch, int n_variants, hipStream_t st);
 template <typename T>
 hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool grad, int n_items,
-                        int n_variants, double item_pixels, hipStream_t st);   // item_pixels: the plan's mean
+                        int n_variants, double item_groups, hipStream_t st);   // item_groups: the plan's mean
 template <typename T>
 hipError_t launch_maps(const MapArgs& a, int nexp, int ndev, int ppl, int n_items, hipStream_t st);
 // point likelihood: the pixels' rate without their own source (once per fixed point), the

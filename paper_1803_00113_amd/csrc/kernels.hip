@@ -1317,13 +1317,13 @@ hipError_t launch_prep_tables(const PrepArgs& a, int n_patches_launch, int n_var
 }
 
 template <typename T, int PPL, bool GRAD>
-static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int n_items, int n_var, double item_pixels,
+static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int n_items, int n_var, double item_groups,
                                  hipStream_t st) {
   dim3 grid(n_items, n_var);
   FusedArgs<T> k = a;
   k.unscale[0] = 1.0 / kExpScale;
   k.unscale[1] = 1.0 / (kExpScale * kExpScale);
-  const bool wide = wide_pixels(sizeof(T) == 8, item_pixels / (64 * PPL), (int64_t)n_items * n_var);
+  const bool wide = wide_pixels(sizeof(T) == 8, item_groups, (int64_t)n_items * n_var);
   if (nexp == 6 && ndev == 8) {
     if (wide) hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, kFlush>), grid, dim3(64 * kFlush), 0, st, k);
     else hipLaunchKernelGGL((k_fused<T, PPL, GRAD, 6, 8, 1>), grid, dim3(64), 0, st, k);
@@ -1336,15 +1336,15 @@ static hipError_t fused_dispatch(const FusedArgs<T>& a, int nexp, int ndev, int 
 
 template <typename T>
 hipError_t launch_fused(const FusedArgs<T>& a, int nexp, int ndev, int ppl, bool grad, int n_items,
-                        int n_variants, double item_pixels, hipStream_t st) {
+                        int n_variants, double item_groups, hipStream_t st) {
   if (n_items <= 0 || n_variants <= 0) return hipSuccess;
   switch (ppl * 2 + (grad ? 1 : 0)) {
-    case 2: return fused_dispatch<T, 1, false>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
-    case 3: return fused_dispatch<T, 1, true>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
-    case 4: return fused_dispatch<T, 2, false>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
-    case 5: return fused_dispatch<T, 2, true>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
-    case 8: return fused_dispatch<T, 4, false>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
-    case 9: return fused_dispatch<T, 4, true>(a, nexp, ndev, n_items, n_variants, item_pixels, st);
+    case 2: return fused_dispatch<T, 1, false>(a, nexp, ndev, n_items, n_variants, item_groups, st);
+    case 3: return fused_dispatch<T, 1, true>(a, nexp, ndev, n_items, n_variants, item_groups, st);
+    case 4: return fused_dispatch<T, 2, false>(a, nexp, ndev, n_items, n_variants, item_groups, st);
+    case 5: return fused_dispatch<T, 2, true>(a, nexp, ndev, n_items, n_variants, item_groups, st);
+    case 8: return fused_dispatch<T, 4, false>(a, nexp, ndev, n_items, n_variants, item_groups, st);
+    case 9: return fused_dispatch<T, 4, true>(a, nexp, ndev, n_items, n_variants, item_groups, st);
     default: return hipErrorInvalidValue;
   }
 }

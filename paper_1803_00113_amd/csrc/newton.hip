@@ -1566,7 +1566,7 @@ static hipError_t launch_hess_t(cel_plan* p, const int32_t* order, int n_items, 
   ha.variant_stride = p->P;
   const bool std_prof = p->nexp == 6 && p->ndev == 8;
   if constexpr (sizeof(T) == 4) {
-    const int waves = hessian_waves(item_pixels(p) / 64, n_items);
+    const int waves = hessian_waves(item_groups(p, 1), n_items);
     if (waves == 8) {
       if (std_prof) hipLaunchKernelGGL((k_hess<T, 6, 8, 8>), dim3(n_items), dim3(64 * 8), 0, sm, ha);
       else hipLaunchKernelGGL((k_hess<T, 8, 8, 8>), dim3(n_items), dim3(64 * 8), 0, sm, ha);

@@ -43,6 +43,7 @@ struct cel_plan {
   cel_options opt;
   int S = 0, N = 0, P = 0;
   int64_t n_units = 0, n_tasks = 0;
+  int64_t n_groups[3] = {0, 0, 0};   // pixel groups of the work items, of 64, 128 and 256 pixels
   // sizes the per-call scratch is allocated for (>= S, P, n_tasks, n_units; grown by
   // cel_plan_append), and the element capacity of each persistent device array that an
   // append may grow, by the address of its pointer field (absent: exactly its count)
@@ -157,8 +158,10 @@ struct cel_plan {
 };
 
 namespace celmi {
-// mean pixels of the plan's work items
-inline double item_pixels(const cel_plan* p) { return p->n_tasks > 0 ? (double)p->n_units / (double)p->n_tasks : 0.0; }
+// mean pixel groups of 64, 128 or 256 pixels (pixels_per_lane 1, 2, 4) in the plan's work items
+inline double item_groups(const cel_plan* p, int pixels_per_lane) {
+  return p->n_tasks > 0 ? (double)p->n_groups[pixels_per_lane / 2] / (double)p->n_tasks : 0.0;
+}
 cel_options default_options();
 void plan_release(cel_plan* p);
 void ctx_release(cel_ctx* c);

@@ -17,6 +17,7 @@ extern "C" {
 int pixels(int fp64, double groups, long n) { return celmi::wide_pixels(fp64, groups, n) ? celmi::kWideWaves : 1; }
 int maps(int fp64, long n) { return celmi::wide_maps(fp64, n); }
 int hessian(double passes, long n) { return celmi::hessian_waves(passes, n); }
+long groups(long n, long item, long group) { return celmi::patch_groups(n, item, group); }
 }
 """
 
@@ -33,6 +34,8 @@ def rules(tmp_path_factory):
     l.pixels.argtypes = [C.c_int, C.c_double, C.c_long]
     l.maps.argtypes = [C.c_int, C.c_long]
     l.hessian.argtypes = [C.c_double, C.c_long]
+    l.groups.argtypes = [C.c_long, C.c_long, C.c_long]
+    l.groups.restype = C.c_long
     return l
 
 
@@ -61,3 +64,16 @@ def test_measured_sizes(rules):
                              (12.0, 185, 8), (12.0, 725, 4), (12.0, 3110, 4)]:
         assert rules.hessian(passes, n) == waves, (passes, n)
     assert rules.maps(0, 20) and not rules.maps(0, 5850) and rules.maps(1, 465) and not rules.maps(1, 2395)
+
+
+@pytest.mark.parametrize("item", [64, 100, 128, 200, 512, 1024])
+@pytest.mark.parametrize("group", [64, 128, 256])
+def test_groups_are_counted_whole(rules, item, group):
+    for n in (1, 63, 64, 65, 99, 128, 144, 200, 201, 512, 700, 1024, 2049):
+        assert rules.groups(n, item, group) == sum(-(-min(item, n - b) // group) for b in range(0, n, item)), n
+
+
+def test_items_of_a_group_and_a_bit(rules):
+    """144 pixels are two passes of 128: 40 sources' 250 items in double precision (25.5 us by one
+    wavefront, 16.9 by several) get several"""
+    assert rules.pixels(1, rules.groups(144, 512, 128), 250) > 1
