@@ -31,7 +31,7 @@ FLOP_OWN = 1368 + 47          # FP arithmetic + transcendentals (45 exp, 1 log, 
 # component 16 + exp (42 galaxy and 3 star components)
 FLOP_OWN_FIXED = 104
 FLOP_PER_COMPONENT = (42 * 30 + 3 * 17) / 45
-VALU_LANE_RATE = 1024 * 16 * 2.4e9   # SIMDs x lanes per cycle x clock: one VALU op per lane
+VALU_LANE_RATE = 1024 * 16 * 2.4e9   # SIMDs x lanes per cycle x clock: a multiply-add's issue rate
 FLOP_PAIR = 2
 FLOP_MAP = 348 + 45
 BYTES_UNIT = 8                # (count, sky) pair per active pixel read by the pixel kernel
@@ -123,7 +123,8 @@ def executed_work(units, pairs, kernel_ms, achieved):
     cut leaves (transcendentals per pixel - 2) of the 45 components evaluated per pixel
     (counter profile); `achieved` / `frac` of the roofline count all 45 (the method's work),
     these count the evaluated ones.  valu_issue_frac: measured VALU lane-instructions per
-    second over one VALU operation per lane per cycle on every SIMD."""
+    second over the rate at which multiply-adds issue (4 cycles of a SIMD for 64 lanes); additions,
+    products and moves issue faster, so it may pass 1."""
     c = counted_valu()
     if c is None:
         return None
